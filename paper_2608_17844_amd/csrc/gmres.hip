@@ -312,22 +312,37 @@ __global__ __launch_bounds__(NW * 64) void arnoldi_kernel(const TB* __restrict__
 }
 
 // ------------------------------------------------------------------ delayed reorthogonalisation (DCGS2)
-constexpr int kDotRows = 16;   // rows of u and w staged in LDS per step of the dot sweep
+constexpr int kDotRows = 8;   // rows of u and w staged in LDS per step of the dot sweep
 
 // Dot sweep: with u the candidate (slot k) and w = A u (slot k+1),
 //   s_i = V_i^H u, z_i = V_i^H w (i < k), alpha = u^H u, beta = u^H w.
 // Partials per chunk: [s_0..s_{k-1}, z_0..z_{k-1}, alpha, beta].  One launch
 // covers the vectors i0 .. i0+nv-1 (the sweep may be split into launches of at
 // most NW*G vectors); alpha and beta come from the launch with i0 = 0.
-template <typename TB, typename TV, int NW, int G, int RPL, bool HASW>
+//
+// Every wave of the workgroup needs the same rows of u and w: they are staged in
+// LDS kDotRows rows at a time by all threads, so each value is read from memory
+// once per workgroup (waves reading them independently drift apart over the
+// chunk and re-fetch lines that the basis stream has evicted).  The next rows
+// are fetched into registers while the staged ones are used, into the other
+// half of the stage.  A wave loads RU rows of its G vectors before it uses any:
+// RU * G loads in flight cover the memory latency, which bounds the sweep when
+// a short batch leaves few workgroups on the chip.
+template <typename TB, typename TV, int NW, int G, int RPL, bool HASW, int RU>
 __global__ __launch_bounds__(NW * 64, (std::is_same<TV, p24x2>::value && G <= 4 ? 4 : 1)) void dcgs2_dots_kernel(const TV* __restrict__ V, int64_t vstride, int k,
                                                              int i0, int nv, const TB* __restrict__ u,
                                                              const TB* __restrict__ w, int64_t N, int R,
                                                              int64_t rows_per_chunk, double2* __restrict__ partial) {
+    static_assert(kDotRows % RU == 0, "the stage holds whole groups of rows");
+    constexpr bool PF = G * RPL <= 2;    // the next rows of V are loaded while these are used
+    // blockIdx.z takes NW * G vectors of the launch's nv
+    i0 += blockIdx.z * NW * G;
+    nv = min(nv - (int)blockIdx.z * NW * G, NW * G);
     const int lane = threadIdx.x & 63;
-    const int wave = threadIdx.x >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // uniform: scalar branches and bases
     const int r0 = (blockIdx.x * 64 + lane) * RPL;
     const bool live = r0 < R;
+    const unsigned rv = (unsigned)vofs<TV>(r0);   // this lane's word of a row
     const int64_t chunk = blockIdx.y;
     const int64_t n0 = chunk * rows_per_chunk;
     const int64_t n1 = min(N, n0 + rows_per_chunk);
@@ -339,67 +354,99 @@ __global__ __launch_bounds__(NW * 64, (std::is_same<TV, p24x2>::value && G <= 4 
 #pragma unroll
         for (int g = 0; g < G; ++g) as[g][k2] = az[g][k2] = make_double2(0, 0);
     }
-    // Every wave of the workgroup needs the same rows of u and w: they are staged
-    // in LDS kDotRows rows at a time by all threads, so each value is read from
-    // memory once per workgroup (waves reading them independently drift apart
-    // over the chunk and re-fetch lines that the basis stream has evicted).
-    __shared__ Raw<TB, RPL> su[kDotRows][64];
-    __shared__ Raw<TB, RPL> sw[HASW ? kDotRows : 1][64];
+    constexpr int NST = (kDotRows * 64 + NW * 64 - 1) / (NW * 64);   // staged values per thread
+    __shared__ Raw<TB, RPL> su[2][kDotRows][64];
+    __shared__ Raw<TB, RPL> sw[HASW ? 2 : 1][HASW ? kDotRows : 1][64];
     const bool ab_here = (i0 == 0) && (wave == 0);
-    for (int64_t nb = n0; nb < n1; nb += kDotRows) {
-        const int nrow = (int)min((int64_t)kDotRows, n1 - nb);
-        for (int i = threadIdx.x; i < kDotRows * 64; i += NW * 64) {
-            const int rr = i >> 6, l = i & 63;
-            const int c = (blockIdx.x * 64 + l) * RPL;
-            if (rr < nrow && c < R) {
-                su[rr][l].load(u + (nb + rr) * R + c);
-                if (HASW) sw[rr][l].load(w + (nb + rr) * R + c);
+    Raw<TB, RPL> pu[NST], pw[HASW ? NST : 1];
+    auto fetch = [&](int64_t nb) {
+#pragma unroll
+        for (int j = 0; j < NST; ++j) {
+            const int i = threadIdx.x + j * NW * 64;
+            const int64_t n = nb + (i >> 6);
+            const int c = (blockIdx.x * 64 + (i & 63)) * RPL;
+            if (i < kDotRows * 64 && n < n1 && c < R) {
+                pu[j].load(u + n * R + c);
+                if (HASW) pw[j].load(w + n * R + c);
             } else {
-                su[rr][l].zero();
-                if (HASW) sw[rr][l].zero();
+                pu[j].zero();
+                if (HASW) pw[j].zero();
+            }
+        }
+    };
+    // the RU rows of this wave's vectors from row n on; rows past the chunk are zero here
+    // and in the stage: they add exact zeros
+    Raw<TV, RPL> cur[RU][G], nxt[PF ? RU : 1][G];
+    auto load_v = [&](int64_t n, Raw<TV, RPL>(&v)[RU][G]) {
+#pragma unroll
+        for (int q = 0; q < RU; ++q) {
+            const int64_t off = vofs<TV>((n + q) * R);   // uniform: the row's offset
+#pragma unroll
+            for (int g = 0; g < G; ++g) {
+                const int j = wave + NW * g;
+                if (j < nv && (n + q < n1 || (RU == 1 && !PF))) v[q][g].load(V + (int64_t)(i0 + j) * vstride + off + rv);
+                else v[q][g].zero();
+            }
+        }
+    };
+    fetch(n0);
+    if (PF && live) load_v(n0, cur);
+    int buf = 0;
+    for (int64_t nb = n0; nb < n1; nb += kDotRows, buf ^= 1) {
+        const int nrow = (int)min((int64_t)kDotRows, n1 - nb);
+#pragma unroll
+        for (int j = 0; j < NST; ++j) {
+            const int i = threadIdx.x + j * NW * 64;
+            if (i < kDotRows * 64) {
+                su[buf][i >> 6][i & 63] = pu[j];
+                if (HASW) sw[buf][i >> 6][i & 63] = pw[j];
             }
         }
         __syncthreads();
-        if (live) {
-            // the packed basis (up to four vectors per wave) runs four waves per SIMD and loads each
-            // row when it is used; the other cases prefetch the next row of the block
-            constexpr bool kPrefetch = !(std::is_same<TV, p24x2>::value && G <= 4);
-            Raw<TV, RPL> cur[G], nxt[G];
-            auto load_row = [&](int rr, Raw<TV, RPL>(&v)[G]) {
-                const int64_t off = (nb + rr) * R + r0;
+        if (nb + kDotRows < n1) fetch(nb + kDotRows);
+        if (!live) continue;
+        auto use_rows = [&](int rr) {
+            if constexpr (!PF) load_v(nb + rr, cur);
+            else load_v(nb + rr + RU, nxt);
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                for (int g = 0; g < G; ++g) {
-                    const int j = wave + NW * g;
-                    if (j < nv) v[g].load(V + (int64_t)(i0 + j) * vstride + vofs<TV>(off));
-                    else v[g].zero();
-                }
-            };
-            if (kPrefetch) load_row(0, cur);
-            for (int rr = 0; rr < nrow; ++rr) {
-                if (!kPrefetch) load_row(rr, cur);
-                else if (rr + 1 < nrow) load_row(rr + 1, nxt);
+            for (int q = 0; q < RU; ++q) {
 #pragma unroll
                 for (int k2 = 0; k2 < RPL; ++k2) {
-                    const double2 uv = su[rr][lane].get(k2);
-                    const double2 wv = HASW ? sw[rr][lane].get(k2) : make_double2(0, 0);
+                    // one value's widening at a time: hoisted above the others' it would spill
+                    __builtin_amdgcn_sched_barrier(0);
+                    const double2 uv = su[buf][rr + q][lane].get(k2);
+                    const double2 wv = HASW ? sw[buf][rr + q][lane].get(k2) : make_double2(0, 0);
 #pragma unroll
                     for (int g = 0; g < G; ++g) {
-                        const double2 vv = cur[g].get(k2);
+                        const double2 vv = cur[q][g].get(k2);
                         as[g][k2] = cfmac(as[g][k2], vv, uv);
                         if (HASW) az[g][k2] = cfmac(az[g][k2], vv, wv);
                     }
-                    if (ab_here) {
-                        aa[k2].x = nfma(aa[k2].x, uv);
-                        if (HASW) ab[k2] = cfmac(ab[k2], uv, wv);
-                    }
-                }
-                if (kPrefetch) {
-#pragma unroll
-                    for (int g = 0; g < G; ++g) cur[g] = nxt[g];
                 }
             }
+            if constexpr (PF)
+#pragma unroll
+                for (int q = 0; q < RU; ++q)
+#pragma unroll
+                    for (int g = 0; g < G; ++g) cur[q][g] = nxt[q][g];
+        };
+        if constexpr (PF) {
+#pragma unroll
+            for (int rr = 0; rr < kDotRows; rr += RU)
+                if (rr < nrow) use_rows(rr);
+        } else {
+            for (int rr = 0; rr < nrow; rr += RU) use_rows(rr);
         }
-        __syncthreads();
+        if (ab_here)
+            for (int rr = 0; rr < nrow; ++rr) {
+#pragma unroll
+                for (int k2 = 0; k2 < RPL; ++k2) {
+                    const double2 uv = su[buf][rr][lane].get(k2);
+                    aa[k2].x = nfma(aa[k2].x, uv);
+                    if (HASW) ab[k2] = cfmac(ab[k2], uv, sw[buf][rr][lane].get(k2));
+                }
+            }
     }
     if (!live) return;
 #pragma unroll
@@ -532,26 +579,43 @@ __global__ void dcgs2_coef_kernel(double2* __restrict__ Hraw, const double2* __r
     cc_out[(int64_t)i * R + r] = make_double2(t.x * in + h.x, t.y * in + h.y);
 }
 
+// Workgroups of a sweep below which its vectors spread over several workgroups of
+// eight (each stages u and w again, from cache): with fewer than 1.5 workgroups
+// per CU the sweep waits for its loads rather than for memory bandwidth.  At 7,936
+// folded rows of 128 RHS (248 workgroups) a sweep over 5-31 vectors takes 120
+// instead of 125 us on average, at 5,797 rows of 187 RHS in FP64 (273) 110
+// instead of 119; with four times the workgroups the extra reads of u and w win.
+constexpr int kDotFewGroups = 384;
+
+// rows whose loads a wave of G vectors issues together: eight loads in flight, or as many as
+// fit beside the accumulators (two RHS per lane) without spilling
+template <int NW, int G, int RPL> constexpr int dot_ru() {
+    return G * RPL >= 8 ? 1 : (RPL == 2 && NW == 4) ? 2 : (RPL == 2 && G == 1) ? 4 : 8 / G;
+}
+
+template <typename TB, typename TV, int NW, int G, int RPL, bool HASW>
+void launch_dcgs2_dots_cfg(const TV* V, int64_t vs, int k, int i0, int nv, const TB* u, const TB* w, int64_t N, int R,
+                           int64_t rpc, int nchunk, double2* partial, hipStream_t s) {
+    const dim3 grid((unsigned)((R / RPL + 63) / 64), (unsigned)nchunk, (unsigned)std::max(1, (nv + NW * G - 1) / (NW * G)));
+    hipLaunchKernelGGL((dcgs2_dots_kernel<TB, TV, NW, G, RPL, HASW, dot_ru<NW, G, RPL>()>), grid, dim3(NW * 64), 0, s, V, vs, k,
+                       i0, nv, u, w, N, R, rpc, partial);
+    MBT_LAUNCH_CHECK();
+}
+
 template <typename TB, typename TV, int RPL, bool HASW>
 void launch_dcgs2_dots_rpl(const TV* V, int64_t vs, int k, int i0, int nv, const TB* u, const TB* w, int64_t N, int R,
                            int64_t rpc, int nchunk, double2* partial, hipStream_t s) {
-    const dim3 grid((unsigned)((R / RPL + 63) / 64), (unsigned)nchunk);
+    const int64_t groups = (int64_t)((R / RPL + 63) / 64) * nchunk;
     if (nv <= 4)
-        hipLaunchKernelGGL((dcgs2_dots_kernel<TB, TV, 4, 1, RPL, HASW>), grid, dim3(256), 0, s, V, vs, k, i0, nv, u, w, N, R,
-                           rpc, partial);
-    else if (nv <= 8)
-        hipLaunchKernelGGL((dcgs2_dots_kernel<TB, TV, 4, 2, RPL, HASW>), grid, dim3(256), 0, s, V, vs, k, i0, nv, u, w, N, R,
-                           rpc, partial);
+        launch_dcgs2_dots_cfg<TB, TV, 4, 1, RPL, HASW>(V, vs, k, i0, nv, u, w, N, R, rpc, nchunk, partial, s);
+    else if (nv <= 8 || groups <= kDotFewGroups)
+        launch_dcgs2_dots_cfg<TB, TV, 8, 1, RPL, HASW>(V, vs, k, i0, nv, u, w, N, R, rpc, nchunk, partial, s);
     else if (nv <= 16)
-        hipLaunchKernelGGL((dcgs2_dots_kernel<TB, TV, 4, 4, RPL, HASW>), grid, dim3(256), 0, s, V, vs, k, i0, nv, u, w, N, R,
-                           rpc, partial);
+        launch_dcgs2_dots_cfg<TB, TV, 8, 2, RPL, HASW>(V, vs, k, i0, nv, u, w, N, R, rpc, nchunk, partial, s);
     else if (nv <= 32)
-        hipLaunchKernelGGL((dcgs2_dots_kernel<TB, TV, 8, 4, RPL, HASW>), grid, dim3(512), 0, s, V, vs, k, i0, nv, u, w, N, R,
-                           rpc, partial);
+        launch_dcgs2_dots_cfg<TB, TV, 8, 4, RPL, HASW>(V, vs, k, i0, nv, u, w, N, R, rpc, nchunk, partial, s);
     else
-        hipLaunchKernelGGL((dcgs2_dots_kernel<TB, TV, 8, 8, RPL, HASW>), grid, dim3(512), 0, s, V, vs, k, i0, nv, u, w, N, R,
-                           rpc, partial);
-    MBT_LAUNCH_CHECK();
+        launch_dcgs2_dots_cfg<TB, TV, 8, 8, RPL, HASW>(V, vs, k, i0, nv, u, w, N, R, rpc, nchunk, partial, s);
 }
 
 // Row-split update sweep: each wave owns RB consecutive rows of 64 RHS columns
@@ -1132,9 +1196,18 @@ inline unsigned ew_grid(int64_t n) {
 
 // Chunks of the row range for the reduction sweeps: a function of N alone, so a
 // right-hand side's sums do not depend on how many others share the batch.  Up
-// to 2048 chunks (at least 128 rows each) keep a few-RHS batch spread over the
-// whole chip while the partial sums stay small next to one basis vector.
-int64_t gmres_rows_per_chunk(int64_t N) { return std::max<int64_t>(128, (N + 2047) / 2048); }
+// to 2048 chunks keep a few-RHS batch spread over the whole chip while the
+// partial sums stay small next to one basis vector.  A workgroup walks its
+// chunk's rows one after the other, so on a small system the chunk length is the
+// length of the sweep: the 32-vector sweep of a 12x10 lattice of 15 bases (450
+// folded rows, 120 RHS) takes 98 us in chunks of 128 rows and 10.6 us in chunks
+// of 16.  Long systems have enough chunks; their partial sums are written and
+// read once per sweep (at 7,936 folded rows of 1024 RHS, 64-row chunks cost the
+// whole solve 3 % against 128), so the chunk grows with N.
+int64_t gmres_rows_per_chunk(int64_t N) {
+    const int64_t least = N < 1024 ? 16 : N < 4096 ? 32 : N < 7000 ? 64 : 128;
+    return std::max<int64_t>(least, (N + 2047) / 2048);
+}
 int gmres_nchunk(int64_t N) { return (int)((N + gmres_rows_per_chunk(N) - 1) / gmres_rows_per_chunk(N)); }
 
 // Row folding: the DCGS2 sweeps give each lane one RHS column (two with the
