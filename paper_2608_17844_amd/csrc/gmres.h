@@ -48,7 +48,12 @@ struct GmresParams {
     bool dcgs2 = true;           // delayed reorthogonalisation (two sweeps); false: classical CGS2 (three)
     bool packed_basis = false;   // FP32 solves with DCGS2, even R, restart >= 4: basis in the packed 24-bit format
     int* host_count = nullptr;   // pinned host int for the active-count readback
+    // pinned host words that the steps report their active counts into (restart + 2 of
+    // them), and the generation that tells one cycle's reports from another's
+    unsigned long long* host_slots = nullptr;
+    unsigned long long* host_gen = nullptr;
 };
+constexpr int kHostSlots = 66;   // restart <= 63
 
 struct GmresResult {
     std::vector<int> iters, conv, flag;

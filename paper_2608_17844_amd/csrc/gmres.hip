@@ -467,116 +467,164 @@ __global__ __launch_bounds__(NW * 64, (std::is_same<TV, p24x2>::value && G <= 4 
         }
 }
 
-// Per-RHS bookkeeping of DCGS2 step k (red: reduced [s, z, alpha, beta]):
-// completes Hessenberg column k-1 (raw and rotated), Givens, convergence.
-// inv_nu[r] = 1/nu for a RHS that takes another step, 0 for one that stops.
-__global__ void dcgs2_finalize_kernel(GmresState st, double2* __restrict__ Hraw, const double2* __restrict__ red,
-                                      int R, int k, int m, double* __restrict__ inv_nu) {
-    const int r = blockIdx.x * blockDim.x + threadIdx.x;
-    if (r >= R) return;
-    const int64_t ldH = (int64_t)(m + 1) * R;
-    auto RED = [&](int i) { return red[(int64_t)i * R + r]; };
-    if (!st.active[r]) {
-        inv_nu[r] = 0.0;
-        return;
-    }
-    double ss = 0;
-    for (int i = 0; i < k; ++i) {
-        const double2 s = RED(i);
-        ss += s.x * s.x + s.y * s.y;
-    }
-    const double alpha = RED(2 * k).x;
-    // nu^2 by Pythagoras loses its relative accuracy as ss -> alpha: below
-    // 1e-12 alpha the candidate lies in the span of the basis (breakdown)
-    const double nu = (alpha - ss > 1e-12 * alpha) ? sqrt(alpha - ss) : 0.0;
-    bool stop = false;
-    if (k == 0) {
-        st.g[r] = make_double2(st.beta[r] * nu, 0.0);
-    } else {
-        double2* Hc = Hraw + (int64_t)(k - 1) * ldH;
-        double2* Hj = st.H + (int64_t)(k - 1) * ldH;
-        for (int i = 0; i < k; ++i) Hc[(int64_t)i * R + r] = cadd(Hc[(int64_t)i * R + r], RED(i));
-        Hc[(int64_t)k * R + r] = make_double2(nu, 0.0);
-        for (int i = 0; i <= k; ++i) Hj[(int64_t)i * R + r] = Hc[(int64_t)i * R + r];
-        const int j = k - 1;
-        for (int i = 0; i < j; ++i) {
-            const double c = st.cs[(int64_t)i * R + r];
-            const double2 s = st.sn[(int64_t)i * R + r];
-            const double2 a = Hj[(int64_t)i * R + r], b = Hj[(int64_t)(i + 1) * R + r];
-            Hj[(int64_t)i * R + r] = cadd(make_double2(c * a.x, c * a.y), cmul(s, b));
-            Hj[(int64_t)(i + 1) * R + r] = csub(make_double2(c * b.x, c * b.y), cmulc(s, a));
-        }
-        const double2 h1v = Hj[(int64_t)j * R + r];
-        double c;
-        double2 s;
-        const double a1 = hypot(h1v.x, h1v.y);
-        if (a1 == 0.0) {
-            c = 0.0;
-            s = make_double2(1.0, 0.0);
-        } else {
-            const double t = hypot(a1, nu);
-            c = a1 / t;
-            s = make_double2(h1v.x / a1 * nu / t, h1v.y / a1 * nu / t);
-        }
-        st.cs[(int64_t)j * R + r] = c;
-        st.sn[(int64_t)j * R + r] = s;
-        Hj[(int64_t)j * R + r] = cadd(make_double2(c * h1v.x, c * h1v.y), make_double2(s.x * nu, s.y * nu));
-        Hj[(int64_t)(j + 1) * R + r] = make_double2(0, 0);
-        const double2 gj = st.g[(int64_t)j * R + r];
-        const double2 gn = make_double2(-(s.x * gj.x + s.y * gj.y), -(s.x * gj.y - s.y * gj.x));
-        st.g[(int64_t)j * R + r] = make_double2(c * gj.x, c * gj.y);
-        st.g[(int64_t)(j + 1) * R + r] = gn;
-        st.iters[r] += 1;
-        st.kcyc[r] = k;
-        const double res = hypot(gn.x, gn.y);
-        if (!(nu == nu) || isinf(nu) || !(res == res)) {
-            st.flag[r] = 1;
-            stop = true;
-        } else if (res <= st.tol * st.bnorm[r] || nu == 0.0 || k == m) {
-            stop = true;
-        }
-    }
-    if (stop || k == m || nu == 0.0) {
-        st.active[r] = 0;
-        inv_nu[r] = 0.0;
-        return;
-    }
-    inv_nu[r] = 1.0 / nu;
+// Adds a workgroup's share of the RHS that still iterate to *counter (low half: the
+// sum, high half: workgroups that have added theirs); the last of nwg workgroups
+// reports the total to the host, tagged with the cycle's generation.
+__device__ __forceinline__ void report_count(unsigned long long* counter, unsigned n, unsigned nwg,
+                                             unsigned long long* host_slot, uint32_t gen) {
+    const unsigned long long old =
+        __hip_atomic_fetch_add(counter, (1ull << 32) | n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if ((unsigned)(old >> 32) == nwg - 1)
+        __hip_atomic_store(host_slot, ((unsigned long long)gen << 32) | (uint32_t)((uint32_t)old + n), __ATOMIC_RELEASE,
+                           __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
-// Coefficients of the DCGS2 update sweep of step k, one thread per (row i, RHS r):
+// Bookkeeping of DCGS2 step k (red: reduced [s, z, alpha, beta]) and the
+// coefficients of its update sweep, one workgroup per kStepR right-hand sides.
+// Completes Hessenberg column k-1 (raw and rotated), Givens, convergence;
+// inv_nu[r] = 1/nu for a RHS that takes another step, 0 for one that stops.  Then
 // t = Hbar_{k-1} s (rows 0..k), h = projections of A v_k (raw column k of H),
-// c = t/nu + h; the coefficients of a RHS that stops are zero.
-__global__ void dcgs2_coef_kernel(double2* __restrict__ Hraw, const double2* __restrict__ red, int R, int k, int m,
-                                  const double* __restrict__ inv_nu, double2* __restrict__ cs_out,
-                                  double2* __restrict__ cc_out) {
-    const int r = blockIdx.x * blockDim.x + threadIdx.x;
-    const int i = blockIdx.y;
-    if (r >= R) return;
-    const double in = inv_nu[r];
-    if (in == 0.0) {
-        if (i < k) cs_out[(int64_t)i * R + r] = make_double2(0, 0);
-        cc_out[(int64_t)i * R + r] = make_double2(0, 0);
-        return;
-    }
+// c = t/nu + h; the coefficients of a RHS that stops are zero (coef = 0: no
+// update follows).  The per-RHS recurrence is a chain of O(k) dependent
+// operations, which bounds the kernel: its inputs are staged in LDS by all
+// threads, and one thread per RHS runs it from there.  At 128 RHS and up to 32
+// vectors it takes 11.8 us on average, where a thread per RHS walking global
+// memory, a second kernel for the coefficients and a third for the count took
+// 24 + 8 + 5 us and the host waited for a copy before the update could start.
+constexpr int kStepR = 16;
+constexpr int kStepRows = 32;   // row threads per RHS
+__global__ __launch_bounds__(kStepR * kStepRows) void dcgs2_step_kernel(GmresState st, double2* __restrict__ Hraw,
+                                                                       const double2* __restrict__ red, int R, int k,
+                                                                       int m, int coef, double* __restrict__ inv_nu,
+                                                                       double2* __restrict__ cs_out,
+                                                                       double2* __restrict__ cc_out,
+                                                                       unsigned long long* counter,
+                                                                       unsigned long long* host_slot, uint32_t gen) {
+    __shared__ double2 S[kMaxVec][kStepR], Z[kMaxVec][kStepR];
+    __shared__ double2 HC[kMaxVec][kStepR], HJ[kMaxVec][kStepR];   // column k-1: raw, rotated
+    __shared__ double2 sn[kMaxVec][kStepR];
+    __shared__ double cs[kMaxVec][kStepR];
+    __shared__ double inus[kStepR];
+    const int rr = threadIdx.x % kStepR, ti = threadIdx.x / kStepR;
+    const int r = blockIdx.x * kStepR + rr;
+    const bool valid = r < R;
+    const bool act = valid && st.active[r] != 0;
     const int64_t ldH = (int64_t)(m + 1) * R;
-    auto RED = [&](int j) { return red[(int64_t)j * R + r]; };
-    double2 t = make_double2(0, 0);
-    for (int l = (i > 0 ? i - 1 : 0); l < k; ++l)   // Hbar is upper Hessenberg: H[i][l] = 0 for l < i-1
-        t = cadd(t, cmul(Hraw[(int64_t)l * ldH + (int64_t)i * R + r], RED(l)));
-    double2 h;
-    if (i < k) {
-        const double2 d = csub(RED(k + i), t);
-        h = make_double2(d.x * in, d.y * in);
-        cs_out[(int64_t)i * R + r] = RED(i);
-    } else {
-        double2 sz = make_double2(0, 0);
-        for (int l = 0; l < k; ++l) sz = cadd(sz, cmulc(RED(l), RED(k + l)));
-        const double2 q = csub(RED(2 * k + 1), sz);
-        h = make_double2((q.x * in - t.x) * in, (q.y * in - t.y) * in);
+    double2* Hc = Hraw + (int64_t)(k > 0 ? k - 1 : 0) * ldH;
+    if (act)
+        for (int i = ti; i < k; i += kStepRows) {
+            const double2 s = red[(int64_t)i * R + r];
+            S[i][rr] = s;
+            Z[i][rr] = red[(int64_t)(k + i) * R + r];
+            const double2 h = cadd(Hc[(int64_t)i * R + r], s);
+            Hc[(int64_t)i * R + r] = h;
+            HC[i][rr] = h;
+            HJ[i][rr] = h;
+            if (i < k - 1) {
+                cs[i][rr] = st.cs[(int64_t)i * R + r];
+                sn[i][rr] = st.sn[(int64_t)i * R + r];
+            }
+        }
+    __syncthreads();
+    if (ti == 0) {
+        double inu = 0.0;
+        if (act) {
+            double ss = 0;
+            for (int i = 0; i < k; ++i) {
+                const double2 s = S[i][rr];
+                ss += s.x * s.x + s.y * s.y;
+            }
+            const double alpha = red[(int64_t)(2 * k) * R + r].x;
+            // nu^2 by Pythagoras loses its relative accuracy as ss -> alpha: below
+            // 1e-12 alpha the candidate lies in the span of the basis (breakdown)
+            const double nu = (alpha - ss > 1e-12 * alpha) ? sqrt(alpha - ss) : 0.0;
+            bool stop = false;
+            if (k == 0) {
+                st.g[r] = make_double2(st.beta[r] * nu, 0.0);
+            } else {
+                HC[k][rr] = make_double2(nu, 0.0);
+                Hc[(int64_t)k * R + r] = make_double2(nu, 0.0);
+                const int j = k - 1;
+                double2 a = HJ[0][rr];
+                for (int i = 0; i < j; ++i) {
+                    const double c = cs[i][rr];
+                    const double2 sv = sn[i][rr];
+                    const double2 b = HJ[i + 1][rr];
+                    HJ[i][rr] = cadd(make_double2(c * a.x, c * a.y), cmul(sv, b));
+                    a = csub(make_double2(c * b.x, c * b.y), cmulc(sv, a));
+                }
+                const double2 h1v = a;
+                double c;
+                double2 sv;
+                const double a1 = hypot(h1v.x, h1v.y);
+                if (a1 == 0.0) {
+                    c = 0.0;
+                    sv = make_double2(1.0, 0.0);
+                } else {
+                    const double t = hypot(a1, nu);
+                    c = a1 / t;
+                    sv = make_double2(h1v.x / a1 * nu / t, h1v.y / a1 * nu / t);
+                }
+                st.cs[(int64_t)j * R + r] = c;
+                st.sn[(int64_t)j * R + r] = sv;
+                HJ[j][rr] = cadd(make_double2(c * h1v.x, c * h1v.y), make_double2(sv.x * nu, sv.y * nu));
+                HJ[k][rr] = make_double2(0, 0);
+                const double2 gj = st.g[(int64_t)j * R + r];
+                const double2 gn = make_double2(-(sv.x * gj.x + sv.y * gj.y), -(sv.x * gj.y - sv.y * gj.x));
+                st.g[(int64_t)j * R + r] = make_double2(c * gj.x, c * gj.y);
+                st.g[(int64_t)(j + 1) * R + r] = gn;
+                st.iters[r] += 1;
+                st.kcyc[r] = k;
+                const double res = hypot(gn.x, gn.y);
+                if (!(nu == nu) || isinf(nu) || !(res == res)) {
+                    st.flag[r] = 1;
+                    stop = true;
+                } else if (res <= st.tol * st.bnorm[r] || nu == 0.0 || k == m) {
+                    stop = true;
+                }
+            }
+            if (stop || k == m || nu == 0.0) st.active[r] = 0;
+            else inu = 1.0 / nu;
+        }
+        inus[rr] = inu;
+        if (valid) inv_nu[r] = inu;
     }
-    Hraw[(int64_t)k * ldH + (int64_t)i * R + r] = h;
-    cc_out[(int64_t)i * R + r] = make_double2(t.x * in + h.x, t.y * in + h.y);
+    __syncthreads();
+    if (act && k > 0)
+        for (int i = ti; i <= k; i += kStepRows) st.H[(int64_t)(k - 1) * ldH + (int64_t)i * R + r] = HJ[i][rr];
+    if (threadIdx.x == 0) {
+        unsigned n = 0;
+        for (int q = 0; q < kStepR; ++q) n += inus[q] != 0.0 ? 1 : 0;
+        report_count(counter, n, gridDim.x, host_slot, gen);
+    }
+    if (!coef || !valid) return;
+    const double in = inus[rr];
+    for (int i = ti; i <= k; i += kStepRows) {
+        if (in == 0.0) {
+            if (i < k) cs_out[(int64_t)i * R + r] = make_double2(0, 0);
+            cc_out[(int64_t)i * R + r] = make_double2(0, 0);
+            continue;
+        }
+        double2 t = make_double2(0, 0);
+        const double2* Hi = Hraw + (int64_t)i * R + r;
+#pragma unroll 8
+        for (int l = (i > 0 ? i - 1 : 0); l < k - 1; ++l)   // Hbar is upper Hessenberg: H[i][l] = 0 for l < i-1
+            t = cadd(t, cmul(Hi[(int64_t)l * ldH], S[l][rr]));
+        if (k > 0) t = cadd(t, cmul(HC[i][rr], S[k - 1][rr]));
+        double2 h;
+        if (i < k) {
+            const double2 d = csub(Z[i][rr], t);
+            h = make_double2(d.x * in, d.y * in);
+            cs_out[(int64_t)i * R + r] = S[i][rr];
+        } else {
+            double2 sz = make_double2(0, 0);
+            for (int l = 0; l < k; ++l) sz = cadd(sz, cmulc(S[l][rr], Z[l][rr]));
+            const double2 q = csub(red[(int64_t)(2 * k + 1) * R + r], sz);
+            h = make_double2((q.x * in - t.x) * in, (q.y * in - t.y) * in);
+        }
+        Hraw[(int64_t)k * ldH + (int64_t)i * R + r] = h;
+        cc_out[(int64_t)i * R + r] = make_double2(t.x * in + h.x, t.y * in + h.y);
+    }
 }
 
 // Workgroups of a sweep below which its vectors spread over several workgroups of
@@ -628,7 +676,8 @@ __global__ __launch_bounds__(256) void dcgs2_update_rows_kernel(const TB* __rest
                                                                 TB* u, TB* w, const double2* __restrict__ cs_,
                                                                 const double2* __restrict__ cc_,
                                                                 const double* __restrict__ inv_nu_, int64_t N, int R,
-                                                                int Rt) {
+                                                                int Rt, const unsigned long long* __restrict__ live) {
+    if ((uint32_t)*live == 0) return;   // every RHS has stopped (the host may not know yet)
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
     const int r = blockIdx.x * 64 + lane;
@@ -702,7 +751,8 @@ __global__ __launch_bounds__(256) void dcgs2_update_rows24_kernel(const p24x2* _
                                                                   p24x2* __restrict__ vk, const double2* __restrict__ cs_,
                                                                   const double2* __restrict__ cc_,
                                                                   const double* __restrict__ inv_nu_, int64_t N, int R,
-                                                                  int Rt) {
+                                                                  int Rt, const unsigned long long* __restrict__ live) {
+    if ((uint32_t)*live == 0) return;
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
     const int r0 = 2 * (blockIdx.x * 64 + lane);
@@ -792,7 +842,7 @@ __global__ __launch_bounds__(256) void dcgs2_update_rows24_kernel(const p24x2* _
 
 void launch_dcgs2_update24(const p24x2* V, int64_t vs, int k, float2* u, const float2* w, p24x2* vk,
                            const double2* cs, const double2* cc, const double* inv_nu, int64_t N, int R, int Rt,
-                           hipStream_t s) {
+                           const unsigned long long* live, hipStream_t s) {
     constexpr int RB = 8;
     MBT_REQUIRE(R % 2 == 0, "packed basis needs an even number of RHS");
     const int64_t rows_per_block = 4 * RB;
@@ -800,7 +850,7 @@ void launch_dcgs2_update24(const p24x2* V, int64_t vs, int k, float2* u, const f
     MBT_REQUIRE(gy < 65536, "dcgs2 update: too many row blocks");
     MBT_REQUIRE(Rt % 2 == 0 && R % Rt == 0, "packed basis: folded width must be a multiple of the even RHS count");
     hipLaunchKernelGGL((dcgs2_update_rows24_kernel<RB>), dim3((unsigned)((R / 2 + 63) / 64), (unsigned)gy), dim3(256), 0,
-                       s, V, vs, k, u, w, vk, cs, cc, inv_nu, N, R, Rt);
+                       s, V, vs, k, u, w, vk, cs, cc, inv_nu, N, R, Rt, live);
     MBT_LAUNCH_CHECK();
 }
 
@@ -909,14 +959,15 @@ void launch_dcgs2_dots(const TV* V, int64_t vs, int k, const TB* u, const TB* w,
 
 template <typename TB>
 void launch_dcgs2_update(const TB* V, int64_t vs, int k, TB* u, TB* w, const double2* cs, const double2* cc,
-                         const double* inv_nu, int64_t N, int R, int Rt, hipStream_t s) {
+                         const double* inv_nu, int64_t N, int R, int Rt, const unsigned long long* live,
+                         hipStream_t s) {
     MBT_REQUIRE(R % Rt == 0, "folded width must be a multiple of the RHS count");
     constexpr int RB = 8;
     const int64_t rows_per_block = 4 * RB;
     const int64_t gy = (N + rows_per_block - 1) / rows_per_block;
     MBT_REQUIRE(gy < 65536, "dcgs2 update: too many row blocks");
     hipLaunchKernelGGL((dcgs2_update_rows_kernel<TB, RB>), dim3((unsigned)((R + 63) / 64), (unsigned)gy), dim3(256), 0,
-                       s, V, vs, k, u, w, cs, cc, inv_nu, N, R, Rt);
+                       s, V, vs, k, u, w, cs, cc, inv_nu, N, R, Rt, live);
     MBT_LAUNCH_CHECK();
 }
 
@@ -953,57 +1004,61 @@ void launch_pass(const TB* V, int64_t vs, int nvec, const double2* coef, TO* w, 
     launch_pass_rpl<TB, TO, MODE, 1>(V, vs, nvec, coef, w, N, R, rpc, nchunk, partial, s, cfg_n);
 }
 
-// out[i][r] = sum over chunks of partial[chunk][i][r], in chunk order
-// out[t] = sum over chunks c of partial[c][t], t < nvec*R, in an order fixed by
-// nchunk alone: groups of kRedGroup consecutive chunks are summed in chunk
-// order, then the group sums in group order.  A workgroup owns 64 outputs and
-// its waves share the groups, so a short batch still spreads its (up to 2048)
-// chunks over many loads in flight.
-constexpr int kRedGroup = 64;
+// out[i][r] = sum over the chunks c and the folded copies f < F of
+// partial[c][i][f * R + r], in an order fixed by nchunk and F alone: the terms
+// j = f * nchunk + c are dealt to kRedSub running sums (sum q takes j = q,
+// q + kRedSub, ...), which are then added in order.  A workgroup owns kRedOut
+// adjacent outputs (whole cache lines of every chunk), so a short batch still
+// spreads its terms over many loads in flight: at 768 chunks of 4 x 32 columns
+// (64x64 elements, 32 RHS) the sums of a sweep take 43 us when each is one
+// thread's walk over 64 chunks; at 62 chunks of 4 x 128 columns 20 us, and 6.6 us
+// so.
+constexpr int kRedOut = 16;
 constexpr int kRedWaves = 8;
+constexpr int kRedSub = kRedWaves * 64 / kRedOut;
 constexpr int kMaxChunks = 2048;
 __global__ __launch_bounds__(64 * kRedWaves) void reduce_partials_kernel(const double2* __restrict__ partial,
-                                                                         int nchunk, int nvec, int R,
+                                                                         int nchunk, int nvec, int R, int F,
                                                                          double2* __restrict__ out) {
-    __shared__ double2 gs[kMaxChunks / kRedGroup][64];
-    const int lane = threadIdx.x & 63;
-    const int wave = threadIdx.x >> 6;
-    const int64_t nout = (int64_t)nvec * R;
-    const int64_t t = (int64_t)blockIdx.x * 64 + lane;
-    const int ng = (nchunk + kRedGroup - 1) / kRedGroup;
-    for (int g = wave; g < ng; g += kRedWaves) {
-        double2 sg = make_double2(0, 0);
-        if (t < nout) {
-            const int c1 = min(nchunk, (g + 1) * kRedGroup);
-            for (int c = g * kRedGroup; c < c1; ++c) sg = cadd(sg, partial[(int64_t)c * nout + t]);
+    __shared__ double2 gs[kRedSub][kRedOut];
+    const int o = threadIdx.x % kRedOut, q = threadIdx.x / kRedOut;
+    const int64_t t = (int64_t)blockIdx.x * kRedOut + o;
+    double2 sum = make_double2(0, 0);
+    if (t < (int64_t)nvec * R) {
+        const int64_t i = t / R, r = t % R;
+        const int64_t row = (int64_t)R * F;
+        const double2* p = partial + i * row + r;
+        int f = 0, c = q;
+        while (c >= nchunk && f < F) {
+            c -= nchunk;
+            ++f;
         }
-        gs[g][lane] = sg;
+#pragma unroll 4
+        while (f < F) {
+            sum = cadd(sum, p[(int64_t)c * nvec * row + (int64_t)f * R]);
+            c += kRedSub;
+            while (c >= nchunk && f < F) {
+                c -= nchunk;
+                ++f;
+            }
+        }
     }
+    gs[q][o] = sum;
     __syncthreads();
-    if (wave == 0 && t < nout) {
-        double2 sum = gs[0][lane];
-        for (int g = 1; g < ng; ++g) sum = cadd(sum, gs[g][lane]);
+    if (q == 0 && t < (int64_t)nvec * R) {
+#pragma unroll 8
+        for (int g = 1; g < kRedSub; ++g) sum = cadd(sum, gs[g][o]);
         out[t] = sum;
     }
 }
 
-void launch_reduce_partials(const double2* partial, int nchunk, int nvec, int R, double2* out, hipStream_t s) {
+// partial holds nvec rows of F * R columns per chunk; out nvec rows of R
+void launch_reduce_partials(const double2* partial, int nchunk, int nvec, int R, int F, double2* out, hipStream_t s) {
     MBT_REQUIRE(nchunk >= 1 && nchunk <= kMaxChunks, "reduction: too many chunks");
     const int64_t nout = (int64_t)nvec * R;
-    hipLaunchKernelGGL(reduce_partials_kernel, dim3((unsigned)((nout + 63) / 64)), dim3(64 * kRedWaves), 0, s, partial,
-                       nchunk, nvec, R, out);
+    hipLaunchKernelGGL(reduce_partials_kernel, dim3((unsigned)((nout + kRedOut - 1) / kRedOut)), dim3(64 * kRedWaves), 0,
+                       s, partial, nchunk, nvec, R, F, out);
     MBT_LAUNCH_CHECK();
-}
-
-// out[i][r] = sum_{f < F} in[i][f * R + r] in order of f (partials of folded rows)
-__global__ void unfold_kernel(const double2* __restrict__ in, int nvec, int R, int F, double2* __restrict__ out) {
-    const int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (t >= (int64_t)nvec * R) return;
-    const int64_t i = t / R;
-    const int r = (int)(t % R);
-    double2 acc = in[i * R * F + r];
-    for (int f = 1; f < F; ++f) acc = cadd(acc, in[i * R * F + (int64_t)f * R + r]);
-    out[t] = acc;
 }
 
 template <typename TB>
@@ -1027,11 +1082,8 @@ __device__ __forceinline__ double sum_norm_partials(const double2* partial, int 
     return sqrt(s);
 }
 
-// Start of a restart cycle: beta = ||r|| (nrm2: the reduced squared norms);
-// decide convergence at restart.
-__global__ void cycle_init_kernel(GmresState st, const double2* __restrict__ nrm2, int R, int first) {
-    const int r = blockIdx.x * blockDim.x + threadIdx.x;
-    if (r >= R) return;
+// One RHS at the start of a restart cycle: whether it goes on.
+__device__ int cycle_init_rhs(GmresState st, const double2* __restrict__ nrm2, int r, int first) {
     const double beta = sqrt(nrm2[r].x);
     if (first) {
         st.bnorm[r] = beta;
@@ -1056,6 +1108,19 @@ __global__ void cycle_init_kernel(GmresState st, const double2* __restrict__ nrm
     st.active[r] = act;
     st.scale[r] = act ? 1.0 / beta : 0.0;
     st.g[r] = make_double2(act ? beta : 0.0, 0.0);
+    return act;
+}
+
+// Start of a restart cycle: beta = ||r|| (nrm2: the reduced squared norms);
+// decide convergence at restart; reports how many RHS go on.
+__global__ __launch_bounds__(256) void cycle_init_kernel(GmresState st, const double2* __restrict__ nrm2, int R,
+                                                         int first, unsigned long long* counter,
+                                                         unsigned long long* host_slot, uint32_t gen) {
+    const int r = blockIdx.x * blockDim.x + threadIdx.x;
+    int act = 0;
+    if (r < R) act = cycle_init_rhs(st, nrm2, r, first);
+    const int n = __syncthreads_count(act);
+    if (threadIdx.x == 0) report_count(counter, (unsigned)n, gridDim.x, host_slot, gen);
 }
 
 // Arnoldi step j bookkeeping: Hessenberg column, Givens rotations, residual
@@ -1131,9 +1196,11 @@ __global__ void scale_cols_kernel(TB* __restrict__ v, const double* __restrict__
 
 // End of cycle: y = R_k^{-1} g_k per RHS (k = steps done this cycle); |g_k|
 // meeting the tolerance makes the RHS a candidate, which the explicit residual
-// of the next restart confirms.
-__global__ void cycle_solve_kernel(GmresState st, int R, int m, double2* __restrict__ y) {
+// of the next restart confirms.  Launched with at least m + 2 threads.
+__global__ void cycle_solve_kernel(GmresState st, int R, int m, double2* __restrict__ y,
+                                   unsigned long long* __restrict__ counters) {
     const int r = blockIdx.x * blockDim.x + threadIdx.x;
+    if (r <= m + 1) counters[r] = 0;   // for the next cycle
     if (r >= R) return;
     const int k = st.kcyc[r];
     const int64_t ldH = (int64_t)(m + 1) * R;
@@ -1188,6 +1255,32 @@ __global__ void zero_kernel(double2* __restrict__ p, int64_t n) {
         p[t] = make_double2(0, 0);
 }
 
+// Waits until the device has reported a count of generation gen into the pinned
+// slot.  The kernel that reports it is already enqueued on s, so the wait ends:
+// with the value, or with an error once the stream has run dry or failed.
+int wait_count(const unsigned long long* slot, uint32_t gen, hipStream_t s) {
+    auto seen = [&](int& n) {
+        const unsigned long long v = __atomic_load_n(slot, __ATOMIC_ACQUIRE);
+        n = (int)(uint32_t)v;
+        return (uint32_t)(v >> 32) == gen;
+    };
+    int n = 0;
+    for (;;) {
+        for (int spin = 0; spin < 4096; ++spin) {
+            if (seen(n)) return n;
+            __builtin_ia32_pause();
+        }
+        const hipError_t e = hipStreamQuery(s);
+        if (e == hipErrorNotReady) {
+            (void)hipGetLastError();   // not an error
+            continue;
+        }
+        MBT_HIP(e);
+        if (seen(n)) return n;
+        throw Error(-4, "the step count was not reported");
+    }
+}
+
 inline unsigned ew_grid(int64_t n) {
     return (unsigned)std::max<int64_t>(1, std::min<int64_t>((n + 255) / 256, 65536));
 }
@@ -1236,7 +1329,7 @@ size_t gmres_state_bytes(int64_t N, int R, int m) {
     s += sizeof(double2) * (size_t)m * R;                      // y
     (void)nchunk;
     s += sizeof(double2) * partial_values(N, R, m);            // partials (of folded rows too)
-    s += sizeof(double2) * (size_t)(2 * m + 2) * R * gmres_fold(N) + 256;   // chunk sums of folded rows
+    s += sizeof(unsigned long long) * (size_t)(m + 3) + 256;   // counters
     s += sizeof(double2) * (size_t)R + 256;                    // reduced squared norms
     s += sizeof(double) * (size_t)R * 4 + sizeof(int) * (size_t)R * 7 + 12 * 256;
     // delayed reorthogonalisation: unrotated Hessenberg, reduced sweep, coefficients, 1/nu
@@ -1275,7 +1368,7 @@ GmresResult gmres_batched(const std::function<void(const TB*, TB*)>& apply, cons
     double2* h2 = arena.get<double2>((size_t)(m + 1) * R);
     double2* y = arena.get<double2>((size_t)m * R);
     double2* partial = arena.get<double2>(partial_values(N, R, m));
-    double2* redf = arena.get<double2>((size_t)(2 * m + 2) * R * gmres_fold(N));
+    unsigned long long* counters = arena.get<unsigned long long>(m + 3);   // RHS still iterating, per step
     double2* nrm2 = arena.get<double2>(R);
     double2* Hraw = nullptr;
     double2* red = nullptr;
@@ -1325,8 +1418,10 @@ GmresResult gmres_batched(const std::function<void(const TB*, TB*)>& apply, cons
     const int64_t rpcf = gmres_rows_per_chunk(Nf);
     const int nchunkf = gmres_nchunk(Nf);
 
+    unsigned long long* slots = prm.host_slots;
     // x = 0, r0 = b
     hipLaunchKernelGGL(zero_kernel, dim3(ew_grid(vs)), dim3(256), 0, s, x, vs);
+    hipLaunchKernelGGL(zero_kernel, dim3(1), dim3(256), 0, s, reinterpret_cast<double2*>(counters), (m + 3) / 2);
     hipLaunchKernelGGL((copy_kernel<TB>), dim3(ew_grid(vs)), dim3(256), 0, s, b, r0v, vs);
     MBT_LAUNCH_CHECK();
     bool first = true;
@@ -1334,11 +1429,13 @@ GmresResult gmres_batched(const std::function<void(const TB*, TB*)>& apply, cons
         // beta = ||r|| (r sits in V_0, or in the candidate vector when packed);
         // the convergence verdict of the previous cycle is taken on it
         hipLaunchKernelGGL((colnorm2_kernel<TB>), dim3((R + 63) / 64, nchunk), dim3(64), 0, s, r0v, N, R, rpc, partial);
-        launch_reduce_partials(partial, nchunk, 1, R, nrm2, s);
-        hipLaunchKernelGGL(cycle_init_kernel, gR, bR, 0, s, st, nrm2, R, first ? 1 : 0);
+        launch_reduce_partials(partial, nchunk, 1, R, 1, nrm2, s);
+        const uint32_t gen = (uint32_t)++*prm.host_gen;
+        hipLaunchKernelGGL(cycle_init_kernel, gR, bR, 0, s, st, nrm2, R, first ? 1 : 0, counters + m + 1, slots + m + 1,
+                           gen);
         MBT_LAUNCH_CHECK();
         first = false;
-        if (count_active() == 0 || cycle == prm.max_cycles) break;
+        if (wait_count(slots + m + 1, gen, s) == 0 || cycle == prm.max_cycles) break;
         res.cycles++;
         hipLaunchKernelGGL((scale_cols_kernel<TB>), dim3(ew_grid(vs)), dim3(256), 0, s, r0v, st.scale, N, R);
         MBT_LAUNCH_CHECK();
@@ -1364,33 +1461,25 @@ GmresResult gmres_batched(const std::function<void(const TB*, TB*)>& apply, cons
                     launch_dcgs2_dots<TB, TB>(Vbasis, vs, k, u, w, Nf, Rf, rpcf, nchunkf, partial, s);
                 }
             }
-            const int nred = 2 * k + 2;
-            if (F == 1) {
-                launch_reduce_partials(partial, nchunkf, nred, R, red, s);
-            } else {
-                launch_reduce_partials(partial, nchunkf, nred, Rf, redf, s);
-                hipLaunchKernelGGL(unfold_kernel, dim3((unsigned)((nred * R + 255) / 256)), dim3(256), 0, s, redf, nred,
-                                   R, F, red);
-                MBT_LAUNCH_CHECK();
-            }
-            hipLaunchKernelGGL(dcgs2_finalize_kernel, gR, bR, 0, s, st, Hraw, red, R, k, m, inv_nu);
+            launch_reduce_partials(partial, nchunkf, 2 * k + 2, R, F, red, s);
+            hipLaunchKernelGGL(dcgs2_step_kernel, dim3((R + kStepR - 1) / kStepR), dim3(kStepR * kStepRows), 0, s, st,
+                               Hraw, red, R, k, m, hasw ? 1 : 0, inv_nu, coef_s, coef_c, counters + k, slots + k, gen);
             MBT_LAUNCH_CHECK();
             steps = k;
-            if (k == m || count_active() == 0) break;
-            hipLaunchKernelGGL(dcgs2_coef_kernel, dim3((R + 255) / 256, k + 1), bR, 0, s, Hraw, red, R, k, m, inv_nu,
-                               coef_s, coef_c);
-            MBT_LAUNCH_CHECK();
+            if (k == m) break;
             {
                 // k basis vectors, u and w read; v_k and u_{k+1} written
                 ProfScope ps(kKArnoldiUpdateDots, (k + 1) * bbytes + 3 * vbytes, 16.0 * k * vs, s);
                 if (packed) {
                     if constexpr (std::is_same<TB, float2>::value)
                         launch_dcgs2_update24(V24, vs24, k, U, Wv, V24 + (int64_t)k * vs24, coef_s, coef_c, inv_nu, Nf,
-                                              Rf, R, s);
+                                              Rf, R, counters + k, s);
                 } else {
-                    launch_dcgs2_update<TB>(Vbasis, vs, k, u, w, coef_s, coef_c, inv_nu, Nf, Rf, R, s);
+                    launch_dcgs2_update<TB>(Vbasis, vs, k, u, w, coef_s, coef_c, inv_nu, Nf, Rf, R, counters + k, s);
                 }
             }
+            // the update is under way (or has nothing to do) while the host learns whether any RHS goes on
+            if (wait_count(slots + k, gen, s) == 0) break;
         }
         for (int j = 0; !prm.dcgs2 && j < m; ++j) {
             steps = j + 1;
@@ -1405,12 +1494,12 @@ GmresResult gmres_batched(const std::function<void(const TB*, TB*)>& apply, cons
                 ProfScope ps(kKArnoldiDots, (nvec + 1) * vbytes, 8.0 * nvec * vs, s);
                 launch_pass<TB, TB, 0>(Vbasis, vs, nvec, nullptr, w, N, R, rpc, nchunk, partial, s);
             }
-            launch_reduce_partials(partial, nchunk, nvec, R, h1, s);
+            launch_reduce_partials(partial, nchunk, nvec, R, 1, h1, s);
             {
                 ProfScope ps(kKArnoldiUpdateDots, (nvec + 2) * vbytes, 16.0 * nvec * vs, s);
                 launch_pass<TB, TB, 1>(Vbasis, vs, nvec, h1, w, N, R, rpc, nchunk, partial, s);
             }
-            launch_reduce_partials(partial, nchunk, nvec, R, h2, s);
+            launch_reduce_partials(partial, nchunk, nvec, R, 1, h2, s);
             {
                 ProfScope ps(kKArnoldiUpdateNorm, (nvec + 2) * vbytes, 8.0 * nvec * vs, s);
                 launch_pass<TB, TB, 2>(Vbasis, vs, nvec, h2, w, N, R, rpc, nchunk, partial, s);
@@ -1421,7 +1510,7 @@ GmresResult gmres_batched(const std::function<void(const TB*, TB*)>& apply, cons
             if (count_active() == 0) break;
         }
         // y = R^{-1} g ; x += V y
-        hipLaunchKernelGGL(cycle_solve_kernel, gR, bR, 0, s, st, R, m, y);
+        hipLaunchKernelGGL(cycle_solve_kernel, gR, bR, 0, s, st, R, m, y, counters);
         MBT_LAUNCH_CHECK();
         // configuration fixed by m: a RHS's update x += V y does not depend on how long
         // the other RHS of the batch kept the cycle going
@@ -1553,7 +1642,7 @@ void pcg_dot(const TB* a, const TB* b, int64_t N, int R, double2* partial, doubl
     const int nchunk = gmres_nchunk(N);
     hipLaunchKernelGGL((pcg_dot_kernel<TB>), dim3((R + 63) / 64, nchunk), dim3(64), 0, s, a, b, N, R, rpc, partial);
     MBT_LAUNCH_CHECK();
-    launch_reduce_partials(partial, nchunk, 1, R, out, s);
+    launch_reduce_partials(partial, nchunk, 1, R, 1, out, s);
 }
 
 }  // namespace
@@ -1758,7 +1847,7 @@ void cocg_dot(const TB* a, const TB* b, int64_t N, int R, double2* partial, doub
     hipLaunchKernelGGL((cocg_dot_kernel<TB, NORM>), dim3((R + 63) / 64, nchunk), dim3(64), 0, s, a, b, N, R, rpc,
                        partial);
     MBT_LAUNCH_CHECK();
-    launch_reduce_partials(partial, nchunk, NORM ? 2 : 1, R, out, s);
+    launch_reduce_partials(partial, nchunk, NORM ? 2 : 1, R, 1, out, s);
 }
 
 }  // namespace

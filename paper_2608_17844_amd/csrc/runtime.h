@@ -75,6 +75,8 @@ struct Worker {
     hipStream_t stream = nullptr;
     DBuf ws, xs;
     int* host_count = nullptr;   // pinned
+    unsigned long long* host_slots = nullptr;   // pinned, kHostSlots words that kernels write
+    unsigned long long host_gen = 0;
     explicit Worker(int dev);
     ~Worker();
     void ensure(size_t bytes);

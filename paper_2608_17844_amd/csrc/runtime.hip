@@ -84,6 +84,8 @@ Worker::Worker(int dev) : device(dev) {
     MBT_HIP(hipSetDevice(dev));
     MBT_HIP(hipStreamCreateWithFlags(&stream, hipStreamNonBlocking));
     MBT_HIP(hipHostMalloc((void**)&host_count, sizeof(int) * 16, hipHostMallocDefault));
+    MBT_HIP(hipHostMalloc((void**)&host_slots, sizeof(unsigned long long) * kHostSlots, hipHostMallocDefault));
+    std::memset(host_slots, 0, sizeof(unsigned long long) * kHostSlots);
 }
 
 Worker::~Worker() {
@@ -94,6 +96,7 @@ Worker::~Worker() {
     }
     ws.release();
     if (host_count) (void)hipHostFree(host_count);
+    if (host_slots) (void)hipHostFree(host_slots);
 }
 
 void Worker::ensure(size_t bytes) {
@@ -758,6 +761,8 @@ SolveOut solve_rhs(const OpData& op, const mbt_solve_opts& o, const double2* V, 
     prm.max_cycles = o.max_cycles;
     prm.matvecs_per_apply = o.pc == MBT_PC_NORMAL_EQ ? 2 : 1;
     prm.host_count = wk.host_count;
+    prm.host_slots = wk.host_slots;
+    prm.host_gen = &wk.host_gen;
     prm.dcgs2 = !(o.flags & MBT_FLAG_CGS2);
     prm.packed_basis = o.prec != MBT_FP64 && !(o.flags & MBT_FLAG_FP32_BASIS);
     std::vector<double> vn;
