@@ -669,9 +669,9 @@ void launch_dcgs2_dots_rpl(const TV* V, int64_t vs, int k, int i0, int nv, const
 // Row-split update sweep: each wave owns RB consecutive rows of 64 RHS columns
 // and walks all k basis vectors itself, so there is no cross-wave reduction and
 // no workgroup barrier; the per-RHS coefficients are re-read (from L2) for each
-// block of rows.  The next vector's rows are loaded while the current ones are
-// accumulated.  Summation over i is sequential per (row, RHS).
-template <typename TB, int RB>
+// block of rows.  The next VU vectors' rows are loaded while the current ones are
+// accumulated.  Summation over i is sequential per (row, RHS), whatever RB and VU.
+template <typename TB, int RB, int VU>
 __global__ __launch_bounds__(256) void dcgs2_update_rows_kernel(const TB* __restrict__ V, int64_t vstride, int k,
                                                                 TB* u, TB* w, const double2* __restrict__ cs_,
                                                                 const double2* __restrict__ cc_,
@@ -693,37 +693,44 @@ __global__ __launch_bounds__(256) void dcgs2_update_rows_kernel(const TB* __rest
 #pragma unroll
     for (int j = 0; j < RB; ++j) a[j] = c[j] = make_double2(0, 0);
     const TB* base = V + n0 * R + r;
-    Raw<TB, 1> cur[RB], nxt[RB];
-    auto load = [&](int i, Raw<TB, 1>(&v)[RB]) {
+    Raw<TB, 1> cur[VU][RB], nxt[VU][RB];
+    double2 fs[VU], fc[VU], fs_n[VU], fc_n[VU];
+    auto load = [&](int i0, Raw<TB, 1>(&v)[VU][RB], double2(&s)[VU], double2(&t)[VU]) {
 #pragma unroll
-        for (int j = 0; j < RB; ++j) {
-            if (j < nr) v[j].load(base + i * vstride + (int64_t)j * R);
-            else v[j].zero();
+        for (int q = 0; q < VU; ++q) {
+            const int i = i0 + q;
+            s[q] = t[q] = make_double2(0, 0);
+            if (i < k) {
+                s[q] = cs[(int64_t)i * Rt];
+                t[q] = cc[(int64_t)i * Rt];
+            }
+#pragma unroll
+            for (int j = 0; j < RB; ++j) {
+                if (i < k && j < nr) v[q][j].load(base + i * vstride + (int64_t)j * R);
+                else v[q][j].zero();
+            }
         }
     };
-    double2 fs = make_double2(0, 0), fc = make_double2(0, 0);
-    if (k > 0) {
-        load(0, cur);
-        fs = cs[0];
-        fc = cc[0];
-    }
-    for (int i = 0; i < k; ++i) {
-        double2 fs_n = make_double2(0, 0), fc_n = make_double2(0, 0);
-        if (i + 1 < k) {
-            load(i + 1, nxt);
-            fs_n = cs[(int64_t)(i + 1) * Rt];
-            fc_n = cc[(int64_t)(i + 1) * Rt];
+    load(0, cur, fs, fc);
+    for (int i = 0; i < k; i += VU) {
+        load(i + VU, nxt, fs_n, fc_n);
+#pragma unroll
+        for (int q = 0; q < VU; ++q) {
+            if (VU > 1 && i + q >= k) break;
+#pragma unroll
+            for (int j = 0; j < RB; ++j) {
+                const double2 vv = cur[q][j].get(0);
+                a[j] = cfma(a[j], fs[q], vv);
+                c[j] = cfma(c[j], fc[q], vv);
+            }
         }
 #pragma unroll
-        for (int j = 0; j < RB; ++j) {
-            const double2 vv = cur[j].get(0);
-            a[j] = cfma(a[j], fs, vv);
-            c[j] = cfma(c[j], fc, vv);
-        }
+        for (int q = 0; q < VU; ++q) {
 #pragma unroll
-        for (int j = 0; j < RB; ++j) cur[j] = nxt[j];
-        fs = fs_n;
-        fc = fc_n;
+            for (int j = 0; j < RB; ++j) cur[q][j] = nxt[q][j];
+            fs[q] = fs_n[q];
+            fc[q] = fc_n[q];
+        }
     }
     const double inu = inv_nu[0];
     const double2 ckv = cc[(int64_t)k * Rt];
@@ -745,7 +752,7 @@ __global__ __launch_bounds__(256) void dcgs2_update_rows_kernel(const TB* __rest
 // with a lane owning two adjacent RHS columns (one packed word per row).  v_k
 // goes to its own slot vk (rounded to the packed format, and the rounded value
 // is the one removed from u_{k+1}); u_{k+1} overwrites u.
-template <int RB>
+template <int RB, int VU>
 __global__ __launch_bounds__(256) void dcgs2_update_rows24_kernel(const p24x2* __restrict__ V, int64_t vstride, int k,
                                                                   float2* u, const float2* __restrict__ w,
                                                                   p24x2* __restrict__ vk, const double2* __restrict__ cs_,
@@ -771,47 +778,51 @@ __global__ __launch_bounds__(256) void dcgs2_update_rows24_kernel(const p24x2* _
 #pragma unroll
         for (int q = 0; q < 2; ++q) a[j][q] = c[j][q] = make_double2(0, 0);
     const p24x2* base = V + (n0 * R + r0) / 2;
-    Raw<p24x2, 2> cur[RB], nxt[RB];
-    auto load = [&](int i, Raw<p24x2, 2>(&v)[RB]) {
+    Raw<p24x2, 2> cur[VU][RB], nxt[VU][RB];
+    double2 fs[VU][2], fc[VU][2], fs_n[VU][2], fc_n[VU][2];
+    auto load = [&](int i0, Raw<p24x2, 2>(&v)[VU][RB], double2(&s)[VU][2], double2(&t)[VU][2]) {
 #pragma unroll
-        for (int j = 0; j < RB; ++j) {
-            if (j < nr) v[j].load(base + i * vstride + (int64_t)j * rw);
-            else v[j].zero();
+        for (int e = 0; e < VU; ++e) {
+            const int i = i0 + e;
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                s[e][q] = t[e][q] = make_double2(0, 0);
+                if (i < k) {
+                    s[e][q] = cs[(int64_t)i * Rt + q];
+                    t[e][q] = cc[(int64_t)i * Rt + q];
+                }
+            }
+#pragma unroll
+            for (int j = 0; j < RB; ++j) {
+                if (i < k && j < nr) v[e][j].load(base + i * vstride + (int64_t)j * rw);
+                else v[e][j].zero();
+            }
         }
     };
-    double2 fs[2] = {make_double2(0, 0), make_double2(0, 0)}, fc[2] = {make_double2(0, 0), make_double2(0, 0)};
-    if (k > 0) {
-        load(0, cur);
+    load(0, cur, fs, fc);
+    for (int i = 0; i < k; i += VU) {
+        load(i + VU, nxt, fs_n, fc_n);
 #pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            fs[q] = cs[q];
-            fc[q] = cc[q];
-        }
-    }
-    for (int i = 0; i < k; ++i) {
-        double2 fs_n[2] = {make_double2(0, 0), make_double2(0, 0)}, fc_n[2] = {make_double2(0, 0), make_double2(0, 0)};
-        if (i + 1 < k) {
-            load(i + 1, nxt);
+        for (int e = 0; e < VU; ++e) {
+            if (VU > 1 && i + e >= k) break;
 #pragma unroll
-            for (int q = 0; q < 2; ++q) {
-                fs_n[q] = cs[(int64_t)(i + 1) * Rt + q];
-                fc_n[q] = cc[(int64_t)(i + 1) * Rt + q];
-            }
+            for (int j = 0; j < RB; ++j)
+#pragma unroll
+                for (int q = 0; q < 2; ++q) {
+                    const double2 vv = cur[e][j].get(q);
+                    a[j][q] = cfma(a[j][q], fs[e][q], vv);
+                    c[j][q] = cfma(c[j][q], fc[e][q], vv);
+                }
         }
 #pragma unroll
-        for (int j = 0; j < RB; ++j)
+        for (int e = 0; e < VU; ++e) {
+#pragma unroll
+            for (int j = 0; j < RB; ++j) cur[e][j] = nxt[e][j];
 #pragma unroll
             for (int q = 0; q < 2; ++q) {
-                const double2 vv = cur[j].get(q);
-                a[j][q] = cfma(a[j][q], fs[q], vv);
-                c[j][q] = cfma(c[j][q], fc[q], vv);
+                fs[e][q] = fs_n[e][q];
+                fc[e][q] = fc_n[e][q];
             }
-#pragma unroll
-        for (int j = 0; j < RB; ++j) cur[j] = nxt[j];
-#pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            fs[q] = fs_n[q];
-            fc[q] = fc_n[q];
         }
     }
     double inu[2];
@@ -840,25 +851,38 @@ __global__ __launch_bounds__(256) void dcgs2_update_rows24_kernel(const p24x2* _
     }
 }
 
+// Rows per wave of the row-split sweeps.  Eight rows amortise the coefficients
+// over the basis traffic once the waves fill the chip; a short batch leaves each
+// wave alone on its CU, waiting one memory latency per vector, so below kFewWaves
+// waves of eight rows it takes two rows and four vectors at a time instead.
+constexpr int64_t kFewWaves = 2048;
+inline bool few_waves(int64_t N, int64_t lanes) { return ((N + 7) / 8) * ((lanes + 63) / 64) < kFewWaves; }
+
+template <int RB, int VU>
+void launch_dcgs2_update24_rb(const p24x2* V, int64_t vs, int k, float2* u, const float2* w, p24x2* vk,
+                              const double2* cs, const double2* cc, const double* inv_nu, int64_t N, int R, int Rt,
+                              const unsigned long long* live, hipStream_t s) {
+    const int64_t gy = (N + 4 * RB - 1) / (4 * RB);
+    MBT_REQUIRE(gy < 65536, "dcgs2 update: too many row blocks");
+    hipLaunchKernelGGL((dcgs2_update_rows24_kernel<RB, VU>), dim3((unsigned)((R / 2 + 63) / 64), (unsigned)gy), dim3(256),
+                       0, s, V, vs, k, u, w, vk, cs, cc, inv_nu, N, R, Rt, live);
+    MBT_LAUNCH_CHECK();
+}
+
 void launch_dcgs2_update24(const p24x2* V, int64_t vs, int k, float2* u, const float2* w, p24x2* vk,
                            const double2* cs, const double2* cc, const double* inv_nu, int64_t N, int R, int Rt,
                            const unsigned long long* live, hipStream_t s) {
-    constexpr int RB = 8;
     MBT_REQUIRE(R % 2 == 0, "packed basis needs an even number of RHS");
-    const int64_t rows_per_block = 4 * RB;
-    const int64_t gy = (N + rows_per_block - 1) / rows_per_block;
-    MBT_REQUIRE(gy < 65536, "dcgs2 update: too many row blocks");
     MBT_REQUIRE(Rt % 2 == 0 && R % Rt == 0, "packed basis: folded width must be a multiple of the even RHS count");
-    hipLaunchKernelGGL((dcgs2_update_rows24_kernel<RB>), dim3((unsigned)((R / 2 + 63) / 64), (unsigned)gy), dim3(256), 0,
-                       s, V, vs, k, u, w, vk, cs, cc, inv_nu, N, R, Rt, live);
-    MBT_LAUNCH_CHECK();
+    if (few_waves(N, R / 2)) launch_dcgs2_update24_rb<2, 4>(V, vs, k, u, w, vk, cs, cc, inv_nu, N, R, Rt, live, s);
+    else launch_dcgs2_update24_rb<8, 1>(V, vs, k, u, w, vk, cs, cc, inv_nu, N, R, Rt, live, s);
 }
 
 // End of a cycle: x += sum_{i < steps} y_i V_i.  Each wave owns RB rows of 64
 // lanes (RPL adjacent RHS per lane) and walks the vectors in order, so a
 // RHS's sum has the same order whatever the batch and however long the cycle
 // of the other RHS ran.
-template <typename TV, int RPL, int RB>
+template <typename TV, int RPL, int RB, int VU>
 __global__ __launch_bounds__(256) void solution_update_kernel(const TV* __restrict__ V, int64_t vstride, int steps,
                                                               const double2* __restrict__ y_, double2* __restrict__ x,
                                                               int64_t N, int R, int Rt) {
@@ -874,37 +898,39 @@ __global__ __launch_bounds__(256) void solution_update_kernel(const TV* __restri
     for (int j = 0; j < RB; ++j)
 #pragma unroll
         for (int q = 0; q < RPL; ++q) acc[j][q] = make_double2(0, 0);
-    Raw<TV, RPL> cur[RB], nxt[RB];
-    auto load = [&](int i, Raw<TV, RPL>(&v)[RB]) {
+    Raw<TV, RPL> cur[VU][RB], nxt[VU][RB];
+    double2 yc[VU][RPL], yn[VU][RPL];
+    auto load = [&](int i0, Raw<TV, RPL>(&v)[VU][RB], double2(&c)[VU][RPL]) {
 #pragma unroll
-        for (int j = 0; j < RB; ++j) {
-            if (j < nr) v[j].load(V + i * vstride + vofs<TV>((n0 + j) * R + r0));
-            else v[j].zero();
+        for (int e = 0; e < VU; ++e) {
+            const int i = i0 + e;
+#pragma unroll
+            for (int q = 0; q < RPL; ++q) c[e][q] = i < steps ? y[(int64_t)i * Rt + q] : make_double2(0, 0);
+#pragma unroll
+            for (int j = 0; j < RB; ++j) {
+                if (i < steps && j < nr) v[e][j].load(V + i * vstride + vofs<TV>((n0 + j) * R + r0));
+                else v[e][j].zero();
+            }
         }
     };
-    double2 yc[RPL];
-    if (steps > 0) {
-        load(0, cur);
+    load(0, cur, yc);
+    for (int i = 0; i < steps; i += VU) {
+        load(i + VU, nxt, yn);
 #pragma unroll
-        for (int q = 0; q < RPL; ++q) yc[q] = y[q];
-    }
-    for (int i = 0; i < steps; ++i) {
-        double2 yn[RPL];
+        for (int e = 0; e < VU; ++e) {
+            if (VU > 1 && i + e >= steps) break;
 #pragma unroll
-        for (int q = 0; q < RPL; ++q) yn[q] = make_double2(0, 0);
-        if (i + 1 < steps) {
-            load(i + 1, nxt);
+            for (int j = 0; j < RB; ++j)
 #pragma unroll
-            for (int q = 0; q < RPL; ++q) yn[q] = y[(int64_t)(i + 1) * Rt + q];
+                for (int q = 0; q < RPL; ++q) acc[j][q] = cfma(acc[j][q], yc[e][q], cur[e][j].get(q));
         }
 #pragma unroll
-        for (int j = 0; j < RB; ++j)
+        for (int e = 0; e < VU; ++e) {
 #pragma unroll
-            for (int q = 0; q < RPL; ++q) acc[j][q] = cfma(acc[j][q], yc[q], cur[j].get(q));
+            for (int j = 0; j < RB; ++j) cur[e][j] = nxt[e][j];
 #pragma unroll
-        for (int j = 0; j < RB; ++j) cur[j] = nxt[j];
-#pragma unroll
-        for (int q = 0; q < RPL; ++q) yc[q] = yn[q];
+            for (int q = 0; q < RPL; ++q) yc[e][q] = yn[e][q];
+        }
     }
 #pragma unroll
     for (int j = 0; j < RB; ++j) {
@@ -916,22 +942,24 @@ __global__ __launch_bounds__(256) void solution_update_kernel(const TV* __restri
     }
 }
 
+template <typename TV, int RPL, int RB, int VU>
+void launch_solution_update_rb(const TV* V, int64_t vs, int steps, const double2* y, double2* x, int64_t N, int R,
+                               int Rt, hipStream_t s) {
+    const int64_t gy = (N + 4 * RB - 1) / (4 * RB);
+    MBT_REQUIRE(gy < 65536, "solution update: too many row blocks");
+    hipLaunchKernelGGL((solution_update_kernel<TV, RPL, RB, VU>), dim3((unsigned)((R / RPL + 63) / 64), (unsigned)gy),
+                       dim3(256), 0, s, V, vs, steps, y, x, N, R, Rt);
+    MBT_LAUNCH_CHECK();
+}
+
 template <typename TV>
 void launch_solution_update(const TV* V, int64_t vs, int steps, const double2* y, double2* x, int64_t N, int R,
                             int Rt, hipStream_t s) {
     MBT_REQUIRE(R % Rt == 0, "folded width must be a multiple of the RHS count");
-    constexpr int RB = 8;
-    const int64_t gy = (N + 4 * RB - 1) / (4 * RB);
-    MBT_REQUIRE(gy < 65536, "solution update: too many row blocks");
-    if constexpr (std::is_same<TV, p24x2>::value) {
-        MBT_REQUIRE(R % 2 == 0, "packed basis needs an even number of RHS");
-        hipLaunchKernelGGL((solution_update_kernel<TV, 2, RB>), dim3((unsigned)((R / 2 + 63) / 64), (unsigned)gy),
-                           dim3(256), 0, s, V, vs, steps, y, x, N, R, Rt);
-    } else {
-        hipLaunchKernelGGL((solution_update_kernel<TV, 1, RB>), dim3((unsigned)((R + 63) / 64), (unsigned)gy),
-                           dim3(256), 0, s, V, vs, steps, y, x, N, R, Rt);
-    }
-    MBT_LAUNCH_CHECK();
+    constexpr int RPL = PerWord<TV>::v;
+    MBT_REQUIRE(R % RPL == 0, "packed basis needs an even number of RHS");
+    if (few_waves(N, R / RPL)) launch_solution_update_rb<TV, RPL, 2, 4>(V, vs, steps, y, x, N, R, Rt, s);
+    else launch_solution_update_rb<TV, RPL, 8, 1>(V, vs, steps, y, x, N, R, Rt, s);
 }
 
 template <typename TB, typename TV>
@@ -957,18 +985,24 @@ void launch_dcgs2_dots(const TV* V, int64_t vs, int k, const TB* u, const TB* w,
     }
 }
 
+template <typename TB, int RB, int VU>
+void launch_dcgs2_update_rb(const TB* V, int64_t vs, int k, TB* u, TB* w, const double2* cs, const double2* cc,
+                            const double* inv_nu, int64_t N, int R, int Rt, const unsigned long long* live,
+                            hipStream_t s) {
+    const int64_t gy = (N + 4 * RB - 1) / (4 * RB);
+    MBT_REQUIRE(gy < 65536, "dcgs2 update: too many row blocks");
+    hipLaunchKernelGGL((dcgs2_update_rows_kernel<TB, RB, VU>), dim3((unsigned)((R + 63) / 64), (unsigned)gy), dim3(256), 0,
+                       s, V, vs, k, u, w, cs, cc, inv_nu, N, R, Rt, live);
+    MBT_LAUNCH_CHECK();
+}
+
 template <typename TB>
 void launch_dcgs2_update(const TB* V, int64_t vs, int k, TB* u, TB* w, const double2* cs, const double2* cc,
                          const double* inv_nu, int64_t N, int R, int Rt, const unsigned long long* live,
                          hipStream_t s) {
     MBT_REQUIRE(R % Rt == 0, "folded width must be a multiple of the RHS count");
-    constexpr int RB = 8;
-    const int64_t rows_per_block = 4 * RB;
-    const int64_t gy = (N + rows_per_block - 1) / rows_per_block;
-    MBT_REQUIRE(gy < 65536, "dcgs2 update: too many row blocks");
-    hipLaunchKernelGGL((dcgs2_update_rows_kernel<TB, RB>), dim3((unsigned)((R + 63) / 64), (unsigned)gy), dim3(256), 0,
-                       s, V, vs, k, u, w, cs, cc, inv_nu, N, R, Rt, live);
-    MBT_LAUNCH_CHECK();
+    if (few_waves(N, R)) launch_dcgs2_update_rb<TB, 2, 4>(V, vs, k, u, w, cs, cc, inv_nu, N, R, Rt, live, s);
+    else launch_dcgs2_update_rb<TB, 8, 1>(V, vs, k, u, w, cs, cc, inv_nu, N, R, Rt, live, s);
 }
 
 template <typename TB, typename TO, int MODE, int RPL>
@@ -1061,19 +1095,29 @@ void launch_reduce_partials(const double2* partial, int nchunk, int nvec, int R,
     MBT_LAUNCH_CHECK();
 }
 
+// partial[chunk][r] = sum over the chunk's rows of |X[n][r]|^2: the rows are dealt to
+// kNormWaves running sums (row n0 + j to sum j mod kNormWaves), added in order
+constexpr int kNormWaves = 8;
 template <typename TB>
-__global__ void colnorm2_kernel(const TB* __restrict__ X, int64_t N, int R, int64_t rows_per_chunk,
-                                double2* __restrict__ partial) {
-    const int r = blockIdx.x * blockDim.x + threadIdx.x;
+__global__ __launch_bounds__(64 * kNormWaves) void colnorm2_kernel(const TB* __restrict__ X, int64_t N, int R,
+                                                                   int64_t rows_per_chunk,
+                                                                   double2* __restrict__ partial) {
+    __shared__ double gs[kNormWaves][64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int r = blockIdx.x * 64 + lane;
     const int64_t chunk = blockIdx.y;
-    if (r >= R) return;
     const int64_t n0 = chunk * rows_per_chunk, n1 = min(N, n0 + rows_per_chunk);
     double s = 0;
-    for (int64_t n = n0; n < n1; ++n) {
-        const double2 v = ld2(X + n * R + r);
-        s = nfma(s, v);
+    if (r < R) {
+#pragma unroll 4
+        for (int64_t n = n0 + wave; n < n1; n += kNormWaves) s = nfma(s, ld2(X + n * R + r));
     }
-    partial[chunk * R + r] = make_double2(s, 0.0);
+    gs[wave][lane] = s;
+    __syncthreads();
+    if (wave == 0 && r < R) {
+        for (int q = 1; q < kNormWaves; ++q) s += gs[q][lane];
+        partial[chunk * R + r] = make_double2(s, 0.0);
+    }
 }
 
 __device__ __forceinline__ double sum_norm_partials(const double2* partial, int nchunk, int R, int r) {
@@ -1196,25 +1240,48 @@ __global__ void scale_cols_kernel(TB* __restrict__ v, const double* __restrict__
 
 // End of cycle: y = R_k^{-1} g_k per RHS (k = steps done this cycle); |g_k|
 // meeting the tolerance makes the RHS a candidate, which the explicit residual
-// of the next restart confirms.  Launched with at least m + 2 threads.
-__global__ void cycle_solve_kernel(GmresState st, int R, int m, double2* __restrict__ y,
-                                   unsigned long long* __restrict__ counters) {
-    const int r = blockIdx.x * blockDim.x + threadIdx.x;
-    if (r <= m + 1) counters[r] = 0;   // for the next cycle
-    if (r >= R) return;
-    const int k = st.kcyc[r];
+// of the next restart confirms.  The back substitution is a chain of k steps: a
+// wave owns one RHS with row l of the triangle in lane l (k <= 63), the triangle
+// staged in LDS with all its loads in flight (a thread per RHS that reads it
+// entry by entry takes 160 us at k = 32 and 455 us at k = 50, 128 RHS).
+// Launched with at least m + 2 threads.
+constexpr int kSolveR = 4;
+__global__ __launch_bounds__(64 * kSolveR) void cycle_solve_kernel(GmresState st, int R, int m, double2* __restrict__ y,
+                                                                   unsigned long long* __restrict__ counters) {
+    __shared__ double2 tri[kSolveR][kMaxVec * (kMaxVec - 1) / 2];   // column i at i (i + 1) / 2, rows 0..i
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    if (blockIdx.x == 0 && threadIdx.x <= m + 1) counters[threadIdx.x] = 0;   // for the next cycle
+    const int rb = blockIdx.x * kSolveR;
     const int64_t ldH = (int64_t)(m + 1) * R;
-    for (int i = 0; i < m; ++i) y[(int64_t)i * R + r] = make_double2(0, 0);
-    if (k == 0 || st.flag[r]) return;
-    for (int i = k - 1; i >= 0; --i) {
-        double2 acc = st.g[(int64_t)i * R + r];
-        for (int l = i + 1; l < k; ++l) acc = csub(acc, cmul(st.H[(int64_t)l * ldH + (int64_t)i * R + r], y[(int64_t)l * R + r]));
-        const double2 d = st.H[(int64_t)i * ldH + (int64_t)i * R + r];
-        const double den = d.x * d.x + d.y * d.y;
-        y[(int64_t)i * R + r] = make_double2((acc.x * d.x + acc.y * d.y) / den, (acc.y * d.x - acc.x * d.y) / den);
+    {
+        // adjacent threads load the same entry of the workgroup's adjacent RHS
+        const int q = threadIdx.x % kSolveR, e0 = threadIdx.x / kSolveR;
+        const int r = rb + q;
+        const int kq = r < R && !st.flag[r] ? st.kcyc[r] : 0;
+        const double2* Hl = st.H + (int64_t)e0 * R + r;
+#pragma unroll 8
+        for (int i = 0; i < kq; ++i)
+            if (e0 <= i) tri[q][i * (i + 1) / 2 + e0] = Hl[(int64_t)i * ldH];
     }
-    const double2 gk = st.g[(int64_t)k * R + r];
-    st.cand[r] = hypot(gk.x, gk.y) <= st.tol * st.bnorm[r] ? 1 : 0;
+    __syncthreads();
+    const int r = rb + wave;
+    if (r >= R) return;
+    const int k = st.flag[r] ? 0 : st.kcyc[r];
+    double2 acc = lane < k ? st.g[(int64_t)lane * R + r] : make_double2(0, 0);
+    double2 mine = make_double2(0, 0);
+    for (int i = k - 1; i >= 0; --i) {
+        const double2 d = tri[wave][i * (i + 1) / 2 + i];
+        const double2 a = make_double2(__shfl(acc.x, i), __shfl(acc.y, i));
+        const double den = d.x * d.x + d.y * d.y;
+        const double2 yi = make_double2((a.x * d.x + a.y * d.y) / den, (a.y * d.x - a.x * d.y) / den);
+        if (lane == i) mine = yi;
+        if (lane < i) acc = csub(acc, cmul(tri[wave][i * (i + 1) / 2 + lane], yi));
+    }
+    if (lane < m) y[(int64_t)lane * R + r] = mine;
+    if (lane == 0 && k > 0) {
+        const double2 gk = st.g[(int64_t)k * R + r];
+        st.cand[r] = hypot(gk.x, gk.y) <= st.tol * st.bnorm[r] ? 1 : 0;
+    }
 }
 
 // sum of active flags into one int (single workgroup)
@@ -1428,7 +1495,7 @@ GmresResult gmres_batched(const std::function<void(const TB*, TB*)>& apply, cons
     for (int cycle = 0;; ++cycle) {
         // beta = ||r|| (r sits in V_0, or in the candidate vector when packed);
         // the convergence verdict of the previous cycle is taken on it
-        hipLaunchKernelGGL((colnorm2_kernel<TB>), dim3((R + 63) / 64, nchunk), dim3(64), 0, s, r0v, N, R, rpc, partial);
+        hipLaunchKernelGGL((colnorm2_kernel<TB>), dim3((R + 63) / 64, nchunk), dim3(64 * kNormWaves), 0, s, r0v, N, R, rpc, partial);
         launch_reduce_partials(partial, nchunk, 1, R, 1, nrm2, s);
         const uint32_t gen = (uint32_t)++*prm.host_gen;
         hipLaunchKernelGGL(cycle_init_kernel, gR, bR, 0, s, st, nrm2, R, first ? 1 : 0, counters + m + 1, slots + m + 1,
@@ -1510,7 +1577,8 @@ GmresResult gmres_batched(const std::function<void(const TB*, TB*)>& apply, cons
             if (count_active() == 0) break;
         }
         // y = R^{-1} g ; x += V y
-        hipLaunchKernelGGL(cycle_solve_kernel, gR, bR, 0, s, st, R, m, y, counters);
+        hipLaunchKernelGGL(cycle_solve_kernel, dim3((R + kSolveR - 1) / kSolveR), dim3(64 * kSolveR), 0, s, st, R, m, y,
+                           counters);
         MBT_LAUNCH_CHECK();
         // configuration fixed by m: a RHS's update x += V y does not depend on how long
         // the other RHS of the batch kept the cycle going

@@ -75,19 +75,33 @@ __global__ void sub_kernel(const double2* __restrict__ a, const double2* __restr
         o[i] = csub(a[i], b[i]);
 }
 
-// partial[chunk][r] = sum over rows of chunk |X[n][r]|^2 ; chunks of rows fixed by N only
-__global__ void colnorm_partial_kernel(const double2* __restrict__ X, int64_t N, int R, int64_t rows_per_chunk,
-                                       double* __restrict__ partial) {
-    const int r = blockIdx.x * blockDim.x + threadIdx.x;
+// partial[chunk][r] = sum over rows of chunk |X[n][r]|^2 ; chunks of rows fixed by N only.
+// The rows are dealt to the workgroup's waves (row n0 + j to wave j mod kNormWaves) and
+// the waves' sums added in order: one wave walking 256 rows waits for each (66 us at any
+// size).
+constexpr int kNormWaves = 16;
+__global__ __launch_bounds__(64 * kNormWaves) void colnorm_partial_kernel(const double2* __restrict__ X, int64_t N,
+                                                                          int R, int64_t rows_per_chunk,
+                                                                          double* __restrict__ partial) {
+    __shared__ double gs[kNormWaves][64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int r = blockIdx.x * 64 + lane;
     const int64_t chunk = blockIdx.y;
-    if (r >= R) return;
     const int64_t n0 = chunk * rows_per_chunk, n1 = min(N, n0 + rows_per_chunk);
     double s = 0;
-    for (int64_t n = n0; n < n1; ++n) {
-        const double2 v = X[n * R + r];
-        s += v.x * v.x + v.y * v.y;
+    if (r < R) {
+#pragma unroll 4
+        for (int64_t n = n0 + wave; n < n1; n += kNormWaves) {
+            const double2 v = X[n * R + r];
+            s += v.x * v.x + v.y * v.y;
+        }
     }
-    partial[chunk * R + r] = s;
+    gs[wave][lane] = s;
+    __syncthreads();
+    if (wave == 0 && r < R) {
+        for (int q = 1; q < kNormWaves; ++q) s += gs[q][lane];
+        partial[chunk * R + r] = s;
+    }
 }
 
 // out[r] = sqrt(sum over chunks of partial[c][r]): groups of 64 consecutive
@@ -227,7 +241,8 @@ void column_norms(const double2* X, int64_t N, int R, double* partial, double* o
     // at least 256 rows per chunk, at most kNormMaxChunks chunks (partial holds ceil(N/256) x R)
     const int64_t rpc = std::max<int64_t>(256, (N + kNormMaxChunks - 1) / kNormMaxChunks);
     const int nchunk = (int)((N + rpc - 1) / rpc);
-    hipLaunchKernelGGL(colnorm_partial_kernel, dim3((R + 63) / 64, nchunk), dim3(64), 0, s, X, N, R, rpc, partial);
+    hipLaunchKernelGGL(colnorm_partial_kernel, dim3((R + 63) / 64, nchunk), dim3(64 * kNormWaves), 0, s, X, N, R, rpc,
+                       partial);
     MBT_LAUNCH_CHECK();
     hipLaunchKernelGGL(colnorm_final_kernel, dim3((R + 63) / 64), dim3(512), 0, s, partial, nchunk, R, out);
     MBT_LAUNCH_CHECK();
