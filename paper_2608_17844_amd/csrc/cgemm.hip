@@ -14,7 +14,7 @@
 // result are (p, re/im) pairs, so each lane's four accumulator rows are two
 // complete complex outputs.
 //
-// Each wave keeps its A_b fragments in registers and streams 16-column tiles
+// Each wave keeps fragments of A_b in registers and streams 16-column tiles
 // of X_b; M is padded to MP (16 or 32) with predicated loads and stores.  At
 // M = 31 the FP64 product has about 8 flop/byte (below the FP64 MFMA ridge of
 // 9.8) and the FP32 one about 16 (below 19.7): both are HBM-bound.
@@ -38,22 +38,40 @@ __device__ __forceinline__ f4 mfma(float a, float b, f4 c) {
     return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
 }
 
-template <typename T, int MP, bool HERM>
+// CPL adjacent columns of X as one access: 16 bytes in FP64 (one column) and in
+// FP32 with two.
+template <typename T, int CPL> struct ColPack { cplx<T> c[CPL]; };
+
+// A wave holds the fragments of RTW of the block's 16-row tiles and streams
+// columns of X; the workgroup's waves that share columns (NRT / RTW of them) read
+// the same ones, which then come from L1.  RTW = NRT keeps most loads of X in
+// flight per workgroup (every wave has columns of its own) but needs 220-256
+// registers and loads the block once per wave; a smaller RTW frees registers for
+// more waves and loads the block once per workgroup.  Measured at 31 bases, 4,096
+// bins (RTW 4 / 2 / 1, us): FP64, 1024 columns 770 / 766 / 833, 128 columns 157 /
+// 114 / 117; FP32, 1024 columns 400 / 423 / 499, 128 columns 77 / 63 / 69; 8,192
+// bins of 64 columns: FP64 220 / 133 / 123, FP32 112 / 74 / 68.
+template <typename T, int MP, bool HERM, int CPL, int RTW>
 __global__ __launch_bounds__(256) void cgemm_kernel(const cplx<T>* __restrict__ A, int64_t strideA,
                                                     const cplx<T>* __restrict__ X, cplx<T>* __restrict__ Y, int M,
                                                     int R, int groups, int tpw) {
     using C = cplx<T>;
     using V = typename Acc<T>::type;
-    constexpr int NRT = MP / 8;   // 16-row tiles of the 2MP-row real matrix
-    constexpr int NS = MP / 4;    // complex K groups of 4
+    using XP = ColPack<T, CPL>;
+    constexpr int NRT = MP / 8;      // 16-row tiles of the 2MP-row real matrix
+    constexpr int NS = MP / 4;       // complex K groups of 4
+    constexpr int RG = NRT / RTW;    // wave groups along the rows
+    constexpr int CTW = 4 / RG;      // column tiles in flight per workgroup
+    constexpr int WT = 16 * CPL;     // columns per tile
     const int lane = threadIdx.x & 63;
-    const int wave = threadIdx.x >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t b = blockIdx.x / groups;
     const int grp = blockIdx.x % groups;
-    const int ntiles = (R + 15) >> 4;
-    const int t0 = (grp * 4 + wave) * tpw;
-    if (t0 >= ntiles) return;
-    const int t1 = min(t0 + tpw, ntiles);
+    const int ntiles = (R + WT - 1) / WT;
+    const int rt0 = (wave % RG) * RTW;   // this wave's first row tile
+    const int t0 = grp * tpw + wave / RG;
+    const int t1 = min((grp + 1) * tpw, ntiles);
+    if (t0 >= t1) return;
 
     const C* Ab = A + b * strideA;
     const C* Xb = X + b * (int64_t)M * R;
@@ -61,23 +79,45 @@ __global__ __launch_bounds__(256) void cgemm_kernel(const cplx<T>* __restrict__ 
     const int g = lane >> 4;       // lane group: K slot inside a group of 4
     const int li = lane & 15;
 
+    XP bcur[NS], bnext[NS];
+    auto load = [&](int tile, XP* dst) {
+        const int col = tile * WT + CPL * li;
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+            const int q = 4 * s + g;
+            if (q < M && col < R) {
+                if constexpr (sizeof(T) == 4 && CPL == 2) {
+                    const float4 v = *reinterpret_cast<const float4*>(Xb + (int64_t)q * R + col);
+                    dst[s].c[0] = mk<T>(v.x, v.y);
+                    dst[s].c[1] = mk<T>(v.z, v.w);
+                } else {
+                    dst[s].c[0] = Xb[(int64_t)q * R + col];
+                }
+            } else {
+#pragma unroll
+                for (int h = 0; h < CPL; ++h) dst[s].c[h] = mk<T>(0, 0);
+            }
+        }
+    };
+    load(t0, bcur);
+
     // A fragments: lane li supplies row li of the tile; K slot q = 4s + g.
     // The accumulator of row i sits in lane group i%4, register i/4 for the
     // f64 16x16x4 MFMA, and in lane group i/4, register i%4 for the f32 one;
     // the row -> (p, re/im) assignment is chosen per type so that every lane
     // ends with registers {(p0, re), (p0, im), (p0+1, re), (p0+1, im)},
     // p0 = 8t + 2*(lane/16).
-    T are[NRT][NS], aim[NRT][NS];
+    T are[RTW][NS], aim[RTW][NS];
 #pragma unroll
-    for (int t = 0; t < NRT; ++t) {
+    for (int t = 0; t < RTW; ++t) {
         int p;
         bool odd;
         if constexpr (sizeof(T) == 8) {
             const int v = li >> 2, gg = li & 3;
-            p = 8 * t + 2 * gg + (v >> 1);
+            p = 8 * (rt0 + t) + 2 * gg + (v >> 1);
             odd = v & 1;
         } else {
-            const int rho = 16 * t + li;
+            const int rho = 16 * (rt0 + t) + li;
             p = rho >> 1;
             odd = rho & 1;
         }
@@ -93,37 +133,38 @@ __global__ __launch_bounds__(256) void cgemm_kernel(const cplx<T>* __restrict__ 
             aim[t][s] = odd ? c.x : -c.y;
         }
     }
-
-    C bcur[NS], bnext[NS];
-    auto load = [&](int tile, C* dst) {
-        const int col = tile * 16 + li;
+    for (int tile = t0; tile < t1; tile += CTW) {
+        if (tile + CTW < t1) load(tile + CTW, bnext);
+        V acc[RTW][CPL];
 #pragma unroll
-        for (int s = 0; s < NS; ++s) {
-            const int q = 4 * s + g;
-            dst[s] = (q < M && col < R) ? Xb[(int64_t)q * R + col] : mk<T>(0, 0);
-        }
-    };
-    load(t0, bcur);
-    for (int tile = t0; tile < t1; ++tile) {
-        if (tile + 1 < t1) load(tile + 1, bnext);
-        V acc[NRT];
+        for (int t = 0; t < RTW; ++t)
 #pragma unroll
-        for (int t = 0; t < NRT; ++t) acc[t] = V{0, 0, 0, 0};
+            for (int h = 0; h < CPL; ++h) acc[t][h] = V{0, 0, 0, 0};
 #pragma unroll
         for (int s = 0; s < NS; ++s) {
 #pragma unroll
-            for (int t = 0; t < NRT; ++t) {
-                acc[t] = mfma(are[t][s], bcur[s].x, acc[t]);
-                acc[t] = mfma(aim[t][s], bcur[s].y, acc[t]);
-            }
+            for (int t = 0; t < RTW; ++t)
+#pragma unroll
+                for (int h = 0; h < CPL; ++h) {
+                    acc[t][h] = mfma(are[t][s], bcur[s].c[h].x, acc[t][h]);
+                    acc[t][h] = mfma(aim[t][s], bcur[s].c[h].y, acc[t][h]);
+                }
         }
-        const int col = tile * 16 + li;
+        const int col = tile * WT + CPL * li;
         if (col < R) {
 #pragma unroll
-            for (int t = 0; t < NRT; ++t) {
-                const int p0 = 8 * t + 2 * g;
-                if (p0 < M) Yb[(int64_t)p0 * R + col] = mk<T>(acc[t][0], acc[t][1]);
-                if (p0 + 1 < M) Yb[(int64_t)(p0 + 1) * R + col] = mk<T>(acc[t][2], acc[t][3]);
+            for (int t = 0; t < RTW; ++t) {
+                const int p0 = 8 * (rt0 + t) + 2 * g;
+#pragma unroll
+                for (int e = 0; e < 2; ++e)
+                    if (p0 + e < M) {
+                        C* yp = Yb + (int64_t)(p0 + e) * R + col;
+                        if constexpr (sizeof(T) == 4 && CPL == 2)
+                            *reinterpret_cast<float4*>(yp) = make_float4(acc[t][0][2 * e], acc[t][0][2 * e + 1],
+                                                                         acc[t][1][2 * e], acc[t][1][2 * e + 1]);
+                        else
+                            *yp = mk<T>(acc[t][0][2 * e], acc[t][0][2 * e + 1]);
+                    }
             }
         }
 #pragma unroll
@@ -131,92 +172,44 @@ __global__ __launch_bounds__(256) void cgemm_kernel(const cplx<T>* __restrict__ 
     }
 }
 
-// FP32 with an even number of columns: each lane carries two adjacent columns,
-// so every access of X and Y is 16 bytes; a wave tile is 32 columns, run as two
-// interleaved 16-column MFMA products with the same fragments of A (per column
-// the arithmetic and its order are those of cgemm_kernel).
-template <int MP, bool HERM>
-__global__ __launch_bounds__(256) void cgemm_pair_kernel(const float2* __restrict__ A, int64_t strideA,
-                                                         const float2* __restrict__ X, float2* __restrict__ Y, int M,
-                                                         int R, int groups, int tpw) {
-    using V = f4;
-    constexpr int NRT = MP / 8;
-    constexpr int NS = MP / 4;
-    const int lane = threadIdx.x & 63;
-    const int wave = threadIdx.x >> 6;
-    const int64_t b = blockIdx.x / groups;
-    const int grp = blockIdx.x % groups;
-    const int ntiles = (R + 31) >> 5;
-    const int t0 = (grp * 4 + wave) * tpw;
-    if (t0 >= ntiles) return;
-    const int t1 = min(t0 + tpw, ntiles);
+template <typename T, int MP, int CPL, int RTW>
+void launch_mp_rtw(const cplx<T>* A, int64_t strideA, const cplx<T>* X, cplx<T>* Y, int M, int R, int64_t nbatch,
+                   int op, hipStream_t s) {
+    constexpr int CTW = 4 * RTW / (MP / 8);
+    const int ntiles = (R + 16 * CPL - 1) / (16 * CPL);
+    // A workgroup takes up to eight rounds of CTW tiles (four with RTW = 4, the same tiles), which amortises
+    // its fragments (16 bases: four, or two of a long row: its blocks are small), in groups of the same
+    // length: at 187 columns in FP64, 12 tiles as 8 + 4 take 119 us and as one group 95.
+    const int rounds = (ntiles + CTW - 1) / CTW;
+    const int most = MP == 32 ? (RTW == 4 ? 4 : 8) : (rounds <= 4 ? 4 : 2);
+    const int groups0 = (rounds + most - 1) / most;
+    const int tpw = (rounds + groups0 - 1) / groups0 * CTW;
+    const int groups = (ntiles + tpw - 1) / tpw;
+    const int64_t blocks = nbatch * groups;
+    MBT_REQUIRE(blocks < (1LL << 31), "cgemm: grid too large");
+    if (op == 0)
+        hipLaunchKernelGGL((cgemm_kernel<T, MP, false, CPL, RTW>), dim3((unsigned)blocks), dim3(256), 0, s, A, strideA,
+                           X, Y, M, R, groups, tpw);
+    else
+        hipLaunchKernelGGL((cgemm_kernel<T, MP, true, CPL, RTW>), dim3((unsigned)blocks), dim3(256), 0, s, A, strideA, X,
+                           Y, M, R, groups, tpw);
+    MBT_LAUNCH_CHECK();
+}
 
-    const float2* Ab = A + b * strideA;
-    const float2* Xb = X + b * (int64_t)M * R;
-    float2* Yb = Y + b * (int64_t)M * R;
-    const int g = lane >> 4;
-    const int li = lane & 15;
-
-    float are[NRT][NS], aim[NRT][NS];
-#pragma unroll
-    for (int t = 0; t < NRT; ++t) {
-        const int rho = 16 * t + li;
-        const int p = rho >> 1;
-        const bool odd = rho & 1;
-#pragma unroll
-        for (int s = 0; s < NS; ++s) {
-            const int q = 4 * s + g;
-            float2 c = make_float2(0.f, 0.f);
-            if (p < M && q < M) {
-                c = HERM ? Ab[(int64_t)q * M + p] : Ab[(int64_t)p * M + q];
-                if (HERM) c.y = -c.y;
-            }
-            are[t][s] = odd ? c.y : c.x;
-            aim[t][s] = odd ? c.x : -c.y;
-        }
-    }
-
-    float4 bcur[NS], bnext[NS];
-    auto load = [&](int tile, float4* dst) {
-        const int col = tile * 32 + 2 * li;
-#pragma unroll
-        for (int s = 0; s < NS; ++s) {
-            const int q = 4 * s + g;
-            dst[s] = (q < M && col < R) ? *reinterpret_cast<const float4*>(Xb + (int64_t)q * R + col)
-                                        : make_float4(0.f, 0.f, 0.f, 0.f);
-        }
-    };
-    load(t0, bcur);
-    for (int tile = t0; tile < t1; ++tile) {
-        if (tile + 1 < t1) load(tile + 1, bnext);
-        V acc0[NRT], acc1[NRT];
-#pragma unroll
-        for (int t = 0; t < NRT; ++t) acc0[t] = acc1[t] = V{0, 0, 0, 0};
-#pragma unroll
-        for (int s = 0; s < NS; ++s) {
-#pragma unroll
-            for (int t = 0; t < NRT; ++t) {
-                acc0[t] = mfma(are[t][s], bcur[s].x, acc0[t]);
-                acc0[t] = mfma(aim[t][s], bcur[s].y, acc0[t]);
-                acc1[t] = mfma(are[t][s], bcur[s].z, acc1[t]);
-                acc1[t] = mfma(aim[t][s], bcur[s].w, acc1[t]);
-            }
-        }
-        const int col = tile * 32 + 2 * li;
-        if (col < R) {
-#pragma unroll
-            for (int t = 0; t < NRT; ++t) {
-                const int p0 = 8 * t + 2 * g;
-                if (p0 < M)
-                    *reinterpret_cast<float4*>(Yb + (int64_t)p0 * R + col) =
-                        make_float4(acc0[t][0], acc0[t][1], acc1[t][0], acc1[t][1]);
-                if (p0 + 1 < M)
-                    *reinterpret_cast<float4*>(Yb + (int64_t)(p0 + 1) * R + col) =
-                        make_float4(acc0[t][2], acc0[t][3], acc1[t][2], acc1[t][3]);
-            }
-        }
-#pragma unroll
-        for (int s = 0; s < NS; ++s) bcur[s] = bnext[s];
+// Row tiles per wave by the length of a row in tiles (of 16 or 32 columns): as few as
+// the row needs to occupy the waves, and FP32 blocks, which fit the registers, whole
+// from eight tiles on.
+template <typename T, int MP, int CPL>
+void launch_mp_cpl(const cplx<T>* A, int64_t strideA, const cplx<T>* X, cplx<T>* Y, int M, int R, int64_t nbatch,
+                   int op, hipStream_t s) {
+    const int ntiles = (R + 16 * CPL - 1) / (16 * CPL);
+    if constexpr (MP == 32) {
+        if (ntiles <= (sizeof(T) == 8 ? 4 : 2)) launch_mp_rtw<T, MP, CPL, 1>(A, strideA, X, Y, M, R, nbatch, op, s);
+        else if (sizeof(T) == 8 || ntiles < 8) launch_mp_rtw<T, MP, CPL, 2>(A, strideA, X, Y, M, R, nbatch, op, s);
+        else if constexpr (sizeof(T) == 4) launch_mp_rtw<T, MP, CPL, 4>(A, strideA, X, Y, M, R, nbatch, op, s);
+    } else {
+        if (ntiles <= 2) launch_mp_rtw<T, MP, CPL, 1>(A, strideA, X, Y, M, R, nbatch, op, s);
+        else launch_mp_rtw<T, MP, CPL, 2>(A, strideA, X, Y, M, R, nbatch, op, s);
     }
 }
 
@@ -224,42 +217,14 @@ template <typename T, int MP>
 void launch_mp(const cplx<T>* A, int64_t strideA, const cplx<T>* X, cplx<T>* Y, int M, int R, int64_t nbatch,
                int op, hipStream_t s) {
     if constexpr (sizeof(T) == 4) {
+        // FP32 with an even number of columns: two adjacent columns per lane, so every
+        // access of X and Y is 16 bytes (per column the arithmetic is the same)
         if (R % 2 == 0 && ((reinterpret_cast<uintptr_t>(X) | reinterpret_cast<uintptr_t>(Y)) & 15) == 0) {
-            const int ntiles = (R + 31) / 32;
-            const int64_t total = nbatch * ntiles;
-            int tpw = (int)std::max<int64_t>(1, std::min<int64_t>(4, total / 32768));
-            if (strideA == 0) tpw = 4;
-            tpw = std::min(tpw, ntiles);
-            const int groups = (ntiles + 4 * tpw - 1) / (4 * tpw);
-            const int64_t blocks = nbatch * groups;
-            MBT_REQUIRE(blocks < (1LL << 31), "cgemm: grid too large");
-            if (op == 0)
-                hipLaunchKernelGGL((cgemm_pair_kernel<MP, false>), dim3((unsigned)blocks), dim3(256), 0, s, A, strideA,
-                                   X, Y, M, R, groups, tpw);
-            else
-                hipLaunchKernelGGL((cgemm_pair_kernel<MP, true>), dim3((unsigned)blocks), dim3(256), 0, s, A, strideA,
-                                   X, Y, M, R, groups, tpw);
-            MBT_LAUNCH_CHECK();
+            launch_mp_cpl<T, MP, 2>(A, strideA, X, Y, M, R, nbatch, op, s);
             return;
         }
     }
-    const int ntiles = (R + 15) / 16;
-    const int64_t total = nbatch * ntiles;
-    int tpw = (int)std::max<int64_t>(1, std::min<int64_t>(8, total / 32768));
-    // one block shared by every batch entry (the element-block preconditioner):
-    // longer runs of tiles per wave amortise loading its fragments
-    if (strideA == 0) tpw = 8;
-    tpw = std::min(tpw, ntiles);
-    const int groups = (ntiles + 4 * tpw - 1) / (4 * tpw);
-    const int64_t blocks = nbatch * groups;
-    MBT_REQUIRE(blocks < (1LL << 31), "cgemm: grid too large");
-    if (op == 0)
-        hipLaunchKernelGGL((cgemm_kernel<T, MP, false>), dim3((unsigned)blocks), dim3(256), 0, s, A, strideA, X, Y, M,
-                           R, groups, tpw);
-    else
-        hipLaunchKernelGGL((cgemm_kernel<T, MP, true>), dim3((unsigned)blocks), dim3(256), 0, s, A, strideA, X, Y, M,
-                           R, groups, tpw);
-    MBT_LAUNCH_CHECK();
+    launch_mp_cpl<T, MP, 1>(A, strideA, X, Y, M, R, nbatch, op, s);
 }
 
 // ---------------------------------------------------------------- large blocks (M up to 128)
