@@ -171,9 +171,9 @@ void embed_blocks_fft(const Geom& g, const double2* T, double2* Chat, double sca
 // twiddle table tw[j] = exp(-2 pi i j / P), j < P
 void make_twiddles(int P, double2* tw, hipStream_t s);
 // Zero-padded forward transform of B columns and the cropped inverse.  scratch
-// (at least ny * Px * B complex values, not overlapping the operands) lets FP32
-// transforms on 128-point axes run as two passes of 1-D transforms; with NULL
-// they run as one LDS-tiled kernel.
+// (at least ny * Px * B complex values, not overlapping the operands) holds the
+// line spectra of the FP32 transforms on 128-point axes, which run as two passes
+// of 1-D transforms; the others do not use it.
 template <typename T>
 void fft_fwd_pad(const Geom& g, const cplx<T>* X, cplx<T>* Xh, int64_t B, const cplx<T>* twx,
                  const cplx<T>* twy, cplx<T>* scratch, hipStream_t s);

@@ -14,7 +14,7 @@
 // parity into four transforms of size L of pre-twiddled inputs:
 //   X[2a+al][2b+be] = DFT_{Ly x Lx}( x[iy][ix] W_Py^{al iy} W_Px^{be ix} )[a][b],
 // and the cropped inverse is the twiddled sum of the four parity sub-grids.
-// Each workgroup holds an Ly x Lx x W tile (W adjacent columns) in LDS and runs
+// Each workgroup holds W adjacent columns (in registers and an LDS tile) and runs
 // the four sub-transforms there, so X is read once and X^ written once.
 #include "common.h"
 
@@ -211,52 +211,270 @@ __global__ __launch_bounds__(kNT) void fft_fwd_pad_kernel(const cplx<T>* __restr
     }
 }
 
+// ------------------------------------------------------------------ LDS-exchanged transforms
+// One axis of length L = R1 * R2 in two register passes (n = n1 R2 + n2, k = k1 + R1 k2):
+// DFT_R1 over n1 times W_L^{n2 k1}, an exchange through LDS, DFT_R2 over n2.  A pass
+// writes back the slots that it read, so an exchange takes one barrier, and position
+// k1 R2 + k2 of a transformed axis holds element k1 + R1 k2.  The input of the first
+// pass and the output of the last go between registers and memory directly.  A
+// thread holds eight values in every pass; W adjacent columns per workgroup.
+// Eight LDS trips per x-parity and six barriers, where transforming every parity
+// grid on its own in place takes twenty and sixteen: the FP64 forward transform of
+// a 64x64 grid runs at 3.7 instead of 2.9 TB/s (3,968 columns: 114 -> 88 us; 31,744:
+// 852 -> 690), of a 32x32 grid of 2,160 columns in 12 instead of 23 us.  Four columns
+// (64-byte runs) keep two workgroups per CU at that grid; eight measured 93 us.
+template <typename T, int LX, int LY, int W> struct LdsFft {
+    static constexpr int NT = LX * LY * W / 8;
+    static constexpr int RX1 = Split<LX>::R1, RX2 = Split<LX>::R2;
+    static constexpr int RY1 = Split<LY>::R1, RY2 = Split<LY>::R2;
+    static constexpr int RS = LX * W + (W * (int)sizeof(cplx<T>) < 128 ? W : 0);   // row stride: spreads rows over the banks
+    // element of the axis at slot s
+    static __device__ __forceinline__ int xel(int s) { return s / RX2 + RX1 * (s % RX2); }
+    static __device__ __forceinline__ int yel(int s) { return s / RY2 + RY1 * (s % RY2); }
+};
+
+// Forward: per x-parity the rows are transformed once; their spectra stay in
+// registers for both y-parities.
 template <typename T, int LX, int LY, int W>
-__global__ __launch_bounds__(kNT) void fft_inv_crop_kernel(const cplx<T>* __restrict__ Yh, cplx<T>* __restrict__ Y,
-                                                           int nx, int ny, int64_t B, const cplx<T>* __restrict__ twx,
-                                                           const cplx<T>* __restrict__ twy) {
+__global__ __launch_bounds__((LdsFft<T, LX, LY, W>::NT)) void fft_fwd_lds_kernel(const cplx<T>* __restrict__ X,
+                                                                              cplx<T>* __restrict__ Xh, int nx, int ny,
+                                                                              int64_t B, const cplx<T>* __restrict__ twx,
+                                                                              const cplx<T>* __restrict__ twy) {
     using C = cplx<T>;
-    constexpr int PX = 2 * LX, NTILE = LX * LY * W;
-    constexpr int NOWN = (NTILE + kNT - 1) / kNT;
-    __shared__ C tile[NTILE];
+    using F = LdsFft<T, LX, LY, W>;
+    constexpr int NT = F::NT, RX1 = F::RX1, RX2 = F::RX2, RY1 = F::RY1, RY2 = F::RY2, RS = F::RS, PX = 2 * LX;
+    constexpr int IX1 = 8 / RX1, IY1 = 8 / RY1;
+    __shared__ C tile[LY * RS];
     const int64_t c0 = xcd_block(blockIdx.x, gridDim.x) * W;
-    C acc[NOWN];
+    const int w = threadIdx.x % W;
+    const int64_t c = c0 + w;
+    const bool cv = c < B;
+    const int q0 = threadIdx.x / W;
+    constexpr int QN = NT / W;
+    C xin[IX1][RX1];
 #pragma unroll
-    for (int i = 0; i < NOWN; ++i) acc[i] = mk<T>(0, 0);
-    for (int par = 0; par < 4; ++par) {
-        const int al = par >> 1, be = par & 1;
-        for (int t = threadIdx.x; t < NTILE; t += kNT) {
-            const int w = t % W, b = (t / W) % LX, a = t / (W * LX);
-            const int64_t c = c0 + w;
-            tile[t] = (c < B) ? Yh[((int64_t)(2 * a + al) * PX + (2 * b + be)) * B + c] : mk<T>(0, 0);
+    for (int j = 0; j < IX1; ++j) {
+        const int it = q0 + j * QN, n2 = it % RX2, iy = it / RX2;
+#pragma unroll
+        for (int n1 = 0; n1 < RX1; ++n1) {
+            const int ix = n1 * RX2 + n2;
+            xin[j][n1] = (cv && ix < nx && iy < ny) ? X[(int64_t)(iy * nx + ix) * B + c] : mk<T>(0, 0);
         }
-        __syncthreads();
-        lds_fft_axis<T, LX, true, false, kNT, LY, LX * W, W, W>(tile, twx);
-        __syncthreads();
-        lds_fft_axis<T, LY, true, true, kNT, LX, W, LX * W, W>(tile, twy);
-        __syncthreads();
+    }
 #pragma unroll
-        for (int i = 0; i < NOWN; ++i) {
-            const int t = threadIdx.x + i * kNT;
-            if (t < NTILE) {
-                const int ix = (t / W) % LX, iy = t / (W * LX);
-                if (ix < nx && iy < ny) {
-                    C v = tile[t];
-                    if (al && iy) v = cmul(v, cconj(twy[iy]));
-                    if (be && ix) v = cmul(v, cconj(twx[ix]));
-                    acc[i] = cadd(acc[i], v);
-                }
+    for (int be = 0; be < 2; ++be) {
+        if (be) __syncthreads();
+#pragma unroll
+        for (int j = 0; j < IX1; ++j) {
+            const int it = q0 + j * QN, n2 = it % RX2, iy = it / RX2;
+            if (iy < ny) {
+                C v[RX1];
+#pragma unroll
+                for (int n1 = 0; n1 < RX1; ++n1) v[n1] = be ? cmul(xin[j][n1], twx[n1 * RX2 + n2]) : xin[j][n1];
+                dft<C, RX1, false>(v);
+#pragma unroll
+                for (int k1 = 0; k1 < RX1; ++k1)
+                    tile[iy * RS + (k1 * RX2 + n2) * W + w] = (k1 && RX2 > 1) ? cmul(v[k1], twx[2 * n2 * k1]) : v[k1];
             }
         }
         __syncthreads();
-    }
+        if constexpr (RX2 > 1) {
 #pragma unroll
-    for (int i = 0; i < NOWN; ++i) {
-        const int t = threadIdx.x + i * kNT;
-        if (t < NTILE) {
-            const int w = t % W, ix = (t / W) % LX, iy = t / (W * LX);
-            const int64_t c = c0 + w;
-            if (ix < nx && iy < ny && c < B) Y[(int64_t)(iy * nx + ix) * B + c] = acc[i];
+            for (int j = 0; j < 8 / RX2; ++j) {
+                const int it = q0 + j * QN, iy = it % LY, k1 = it / LY;
+                if (iy < ny) {
+                    C* base = tile + iy * RS + k1 * RX2 * W + w;
+                    C v[RX2];
+#pragma unroll
+                    for (int n2 = 0; n2 < RX2; ++n2) v[n2] = base[n2 * W];
+                    dft<C, RX2, false>(v);
+#pragma unroll
+                    for (int k2 = 0; k2 < RX2; ++k2) base[k2 * W] = v[k2];
+                }
+            }
+            __syncthreads();
+        }
+        C yin[IY1][RY1];
+#pragma unroll
+        for (int j = 0; j < IY1; ++j) {
+            const int it = q0 + j * QN, sx = it % LX, n2 = it / LX;
+#pragma unroll
+            for (int n1 = 0; n1 < RY1; ++n1) {
+                const int iy = n1 * RY2 + n2;
+                yin[j][n1] = iy < ny ? tile[iy * RS + sx * W + w] : mk<T>(0, 0);
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int al = 0; al < 2; ++al) {
+            if (al && RY2 > 1) __syncthreads();
+#pragma unroll
+            for (int j = 0; j < IY1; ++j) {
+                const int it = q0 + j * QN, sx = it % LX, n2 = it / LX;
+                C v[RY1];
+#pragma unroll
+                for (int n1 = 0; n1 < RY1; ++n1) v[n1] = al ? cmul(yin[j][n1], twy[n1 * RY2 + n2]) : yin[j][n1];
+                dft<C, RY1, false>(v);
+#pragma unroll
+                for (int k1 = 0; k1 < RY1; ++k1) {
+                    if constexpr (RY2 > 1)
+                        tile[(k1 * RY2 + n2) * RS + sx * W + w] = k1 ? cmul(v[k1], twy[2 * n2 * k1]) : v[k1];
+                    else if (cv)
+                        Xh[((int64_t)(2 * k1 + al) * PX + (2 * F::xel(sx) + be)) * B + c] = v[k1];
+                }
+            }
+            if constexpr (RY2 > 1) {
+                __syncthreads();
+#pragma unroll
+                for (int j = 0; j < 8 / RY2; ++j) {
+                    const int it = q0 + j * QN, sx = it % LX, k1 = it / LX;
+                    C v[RY2];
+#pragma unroll
+                    for (int n2 = 0; n2 < RY2; ++n2) v[n2] = tile[(k1 * RY2 + n2) * RS + sx * W + w];
+                    dft<C, RY2, false>(v);
+                    if (cv) {
+                        C* o = Xh + ((int64_t)(2 * k1 + al) * PX + (2 * F::xel(sx) + be)) * B + c;
+#pragma unroll
+                        for (int k2 = 0; k2 < RY2; ++k2) o[(int64_t)(2 * RY1 * k2) * PX * B] = v[k2];
+                    }
+                }
+            }
+        }
+    }
+}
+
+// Inverse (mirror): the two y-parities of an x-parity are summed after their
+// column transforms, so the rows are transformed once per x-parity.
+template <typename T, int LX, int LY, int W>
+__global__ __launch_bounds__((LdsFft<T, LX, LY, W>::NT)) void fft_inv_lds_kernel(const cplx<T>* __restrict__ Yh,
+                                                                              cplx<T>* __restrict__ Y, int nx, int ny,
+                                                                              int64_t B, const cplx<T>* __restrict__ twx,
+                                                                              const cplx<T>* __restrict__ twy) {
+    using C = cplx<T>;
+    using F = LdsFft<T, LX, LY, W>;
+    constexpr int NT = F::NT, RX1 = F::RX1, RX2 = F::RX2, RY1 = F::RY1, RY2 = F::RY2, RS = F::RS, PX = 2 * LX;
+    constexpr int IX1 = 8 / RX1, IY1 = 8 / RY1;
+    __shared__ C tile[LY * RS];
+    const int64_t c0 = xcd_block(blockIdx.x, gridDim.x) * W;
+    const int w = threadIdx.x % W;
+    const int64_t c = c0 + w;
+    const bool cv = c < B;
+    const int q0 = threadIdx.x / W;
+    constexpr int QN = NT / W;
+    // the last pass over x leaves each thread the same eight elements for both x-parities
+    constexpr int RXL = RX2 > 1 ? RX2 : RX1, RYL = RY2 > 1 ? RY2 : RY1;
+    C out[8 / RXL][RXL];
+#pragma unroll
+    for (int be = 0; be < 2; ++be) {
+        C acc[8 / RYL][RYL];
+#pragma unroll
+        for (int al = 0; al < 2; ++al) {
+            C v[IY1][RY1];
+#pragma unroll
+            for (int j = 0; j < IY1; ++j) {
+                const int it = q0 + j * QN, b = it % LX, n2 = it / LX;
+#pragma unroll
+                for (int n1 = 0; n1 < RY1; ++n1)
+                    v[j][n1] = cv ? Yh[((int64_t)(2 * (n1 * RY2 + n2) + al) * PX + (2 * b + be)) * B + c] : mk<T>(0, 0);
+            }
+#pragma unroll
+            for (int j = 0; j < IY1; ++j) dft<C, RY1, true>(v[j]);
+            if constexpr (RY2 > 1) {
+                if (be || al) __syncthreads();   // the tile's last readers
+#pragma unroll
+                for (int j = 0; j < IY1; ++j) {
+                    const int it = q0 + j * QN, b = it % LX, n2 = it / LX;
+#pragma unroll
+                    for (int k1 = 0; k1 < RY1; ++k1)
+                        tile[(k1 * RY2 + n2) * RS + b * W + w] = k1 ? cmul(v[j][k1], cconj(twy[2 * n2 * k1])) : v[j][k1];
+                }
+                __syncthreads();
+#pragma unroll
+                for (int j = 0; j < 8 / RY2; ++j) {
+                    const int it = q0 + j * QN, b = it % LX, k1 = it / LX;
+                    C u[RY2];
+#pragma unroll
+                    for (int n2 = 0; n2 < RY2; ++n2) u[n2] = tile[(k1 * RY2 + n2) * RS + b * W + w];
+                    dft<C, RY2, true>(u);
+#pragma unroll
+                    for (int k2 = 0; k2 < RY2; ++k2)
+                        acc[j][k2] = al ? cadd(acc[j][k2], cmul(u[k2], cconj(twy[k1 + RY1 * k2]))) : u[k2];
+                }
+            } else {
+#pragma unroll
+                for (int k1 = 0; k1 < RY1; ++k1)
+                    acc[0][k1] = al ? cadd(acc[0][k1], cmul(v[0][k1], cconj(twy[k1]))) : v[0][k1];
+            }
+        }
+        // rows back in place (slot k1 RY2 + k2 holds row k1 + RY1 k2)
+        if constexpr (RY2 > 1) {
+#pragma unroll
+            for (int j = 0; j < 8 / RY2; ++j) {
+                const int it = q0 + j * QN, b = it % LX, k1 = it / LX;
+#pragma unroll
+                for (int k2 = 0; k2 < RY2; ++k2) tile[(k1 * RY2 + k2) * RS + b * W + w] = acc[j][k2];
+            }
+        } else {
+            if (be) __syncthreads();
+#pragma unroll
+            for (int k1 = 0; k1 < RY1; ++k1) tile[k1 * RS + q0 * W + w] = acc[0][k1];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < IX1; ++j) {
+            const int it = q0 + j * QN, n2 = it % RX2, sy = it / RX2;
+            if (F::yel(sy) < ny) {
+                C* base = tile + sy * RS + n2 * W + w;
+                C u[RX1];
+#pragma unroll
+                for (int n1 = 0; n1 < RX1; ++n1) u[n1] = base[n1 * RX2 * W];
+                dft<C, RX1, true>(u);
+                if constexpr (RX2 > 1) {
+#pragma unroll
+                    for (int k1 = 0; k1 < RX1; ++k1)
+                        base[k1 * RX2 * W] = k1 ? cmul(u[k1], cconj(twx[2 * n2 * k1])) : u[k1];
+                } else {
+#pragma unroll
+                    for (int k1 = 0; k1 < RX1; ++k1)
+                        out[j][k1] = be ? cadd(out[j][k1], cmul(u[k1], cconj(twx[k1]))) : u[k1];
+                }
+            }
+        }
+        if constexpr (RX2 > 1) {
+            __syncthreads();
+#pragma unroll
+            for (int j = 0; j < 8 / RX2; ++j) {
+                const int it = q0 + j * QN, sy = it % LY, k1 = it / LY;
+                if (F::yel(sy) < ny) {
+                    C u[RX2];
+#pragma unroll
+                    for (int n2 = 0; n2 < RX2; ++n2) u[n2] = tile[sy * RS + (k1 * RX2 + n2) * W + w];
+                    dft<C, RX2, true>(u);
+#pragma unroll
+                    for (int k2 = 0; k2 < RX2; ++k2)
+                        out[j][k2] = be ? cadd(out[j][k2], cmul(u[k2], cconj(twx[k1 + RX1 * k2]))) : u[k2];
+                }
+            }
+        }
+    }
+    if (!cv) return;
+    if constexpr (RX2 > 1) {
+#pragma unroll
+        for (int j = 0; j < 8 / RX2; ++j) {
+            const int it = q0 + j * QN, iy = F::yel(it % LY), k1 = it / LY;
+#pragma unroll
+            for (int k2 = 0; k2 < RX2; ++k2) {
+                const int ix = k1 + RX1 * k2;
+                if (ix < nx && iy < ny) Y[(int64_t)(iy * nx + ix) * B + c] = out[j][k2];
+            }
+        }
+    } else {
+#pragma unroll
+        for (int j = 0; j < IX1; ++j) {
+            const int iy = F::yel(q0 + j * QN);
+#pragma unroll
+            for (int k1 = 0; k1 < RX1; ++k1)
+                if (k1 < nx && iy < ny) Y[(int64_t)(iy * nx + k1) * B + c] = out[j][k1];
         }
     }
 }
@@ -704,16 +922,18 @@ void launch_embed_axis(int P, const double2* in, double2* out, int n, int64_t nl
     MBT_LAUNCH_CHECK();
 }
 
-// Columns per workgroup: fill a 128 KB LDS tile (one workgroup per CU), at
-// most 16 columns.  At the 64x64 grid this gives 128 contiguous bytes per
-// lattice point in FP64 (8 columns) and in FP32 (16 columns).
 // columns per workgroup of the FP64 register transforms
 constexpr int kRegW64 = 4;
 
+// Columns per workgroup of the FP32 register transforms: 16 (128 contiguous bytes
+// per lattice point)
 template <typename T> constexpr int tile_w(int lx, int ly) {
     int w = (int)(131072 / (lx * ly * (int)sizeof(cplx<T>)));
     return w > 16 ? 16 : (w < 1 ? 1 : w);
 }
+// Columns per workgroup of the LDS-exchanged transforms: four; eight on the
+// smallest grid (a whole wave), two on the largest (the tile has to fit the LDS)
+constexpr int lds_w(int lx, int ly) { return lx * ly <= 64 ? 8 : lx * ly <= 2048 ? 4 : 2; }
 
 template <typename T, bool FWD, int LX, int LY>
 void launch_fft_t(const Geom& g, const cplx<T>* in, cplx<T>* out, int64_t B, const cplx<T>* twx, const cplx<T>* twy,
@@ -722,46 +942,46 @@ void launch_fft_t(const Geom& g, const cplx<T>* in, cplx<T>* out, int64_t B, con
     const int64_t blocks = (B + W - 1) / W;
     MBT_REQUIRE(blocks < (1LL << 31), "fft: batch too large");
     if constexpr (sizeof(T) == 4 && (LX > 32 || LY > 32)) {
-        if (scratch) {
-            launch_two_pass<FWD, LX, LY, kFmtNone>(g, in, out, B, twx, twy, scratch, s);
-            return;
-        }
-    }
-    if constexpr (sizeof(T) == 8 && LX <= 32 && LY <= 32) {
-        // FP64 inverse: the register transform with fewer columns per workgroup
-        // (a row of 32 values fills 128 registers), two workgroups per CU.  The
-        // FP64 forward stays on the LDS kernel, which measured faster.
-        if (!FWD) {
-            constexpr int WD = W > kRegW64 ? kRegW64 : W;
-            constexpr int NT = (LX > LY ? LX : LY) * WD;
-            const int64_t nb = (B + WD - 1) / WD;
-            hipLaunchKernelGGL((fft_inv_reg_kernel<T, LX, LY, WD>), dim3((unsigned)nb), dim3(NT), 0, s, in, out, g.nx,
-                               g.ny, B, twx, twy);
-            MBT_LAUNCH_CHECK();
-            return;
-        }
-    }
-    if constexpr (sizeof(T) == 4 && LX <= 32 && LY <= 32) {
+        MBT_REQUIRE(scratch != nullptr, "fft: FP32 transforms on a 128-point axis need scratch");
+        launch_two_pass<FWD, LX, LY, kFmtNone>(g, in, out, B, twx, twy, scratch, s);
+    } else if constexpr (sizeof(T) == 4) {
         constexpr int NT = (LX > LY ? LX : LY) * W;
         if (FWD)
             hipLaunchKernelGGL((fft_fwd_reg_kernel<T, LX, LY, W, kFmtNone>), dim3((unsigned)blocks), dim3(NT), 0, s, in,
                                (void*)out, g.nx, g.ny, B, twx, twy);
-        else {
+        else
             // the inverse reads four times what it writes and reads each spectrum
             // value once: full-width tiles with non-temporal loads measured ahead of
             // half-width tiles (two workgroups per CU) with either kind of load
-            hipLaunchKernelGGL((fft_inv_reg_kernel<T, LX, LY, W, true>), dim3((unsigned)blocks),
-                               dim3((LX > LY ? LX : LY) * W), 0, s, in, out, g.nx, g.ny, B, twx, twy);
+            hipLaunchKernelGGL((fft_inv_reg_kernel<T, LX, LY, W, true>), dim3((unsigned)blocks), dim3(NT), 0, s, in, out,
+                               g.nx, g.ny, B, twx, twy);
+    } else {
+        constexpr int WL = lds_w(LX, LY);
+        const dim3 lds_blocks((unsigned)((B + WL - 1) / WL)), lds_threads(LdsFft<T, LX, LY, WL>::NT);
+        if constexpr (FWD && LX == 64 && LY == 64) {
+            // two columns per workgroup either way; here the LDS-exchanged form, whose sixteen waves store
+            // 32-byte runs all at once, measured slower (630 against 492 us at 3,072 columns)
+            hipLaunchKernelGGL((fft_fwd_pad_kernel<T, LX, LY, W>), dim3((unsigned)blocks), dim3(kNT), 0, s, in, out, g.nx,
+                               g.ny, B, twx, twy);
+        } else if constexpr (FWD) {
+            hipLaunchKernelGGL((fft_fwd_lds_kernel<T, LX, LY, WL>), lds_blocks, lds_threads, 0, s, in, out, g.nx, g.ny, B,
+                               twx, twy);
+        } else if constexpr (LX > 32 || LY > 32 || LX != LY) {
+            // against transforming each parity grid in place: 545 -> 461 us on the 128x128 grid (3,072
+            // columns), 152 -> 127 on 128x64 (1,984); against the register transform, half of whose threads
+            // have no line in one of the passes where the axes differ: 47 -> 42 us on 64x32 (5,797)
+            hipLaunchKernelGGL((fft_inv_lds_kernel<T, LX, LY, WL>), lds_blocks, lds_threads, 0, s, in, out, g.nx, g.ny, B,
+                               twx, twy);
+        } else {
+            // the register transform with fewer columns per workgroup (a row of 32 values fills 128
+            // registers), two workgroups per CU: it reads most of its bytes and needs no exchange between
+            // them, so it measured ahead of the LDS-exchanged form (636 against 732 us, 64x64 grid, 31,744
+            // columns)
+            constexpr int WD = W > kRegW64 ? kRegW64 : W;
+            hipLaunchKernelGGL((fft_inv_reg_kernel<T, LX, LY, WD>), dim3((unsigned)((B + WD - 1) / WD)),
+                               dim3((LX > LY ? LX : LY) * WD), 0, s, in, out, g.nx, g.ny, B, twx, twy);
         }
-        MBT_LAUNCH_CHECK();
-        return;
     }
-    if (FWD)
-        hipLaunchKernelGGL((fft_fwd_pad_kernel<T, LX, LY, W>), dim3((unsigned)blocks), dim3(kNT), 0, s, in, out,
-                           g.nx, g.ny, B, twx, twy);
-    else
-        hipLaunchKernelGGL((fft_inv_crop_kernel<T, LX, LY, W>), dim3((unsigned)blocks), dim3(kNT), 0, s, in, out,
-                           g.nx, g.ny, B, twx, twy);
     MBT_LAUNCH_CHECK();
 }
 
