@@ -40,6 +40,14 @@ struct GmresState {
     int* iters;      // [R]  Arnoldi steps in total
 };
 
+// Pinned host words that kernels report active counts into, and the generation
+// that tells one cycle's or step's report from another's.
+struct HostReport {
+    unsigned long long* slots = nullptr;
+    unsigned long long* gen = nullptr;
+};
+constexpr int kHostSlots = 66;   // restart <= 63
+
 struct GmresParams {
     int restart = 50;
     double tol = 1e-10;
@@ -48,12 +56,8 @@ struct GmresParams {
     bool dcgs2 = true;           // delayed reorthogonalisation (two sweeps); false: classical CGS2 (three)
     bool packed_basis = false;   // FP32 solves with DCGS2, even R, restart >= 4: basis in the packed 24-bit format
     int* host_count = nullptr;   // pinned host int for the active-count readback
-    // pinned host words that the steps report their active counts into (restart + 2 of
-    // them), and the generation that tells one cycle's reports from another's
-    unsigned long long* host_slots = nullptr;
-    unsigned long long* host_gen = nullptr;
+    HostReport host;             // the steps' active counts (restart + 2 slots)
 };
-constexpr int kHostSlots = 66;   // restart <= 63
 
 struct GmresResult {
     std::vector<int> iters, conv, flag;
@@ -84,13 +88,15 @@ size_t cocg_state_bytes(int64_t N, int R);
 template <typename TB>
 GmresResult cocg_batched(const std::function<void(const TB*, TB*)>& applyZ,
                          const std::function<void(const TB*, TB*)>& applyMinv, const TB* b, double2* x, TB* work,
-                         int64_t N, int R, double tol, int maxit, int* host_count, DevArena& arena, hipStream_t s);
+                         int64_t N, int R, double tol, int maxit, const HostReport& host, DevArena& arena,
+                         hipStream_t s);
 
 size_t pcg_state_bytes(int64_t N, int R);
 template <typename TB>
 GmresResult pcg_batched(const std::function<void(const TB*, TB*)>& applyN,
                         const std::function<void(const TB*, TB*)>& applyPinv, const TB* b, double2* x, TB* work,
-                        int64_t N, int R, double tol, int maxit, int* host_count, DevArena& arena, hipStream_t s);
+                        int64_t N, int R, double tol, int maxit, const HostReport& host, DevArena& arena,
+                         hipStream_t s);
 
 
 }  // namespace mbt

@@ -1485,7 +1485,7 @@ GmresResult gmres_batched(const std::function<void(const TB*, TB*)>& apply, cons
     const int64_t rpcf = gmres_rows_per_chunk(Nf);
     const int nchunkf = gmres_nchunk(Nf);
 
-    unsigned long long* slots = prm.host_slots;
+    unsigned long long* slots = prm.host.slots;
     // x = 0, r0 = b
     hipLaunchKernelGGL(zero_kernel, dim3(ew_grid(vs)), dim3(256), 0, s, x, vs);
     hipLaunchKernelGGL(zero_kernel, dim3(1), dim3(256), 0, s, reinterpret_cast<double2*>(counters), (m + 3) / 2);
@@ -1497,7 +1497,7 @@ GmresResult gmres_batched(const std::function<void(const TB*, TB*)>& apply, cons
         // the convergence verdict of the previous cycle is taken on it
         hipLaunchKernelGGL((colnorm2_kernel<TB>), dim3((R + 63) / 64, nchunk), dim3(64 * kNormWaves), 0, s, r0v, N, R, rpc, partial);
         launch_reduce_partials(partial, nchunk, 1, R, 1, nrm2, s);
-        const uint32_t gen = (uint32_t)++*prm.host_gen;
+        const uint32_t gen = (uint32_t)++*prm.host.gen;
         hipLaunchKernelGGL(cycle_init_kernel, gR, bR, 0, s, st, nrm2, R, first ? 1 : 0, counters + m + 1, slots + m + 1,
                            gen);
         MBT_LAUNCH_CHECK();
@@ -1602,6 +1602,104 @@ GmresResult gmres_batched(const std::function<void(const TB*, TB*)>& apply, cons
     return res;
 }
 
+// ------------------------------------------------------------------ short recurrences (PCG, COCG)
+// Both need two per-RHS dot products per step, each followed by a per-RHS scalar
+// update.  A dot sweep writes chunk partials; the kernel that adds them also runs
+// the scalar update and, where the step's verdict falls, reports how many RHS go
+// on.
+namespace {
+
+constexpr int kDotWaves = 8;
+// MODE 0: sum conj(a) b; 1: sum a b; 2: sum a b and sum |a|^2.  Partials
+// [chunk][v][r]; a chunk's rows are dealt to the workgroup's waves (row n0 + j to
+// wave j mod kDotWaves) and the waves' sums added in order.  One wave per chunk
+// walking its rows one by one takes 61 us for 29,760 rows of 64 RHS in FP64 (31 MB
+// per vector).
+template <typename TB, int MODE>
+__global__ __launch_bounds__(64 * kDotWaves) void krylov_dot_kernel(const TB* __restrict__ a, const TB* __restrict__ b,
+                                                                    int64_t N, int R, int64_t rows_per_chunk,
+                                                                    double2* __restrict__ partial) {
+    __shared__ double2 gs[kDotWaves][64];
+    __shared__ double gn[MODE == 2 ? kDotWaves : 1][64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int r = blockIdx.x * 64 + lane;
+    const int64_t chunk = blockIdx.y;
+    const int64_t n0 = chunk * rows_per_chunk, n1 = min(N, n0 + rows_per_chunk);
+    double2 ab = make_double2(0, 0);
+    double aa = 0.0;
+    if (r < R) {
+#pragma unroll 4
+        for (int64_t n = n0 + wave; n < n1; n += kDotWaves) {
+            const double2 av = ld2(a + n * R + r), bv = ld2(b + n * R + r);
+            ab = MODE == 0 ? cfmac(ab, av, bv) : cfma(ab, av, bv);
+            if (MODE == 2) aa = nfma(aa, av);
+        }
+    }
+    gs[wave][lane] = ab;
+    if (MODE == 2) gn[wave][lane] = aa;
+    __syncthreads();
+    if (wave != 0 || r >= R) return;
+    for (int q = 1; q < kDotWaves; ++q) {
+        ab = cadd(ab, gs[q][lane]);
+        if (MODE == 2) aa += gn[q][lane];
+    }
+    constexpr int nv = MODE == 2 ? 2 : 1;
+    partial[chunk * nv * R + r] = ab;
+    if (MODE == 2) partial[(chunk * nv + 1) * R + r] = make_double2(aa, 0.0);
+}
+
+// The chunk partials of NV dots added per RHS (in the order of
+// reduce_partials_kernel) and handed to op(r, sums), which updates the RHS's
+// scalars and says whether it goes on.  COUNT: reports the number that do; else
+// the counter is cleared for the step's report.
+template <int NV, bool COUNT, typename Op>
+__global__ __launch_bounds__(64 * kRedWaves) void krylov_scalar_kernel(const double2* __restrict__ partial, int nchunk,
+                                                                       int R, Op op, unsigned long long* counter,
+                                                                       unsigned long long* host_slot, uint32_t gen) {
+    __shared__ double2 gs[NV][kRedSub][kRedOut];
+    const int o = threadIdx.x % kRedOut, q = threadIdx.x / kRedOut;
+    const int r = blockIdx.x * kRedOut + o;
+    double2 sum[NV];
+#pragma unroll
+    for (int v = 0; v < NV; ++v) {
+        sum[v] = make_double2(0, 0);
+        if (r < R) {
+#pragma unroll 4
+            for (int c = q; c < nchunk; c += kRedSub) sum[v] = cadd(sum[v], partial[((int64_t)c * NV + v) * R + r]);
+        }
+        gs[v][q][o] = sum[v];
+    }
+    __syncthreads();
+    int act = 0;
+    if (q == 0 && r < R) {
+#pragma unroll
+        for (int v = 0; v < NV; ++v)
+#pragma unroll 8
+            for (int g = 1; g < kRedSub; ++g) sum[v] = cadd(sum[v], gs[v][g][o]);
+        act = op(r, sum);
+    }
+    if (COUNT) {
+        const int n = __syncthreads_count(act);
+        if (threadIdx.x == 0) report_count(counter, (unsigned)n, gridDim.x, host_slot, gen);
+    } else if (blockIdx.x == 0 && threadIdx.x == 0) {
+        *counter = 0;
+    }
+}
+
+template <typename TB, int MODE, bool COUNT, typename Op>
+void krylov_dot(const TB* a, const TB* b, int64_t N, int R, double2* partial, const Op& op, unsigned long long* counter,
+                unsigned long long* host_slot, uint32_t gen, hipStream_t s) {
+    const int64_t rpc = gmres_rows_per_chunk(N);
+    const int nchunk = gmres_nchunk(N);
+    hipLaunchKernelGGL((krylov_dot_kernel<TB, MODE>), dim3((R + 63) / 64, nchunk), dim3(64 * kDotWaves), 0, s, a, b, N, R,
+                       rpc, partial);
+    hipLaunchKernelGGL((krylov_scalar_kernel<MODE == 2 ? 2 : 1, COUNT, Op>), dim3((R + kRedOut - 1) / kRedOut),
+                       dim3(64 * kRedWaves), 0, s, partial, nchunk, R, op, counter, host_slot, gen);
+    MBT_LAUNCH_CHECK();
+}
+
+}  // namespace
+
 // ------------------------------------------------------------------ batched PCG (Sec. II-C)
 // Conjugate gradients on N x = b (N = Z^H Z, Hermitian positive definite) with
 // the preconditioner P applied as P^{-1}; one independent recurrence per RHS
@@ -1610,54 +1708,46 @@ GmresResult gmres_batched(const std::function<void(const TB*, TB*)>& apply, cons
 // stop test is that system's relative residual sqrt(r^H P^{-1} r / b^H P^{-1} b).
 namespace {
 
-// partial[chunk][r] = sum over the chunk's rows of conj(a) b
-template <typename TB>
-__global__ void pcg_dot_kernel(const TB* __restrict__ a, const TB* __restrict__ b, int64_t N, int R,
-                               int64_t rows_per_chunk, double2* __restrict__ partial) {
-    const int r = blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t chunk = blockIdx.y;
-    if (r >= R) return;
-    const int64_t n0 = chunk * rows_per_chunk, n1 = min(N, n0 + rows_per_chunk);
-    double2 acc = make_double2(0, 0);
-    for (int64_t n = n0; n < n1; ++n) acc = cfmac(acc, ld2(a + n * R + r), ld2(b + n * R + r));
-    partial[chunk * R + r] = acc;
-}
-
 struct PcgState {
     double tol;
     double *rho, *rho0, *alpha, *beta;
     int *active, *conv, *flag, *iters;
 };
 
-__global__ void pcg_init_kernel(PcgState st, const double2* __restrict__ rz, int R) {
-    const int r = blockIdx.x * blockDim.x + threadIdx.x;
-    if (r >= R) return;
-    const double rho = rz[r].x;
-    st.rho[r] = rho;
-    st.rho0[r] = rho;
-    st.iters[r] = 0;
-    st.flag[r] = !(rho == rho) || isinf(rho) || rho < 0.0;
-    st.conv[r] = !st.flag[r] && rho == 0.0;
-    st.active[r] = !st.flag[r] && !st.conv[r];
-    st.alpha[r] = 0.0;
-    st.beta[r] = 0.0;
-}
+// rho of the initial residual
+struct PcgInit {
+    PcgState st;
+    __device__ int operator()(int r, const double2* rz) const {
+        const double rho = rz[0].x;
+        st.rho[r] = rho;
+        st.rho0[r] = rho;
+        st.iters[r] = 0;
+        st.flag[r] = !(rho == rho) || isinf(rho) || rho < 0.0;
+        st.conv[r] = !st.flag[r] && rho == 0.0;
+        st.active[r] = !st.flag[r] && !st.conv[r];
+        st.alpha[r] = 0.0;
+        st.beta[r] = 0.0;
+        return st.active[r];
+    }
+};
 
 // alpha = rho / p^H q for the RHS still iterating
-__global__ void pcg_alpha_kernel(PcgState st, const double2* __restrict__ pq, int R) {
-    const int r = blockIdx.x * blockDim.x + threadIdx.x;
-    if (r >= R) return;
-    double a = 0.0;
-    if (st.active[r]) {
-        a = st.rho[r] / pq[r].x;
-        if (!(a == a) || isinf(a)) {
-            st.flag[r] = 1;
-            st.active[r] = 0;
-            a = 0.0;
+struct PcgAlpha {
+    PcgState st;
+    __device__ int operator()(int r, const double2* pq) const {
+        double a = 0.0;
+        if (st.active[r]) {
+            a = st.rho[r] / pq[0].x;
+            if (!(a == a) || isinf(a)) {
+                st.flag[r] = 1;
+                st.active[r] = 0;
+                a = 0.0;
+            }
         }
+        st.alpha[r] = a;
+        return st.active[r];
     }
-    st.alpha[r] = a;
-}
+};
 
 // x += alpha p (x in FP64), r -= alpha q
 template <typename TB>
@@ -1672,26 +1762,28 @@ __global__ void pcg_xr_kernel(double2* __restrict__ x, TB* __restrict__ rv, cons
 }
 
 // rho_new = r^H z: stop test on the split-system residual, then beta
-__global__ void pcg_beta_kernel(PcgState st, const double2* __restrict__ rz, int R) {
-    const int r = blockIdx.x * blockDim.x + threadIdx.x;
-    if (r >= R) return;
-    double b = 0.0;
-    if (st.active[r]) {
-        const double rn = rz[r].x;
-        st.iters[r] += 1;
-        if (!(rn == rn) || isinf(rn)) {
-            st.flag[r] = 1;
-            st.active[r] = 0;
-        } else if (sqrt(fmax(rn, 0.0) / st.rho0[r]) <= st.tol) {
-            st.conv[r] = 1;
-            st.active[r] = 0;
-        } else {
-            b = rn / st.rho[r];
-            st.rho[r] = rn;
+struct PcgBeta {
+    PcgState st;
+    __device__ int operator()(int r, const double2* rz) const {
+        double b = 0.0;
+        if (st.active[r]) {
+            const double rn = rz[0].x;
+            st.iters[r] += 1;
+            if (!(rn == rn) || isinf(rn)) {
+                st.flag[r] = 1;
+                st.active[r] = 0;
+            } else if (sqrt(fmax(rn, 0.0) / st.rho0[r]) <= st.tol) {
+                st.conv[r] = 1;
+                st.active[r] = 0;
+            } else {
+                b = rn / st.rho[r];
+                st.rho[r] = rn;
+            }
         }
+        st.beta[r] = b;
+        return st.active[r];
     }
-    st.beta[r] = b;
-}
+};
 
 // p = z + beta p
 template <typename TB>
@@ -1704,15 +1796,6 @@ __global__ void pcg_p_kernel(TB* __restrict__ p, const TB* __restrict__ z, const
     }
 }
 
-template <typename TB>
-void pcg_dot(const TB* a, const TB* b, int64_t N, int R, double2* partial, double2* out, hipStream_t s) {
-    const int64_t rpc = gmres_rows_per_chunk(N);
-    const int nchunk = gmres_nchunk(N);
-    hipLaunchKernelGGL((pcg_dot_kernel<TB>), dim3((R + 63) / 64, nchunk), dim3(64), 0, s, a, b, N, R, rpc, partial);
-    MBT_LAUNCH_CHECK();
-    launch_reduce_partials(partial, nchunk, 1, R, 1, out, s);
-}
-
 }  // namespace
 
 size_t pcg_state_bytes(int64_t N, int R) {
@@ -1723,7 +1806,8 @@ size_t pcg_state_bytes(int64_t N, int R) {
 template <typename TB>
 GmresResult pcg_batched(const std::function<void(const TB*, TB*)>& applyN,
                         const std::function<void(const TB*, TB*)>& applyPinv, const TB* b, double2* x, TB* work,
-                        int64_t N, int R, double tol, int maxit, int* host_count, DevArena& arena, hipStream_t s) {
+                        int64_t N, int R, double tol, int maxit, const HostReport& host, DevArena& arena,
+                         hipStream_t s) {
     const size_t mark = arena.off;
     const int64_t NR = N * R;
     TB* rv = work;
@@ -1741,37 +1825,28 @@ GmresResult pcg_batched(const std::function<void(const TB*, TB*)>& applyN,
     st.flag = arena.get<int>(R);
     st.iters = arena.get<int>(R);
     double2* partial = arena.get<double2>((size_t)gmres_nchunk(N) * R);
-    double2* dot = arena.get<double2>(R);
-    int* d_count = arena.get<int>(16);
-    const dim3 gR((R + 255) / 256), bR(256);
-    auto count_active = [&]() -> int {
-        hipLaunchKernelGGL(count_kernel, dim3(1), dim3(256), 0, s, st.active, R, d_count);
-        MBT_LAUNCH_CHECK();
-        MBT_HIP(hipMemcpyAsync(host_count, d_count, sizeof(int), hipMemcpyDeviceToHost, s));
-        MBT_HIP(hipStreamSynchronize(s));
-        return *host_count;
-    };
+    unsigned long long* counter = arena.get<unsigned long long>(2);
     GmresResult res;
     // x = 0, r = b, z = P^{-1} r, p = z, rho = r^H z
     hipLaunchKernelGGL(zero_kernel, dim3(ew_grid(NR)), dim3(256), 0, s, x, NR);
+    hipLaunchKernelGGL(zero_kernel, dim3(1), dim3(256), 0, s, reinterpret_cast<double2*>(counter), 1);
     hipLaunchKernelGGL((copy_kernel<TB>), dim3(ew_grid(NR)), dim3(256), 0, s, b, rv, NR);
     MBT_LAUNCH_CHECK();
     applyPinv(rv, z);
     hipLaunchKernelGGL((copy_kernel<TB>), dim3(ew_grid(NR)), dim3(256), 0, s, z, p, NR);
     MBT_LAUNCH_CHECK();
-    pcg_dot<TB>(rv, z, N, R, partial, dot, s);
-    hipLaunchKernelGGL(pcg_init_kernel, gR, bR, 0, s, st, dot, R);
-    MBT_LAUNCH_CHECK();
+    uint32_t gen = (uint32_t)++*host.gen;
+    krylov_dot<TB, 0, true>(rv, z, N, R, partial, PcgInit{st}, counter, host.slots, gen, s);
     res.cycles = 1;
-    for (int it = 0; it < maxit && count_active() > 0; ++it) {
+    for (int it = 0; it < maxit && wait_count(host.slots, gen, s) > 0; ++it) {
         applyN(p, q);
-        pcg_dot<TB>(p, q, N, R, partial, dot, s);
-        hipLaunchKernelGGL(pcg_alpha_kernel, gR, bR, 0, s, st, dot, R);
+        krylov_dot<TB, 0, false>(p, q, N, R, partial, PcgAlpha{st}, counter, host.slots, 0, s);
         hipLaunchKernelGGL((pcg_xr_kernel<TB>), dim3(ew_grid(NR)), dim3(256), 0, s, x, rv, p, q, st.alpha, NR, R);
         MBT_LAUNCH_CHECK();
         applyPinv(rv, z);
-        pcg_dot<TB>(rv, z, N, R, partial, dot, s);
-        hipLaunchKernelGGL(pcg_beta_kernel, gR, bR, 0, s, st, dot, R);
+        gen = (uint32_t)++*host.gen;
+        krylov_dot<TB, 0, true>(rv, z, N, R, partial, PcgBeta{st}, counter, host.slots, gen, s);
+        // the new direction is formed while the host learns whether any RHS goes on
         hipLaunchKernelGGL((pcg_p_kernel<TB>), dim3(ew_grid(NR)), dim3(256), 0, s, p, z, st.beta, NR, R);
         MBT_LAUNCH_CHECK();
         res.matvecs += 2;
@@ -1797,26 +1872,6 @@ GmresResult pcg_batched(const std::function<void(const TB*, TB*)>& applyN,
 // valid.  One independent recurrence per RHS column, FP64 coefficients.
 namespace {
 
-// partial[chunk][v][r]: v = 0: sum a b (bilinear); NORM: v = 1: sum |a|^2
-template <typename TB, bool NORM>
-__global__ void cocg_dot_kernel(const TB* __restrict__ a, const TB* __restrict__ b, int64_t N, int R,
-                                int64_t rows_per_chunk, double2* __restrict__ partial) {
-    const int r = blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t chunk = blockIdx.y;
-    if (r >= R) return;
-    const int64_t n0 = chunk * rows_per_chunk, n1 = min(N, n0 + rows_per_chunk);
-    double2 ab = make_double2(0, 0);
-    double aa = 0.0;
-    for (int64_t n = n0; n < n1; ++n) {
-        const double2 av = ld2(a + n * R + r);
-        ab = cfma(ab, av, ld2(b + n * R + r));
-        if (NORM) aa = fma(av.y, av.y, fma(av.x, av.x, aa));
-    }
-    constexpr int nv = NORM ? 2 : 1;
-    partial[(chunk * nv) * R + r] = ab;
-    if (NORM) partial[(chunk * nv + 1) * R + r] = make_double2(aa, 0.0);
-}
-
 struct CocgState {
     double tol;
     double2 *rho, *alpha, *beta;
@@ -1830,36 +1885,40 @@ __device__ __forceinline__ double2 cdiv(double2 a, double2 b) {
 }
 
 // red = [r^T z, |r|^2] of the initial residual r = b
-__global__ void cocg_init_kernel(CocgState st, const double2* __restrict__ red, int R) {
-    const int r = blockIdx.x * blockDim.x + threadIdx.x;
-    if (r >= R) return;
-    const double2 rho = red[r];
-    const double bb = red[R + r].x;
-    st.rho[r] = rho;
-    st.bnorm2[r] = bb;
-    st.iters[r] = 0;
-    st.flag[r] = !(bb == bb) || isinf(bb) || !(rho.x == rho.x) || !(rho.y == rho.y);
-    st.conv[r] = !st.flag[r] && bb == 0.0;
-    st.active[r] = !st.flag[r] && !st.conv[r];
-    st.alpha[r] = make_double2(0, 0);
-    st.beta[r] = make_double2(0, 0);
-}
+struct CocgInit {
+    CocgState st;
+    __device__ int operator()(int r, const double2* red) const {
+        const double2 rho = red[0];
+        const double bb = red[1].x;
+        st.rho[r] = rho;
+        st.bnorm2[r] = bb;
+        st.iters[r] = 0;
+        st.flag[r] = !(bb == bb) || isinf(bb) || !(rho.x == rho.x) || !(rho.y == rho.y);
+        st.conv[r] = !st.flag[r] && bb == 0.0;
+        st.active[r] = !st.flag[r] && !st.conv[r];
+        st.alpha[r] = make_double2(0, 0);
+        st.beta[r] = make_double2(0, 0);
+        return st.active[r];
+    }
+};
 
 // alpha = rho / p^T q for the RHS still iterating (a vanishing p^T q is a breakdown)
-__global__ void cocg_alpha_kernel(CocgState st, const double2* __restrict__ pq, int R) {
-    const int r = blockIdx.x * blockDim.x + threadIdx.x;
-    if (r >= R) return;
-    double2 a = make_double2(0, 0);
-    if (st.active[r]) {
-        a = cdiv(st.rho[r], pq[r]);
-        if (!(a.x == a.x) || !(a.y == a.y) || isinf(a.x) || isinf(a.y)) {
-            st.flag[r] = 1;
-            st.active[r] = 0;
-            a = make_double2(0, 0);
+struct CocgAlpha {
+    CocgState st;
+    __device__ int operator()(int r, const double2* pq) const {
+        double2 a = make_double2(0, 0);
+        if (st.active[r]) {
+            a = cdiv(st.rho[r], pq[0]);
+            if (!(a.x == a.x) || !(a.y == a.y) || isinf(a.x) || isinf(a.y)) {
+                st.flag[r] = 1;
+                st.active[r] = 0;
+                a = make_double2(0, 0);
+            }
         }
+        st.alpha[r] = a;
+        return st.active[r];
     }
-    st.alpha[r] = a;
-}
+};
 
 // x += alpha p (x in FP64), r -= alpha q
 template <typename TB>
@@ -1874,31 +1933,33 @@ __global__ void cocg_xr_kernel(double2* __restrict__ x, TB* __restrict__ rv, con
 }
 
 // red = [r^T z, |r|^2]: stop test on ||r|| / ||b||, then beta = rho_new / rho
-__global__ void cocg_beta_kernel(CocgState st, const double2* __restrict__ red, int R) {
-    const int r = blockIdx.x * blockDim.x + threadIdx.x;
-    if (r >= R) return;
-    double2 b = make_double2(0, 0);
-    if (st.active[r]) {
-        const double2 rz = red[r];
-        const double rr = red[R + r].x;
-        st.iters[r] += 1;
-        if (!(rr == rr) || isinf(rr) || !(rz.x == rz.x) || !(rz.y == rz.y)) {
-            st.flag[r] = 1;
-            st.active[r] = 0;
-        } else if (sqrt(rr / st.bnorm2[r]) <= st.tol) {
-            st.conv[r] = 1;
-            st.active[r] = 0;
-        } else if (rr > 1e12 * st.bnorm2[r]) {
-            // a residual a million times the right-hand side: the recurrence has run away
-            // (the FP32 short recurrence does so on a few RHS); stop it unconverged
-            st.active[r] = 0;
-        } else {
-            b = cdiv(rz, st.rho[r]);
-            st.rho[r] = rz;
+struct CocgBeta {
+    CocgState st;
+    __device__ int operator()(int r, const double2* red) const {
+        double2 b = make_double2(0, 0);
+        if (st.active[r]) {
+            const double2 rz = red[0];
+            const double rr = red[1].x;
+            st.iters[r] += 1;
+            if (!(rr == rr) || isinf(rr) || !(rz.x == rz.x) || !(rz.y == rz.y)) {
+                st.flag[r] = 1;
+                st.active[r] = 0;
+            } else if (sqrt(rr / st.bnorm2[r]) <= st.tol) {
+                st.conv[r] = 1;
+                st.active[r] = 0;
+            } else if (rr > 1e12 * st.bnorm2[r]) {
+                // a residual a million times the right-hand side: the recurrence has run away
+                // (the FP32 short recurrence does so on a few RHS); stop it unconverged
+                st.active[r] = 0;
+            } else {
+                b = cdiv(rz, st.rho[r]);
+                st.rho[r] = rz;
+            }
         }
+        st.beta[r] = b;
+        return st.active[r];
     }
-    st.beta[r] = b;
-}
+};
 
 // p = z + beta p
 template <typename TB>
@@ -1906,16 +1967,6 @@ __global__ void cocg_p_kernel(TB* __restrict__ p, const TB* __restrict__ z, cons
                               int64_t NR, int R) {
     for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < NR; t += (int64_t)gridDim.x * blockDim.x)
         st2(p + t, cfma(ld2(z + t), beta[t % R], ld2(p + t)));
-}
-
-template <typename TB, bool NORM>
-void cocg_dot(const TB* a, const TB* b, int64_t N, int R, double2* partial, double2* out, hipStream_t s) {
-    const int64_t rpc = gmres_rows_per_chunk(N);
-    const int nchunk = gmres_nchunk(N);
-    hipLaunchKernelGGL((cocg_dot_kernel<TB, NORM>), dim3((R + 63) / 64, nchunk), dim3(64), 0, s, a, b, N, R, rpc,
-                       partial);
-    MBT_LAUNCH_CHECK();
-    launch_reduce_partials(partial, nchunk, NORM ? 2 : 1, R, 1, out, s);
 }
 
 }  // namespace
@@ -1928,7 +1979,8 @@ size_t cocg_state_bytes(int64_t N, int R) {
 template <typename TB>
 GmresResult cocg_batched(const std::function<void(const TB*, TB*)>& applyZ,
                          const std::function<void(const TB*, TB*)>& applyMinv, const TB* b, double2* x, TB* work,
-                         int64_t N, int R, double tol, int maxit, int* host_count, DevArena& arena, hipStream_t s) {
+                         int64_t N, int R, double tol, int maxit, const HostReport& host, DevArena& arena,
+                         hipStream_t s) {
     const size_t mark = arena.off;
     const int64_t NR = N * R;
     TB* rv = work;
@@ -1946,37 +1998,28 @@ GmresResult cocg_batched(const std::function<void(const TB*, TB*)>& applyZ,
     st.flag = arena.get<int>(R);
     st.iters = arena.get<int>(R);
     double2* partial = arena.get<double2>(2 * (size_t)gmres_nchunk(N) * R);
-    double2* red = arena.get<double2>(2 * (size_t)R);
-    int* d_count = arena.get<int>(16);
-    const dim3 gR((R + 255) / 256), bR(256);
-    auto count_active = [&]() -> int {
-        hipLaunchKernelGGL(count_kernel, dim3(1), dim3(256), 0, s, st.active, R, d_count);
-        MBT_LAUNCH_CHECK();
-        MBT_HIP(hipMemcpyAsync(host_count, d_count, sizeof(int), hipMemcpyDeviceToHost, s));
-        MBT_HIP(hipStreamSynchronize(s));
-        return *host_count;
-    };
+    unsigned long long* counter = arena.get<unsigned long long>(2);
     GmresResult res;
     // x = 0, r = b, z = M^{-1} r, p = z, rho = r^T z
     hipLaunchKernelGGL(zero_kernel, dim3(ew_grid(NR)), dim3(256), 0, s, x, NR);
+    hipLaunchKernelGGL(zero_kernel, dim3(1), dim3(256), 0, s, reinterpret_cast<double2*>(counter), 1);
     hipLaunchKernelGGL((copy_kernel<TB>), dim3(ew_grid(NR)), dim3(256), 0, s, b, rv, NR);
     MBT_LAUNCH_CHECK();
     applyMinv(rv, z);
     hipLaunchKernelGGL((copy_kernel<TB>), dim3(ew_grid(NR)), dim3(256), 0, s, z, p, NR);
     MBT_LAUNCH_CHECK();
-    cocg_dot<TB, true>(rv, z, N, R, partial, red, s);
-    hipLaunchKernelGGL(cocg_init_kernel, gR, bR, 0, s, st, red, R);
-    MBT_LAUNCH_CHECK();
+    uint32_t gen = (uint32_t)++*host.gen;
+    krylov_dot<TB, 2, true>(rv, z, N, R, partial, CocgInit{st}, counter, host.slots, gen, s);
     res.cycles = 1;
-    for (int it = 0; it < maxit && count_active() > 0; ++it) {
+    for (int it = 0; it < maxit && wait_count(host.slots, gen, s) > 0; ++it) {
         applyZ(p, q);
-        cocg_dot<TB, false>(p, q, N, R, partial, red, s);
-        hipLaunchKernelGGL(cocg_alpha_kernel, gR, bR, 0, s, st, red, R);
+        krylov_dot<TB, 1, false>(p, q, N, R, partial, CocgAlpha{st}, counter, host.slots, 0, s);
         hipLaunchKernelGGL((cocg_xr_kernel<TB>), dim3(ew_grid(NR)), dim3(256), 0, s, x, rv, p, q, st.alpha, NR, R);
         MBT_LAUNCH_CHECK();
         applyMinv(rv, z);
-        cocg_dot<TB, true>(rv, z, N, R, partial, red, s);
-        hipLaunchKernelGGL(cocg_beta_kernel, gR, bR, 0, s, st, red, R);
+        gen = (uint32_t)++*host.gen;
+        krylov_dot<TB, 2, true>(rv, z, N, R, partial, CocgBeta{st}, counter, host.slots, gen, s);
+        // the new direction is formed while the host learns whether any RHS goes on
         hipLaunchKernelGGL((cocg_p_kernel<TB>), dim3(ew_grid(NR)), dim3(256), 0, s, p, z, st.beta, NR, R);
         MBT_LAUNCH_CHECK();
         res.matvecs += 1;
@@ -1994,17 +2037,21 @@ GmresResult cocg_batched(const std::function<void(const TB*, TB*)>& applyZ,
 
 template GmresResult cocg_batched<double2>(const std::function<void(const double2*, double2*)>&,
                                            const std::function<void(const double2*, double2*)>&, const double2*,
-                                           double2*, double2*, int64_t, int, double, int, int*, DevArena&, hipStream_t);
+                                           double2*, double2*, int64_t, int, double, int, const HostReport&, DevArena&,
+                                           hipStream_t);
 template GmresResult cocg_batched<float2>(const std::function<void(const float2*, float2*)>&,
                                           const std::function<void(const float2*, float2*)>&, const float2*, double2*,
-                                          float2*, int64_t, int, double, int, int*, DevArena&, hipStream_t);
+                                          float2*, int64_t, int, double, int, const HostReport&, DevArena&,
+                                           hipStream_t);
 
 template GmresResult pcg_batched<double2>(const std::function<void(const double2*, double2*)>&,
                                           const std::function<void(const double2*, double2*)>&, const double2*,
-                                          double2*, double2*, int64_t, int, double, int, int*, DevArena&, hipStream_t);
+                                          double2*, double2*, int64_t, int, double, int, const HostReport&, DevArena&,
+                                           hipStream_t);
 template GmresResult pcg_batched<float2>(const std::function<void(const float2*, float2*)>&,
                                          const std::function<void(const float2*, float2*)>&, const float2*, double2*,
-                                         float2*, int64_t, int, double, int, int*, DevArena&, hipStream_t);
+                                         float2*, int64_t, int, double, int, const HostReport&, DevArena&,
+                                           hipStream_t);
 
 template GmresResult gmres_batched<double2>(const std::function<void(const double2*, double2*)>&, const double2*,
                                             double2*, double2*, int64_t, int, const GmresParams&, DevArena&, hipStream_t);

@@ -761,8 +761,7 @@ SolveOut solve_rhs(const OpData& op, const mbt_solve_opts& o, const double2* V, 
     prm.max_cycles = o.max_cycles;
     prm.matvecs_per_apply = o.pc == MBT_PC_NORMAL_EQ ? 2 : 1;
     prm.host_count = wk.host_count;
-    prm.host_slots = wk.host_slots;
-    prm.host_gen = &wk.host_gen;
+    prm.host = HostReport{wk.host_slots, &wk.host_gen};
     prm.dcgs2 = !(o.flags & MBT_FLAG_CGS2);
     prm.packed_basis = o.prec != MBT_FP64 && !(o.flags & MBT_FLAG_FP32_BASIS);
     std::vector<double> vn;
@@ -788,7 +787,7 @@ SolveOut solve_rhs(const OpData& op, const mbt_solve_opts& o, const double2* V, 
             std::function<void(const double2*, double2*)> fp = [&](const double2* x, double2* y) {
                 pinv<double>(ov, x, y);
             };
-            gr = pcg_batched<double2>(fn, fp, b, X, basis, g.N, R, o.tol, pcg_maxit, wk.host_count, arena, s);
+            gr = pcg_batched<double2>(fn, fp, b, X, basis, g.N, R, o.tol, pcg_maxit, prm.host, arena, s);
         } else if (use_cocg) {
             // Z I = V with M = P_K, both complex symmetric
             std::function<void(const double2*, double2*)> fz = [&](const double2* x, double2* y) {
@@ -797,7 +796,7 @@ SolveOut solve_rhs(const OpData& op, const mbt_solve_opts& o, const double2* V, 
             std::function<void(const double2*, double2*)> fm = [&](const double2* x, double2* y) {
                 pinv<double>(ov, x, y);
             };
-            gr = cocg_batched<double2>(fz, fm, V, X, basis, g.N, R, o.tol, pcg_maxit, wk.host_count, arena, s);
+            gr = cocg_batched<double2>(fz, fm, V, X, basis, g.N, R, o.tol, pcg_maxit, prm.host, arena, s);
         } else {
             apply_rhs<double>(ov, V, b);
             out.matvecs += o.pc == MBT_PC_NORMAL_EQ ? 1 : 0;
@@ -896,7 +895,7 @@ SolveOut solve_rhs(const OpData& op, const mbt_solve_opts& o, const double2* V, 
                 std::function<void(const float2*, float2*)> fp = [&](const float2* x, float2* y) {
                     pinv<float>(ov32, x, y);
                 };
-                gr = pcg_batched<float2>(fn, fp, b32, d, basis, g.N, R, prm.tol, pcg_maxit, wk.host_count, arena, s);
+                gr = pcg_batched<float2>(fn, fp, b32, d, basis, g.N, R, prm.tol, pcg_maxit, prm.host, arena, s);
             } else if (use_cocg) {
                 std::function<void(const float2*, float2*)> fz = [&](const float2* x, float2* y) {
                     zmul<float>(ov32, 0, x, y);
@@ -904,7 +903,7 @@ SolveOut solve_rhs(const OpData& op, const mbt_solve_opts& o, const double2* V, 
                 std::function<void(const float2*, float2*)> fm = [&](const float2* x, float2* y) {
                     pinv<float>(ov32, x, y);
                 };
-                gr = cocg_batched<float2>(fz, fm, r32, d, basis, g.N, R, prm.tol, pcg_maxit, wk.host_count, arena, s);
+                gr = cocg_batched<float2>(fz, fm, r32, d, basis, g.N, R, prm.tol, pcg_maxit, prm.host, arena, s);
             } else {
                 apply_rhs<float>(ov32, r32, b32);
                 out.matvecs += o.pc == MBT_PC_NORMAL_EQ ? 1 : 0;
