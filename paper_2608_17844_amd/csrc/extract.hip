@@ -14,14 +14,11 @@
 //   gap currents the solve returns, the center element's active impedance
 //   Z_a,c = V_c / I_p,c (eq. (actZ) with those port currents) and its ARC.
 //
-// The dense inverses use Gauss-Jordan elimination with partial pivoting.  For
-// 64 <= n <= 1024 it is blocked: one workgroup factors a panel of eight
-// columns with each row in its owner thread's registers, then applies the
-// panel's row interchanges and pivot rows to the other columns; a rank-8
-// update of the remaining rows follows, so the matrix is streamed once per
-// panel instead of once per column.  Other sizes use one pivot kernel and one
-// rank-1 elimination kernel per column.  The blocked pivot search compares
-// magnitudes rounded to FP32 (ties: smallest row), the unblocked one in FP64.
+// The dense inverses use Gauss-Jordan elimination with partial pivoting: up to 64
+// rows in one workgroup's registers, up to 4,096 in panels of eight (four) columns,
+// each launch factoring the next panel while it applies the current one, so the
+// matrix is streamed once per panel.  Larger sizes use one pivot kernel and one
+// rank-1 elimination kernel per column.
 #include "common.h"
 #include "extract.h"
 
@@ -91,244 +88,339 @@ __global__ void gj_elim_kernel(double2* __restrict__ A, int n, int k, const doub
     A[t] = csub(base, cmul(colbuf[i], A[(int64_t)k * n + j]));
 }
 
-// ---- blocked form (n <= kPanT: one row per thread of the panel workgroup)
-constexpr int kPanT = 1024;       // threads of the panel workgroup
-constexpr int kMaxPan = 8;        // columns per panel
-constexpr int kBlockedMinN = 64;
-constexpr int kUpdRows = 4;       // rows per thread of the rank-nb update
+// ---- one-launch and panelled forms
+// Both keep the rows where they are: a step's pivot is the unused row of largest
+// magnitude in its column, and the elimination ends with the row of step k at row
+// p_k.  With B the in-place result, A^{-1}[k][p_j] = B[p_k][j].
 
-// Wave-wide maximum of a 64-bit key through DPP lane permutations (pairs,
-// quads, eight, sixteen lanes) and the four row results read out of lanes 0,
-// 16, 32 and 48.  Called by all 64 lanes.
-template <int CTRL>
-__device__ __forceinline__ uint64_t dpp_max_step(uint64_t key) {
-    const int lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)key, CTRL, 0xF, 0xF, false);
-    const int hi = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)(key >> 32), CTRL, 0xF, 0xF, false);
-    const uint64_t o = ((uint64_t)(uint32_t)hi << 32) | (uint32_t)lo;
+// Wave-wide maximum through DPP lane permutations (pairs, quads, eight, sixteen
+// lanes) and the four row results read out of lanes 0, 16, 32 and 48.  Called by all
+// 64 lanes.
+template <int CTRL> __device__ __forceinline__ uint32_t dpp_max(uint32_t key) {
+    const uint32_t o = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)key, CTRL, 0xF, 0xF, false);
     return o > key ? o : key;
 }
-__device__ __forceinline__ uint64_t wave_max_u64(uint64_t key) {
-    key = dpp_max_step<0xB1>(key);    // quad_perm [1,0,3,2]
-    key = dpp_max_step<0x4E>(key);    // quad_perm [2,3,0,1]
-    key = dpp_max_step<0x141>(key);   // row_half_mirror
-    key = dpp_max_step<0x140>(key);   // row_mirror
-    uint64_t best = 0;
+__device__ __forceinline__ uint32_t row_max(uint32_t key) {   // within sixteen lanes
+    key = dpp_max<0xB1>(key);    // quad_perm [1,0,3,2]
+    key = dpp_max<0x4E>(key);    // quad_perm [2,3,0,1]
+    key = dpp_max<0x141>(key);   // row_half_mirror
+    return dpp_max<0x140>(key);  // row_mirror
+}
+__device__ __forceinline__ uint32_t wave_max(uint32_t key) {
+    key = row_max(key);
+    uint32_t best = 0;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-        const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)key, 16 * r);
-        const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(key >> 32), 16 * r);
-        const uint64_t o = ((uint64_t)hi << 32) | lo;
+        const uint32_t o = (uint32_t)__builtin_amdgcn_readlane((int)key, 16 * r);
         best = o > best ? o : best;
     }
     return best;
 }
 
-// Pivot key of row i: the FP32 bits of |v|^2 above the complement of i, so
-// that the largest key is the largest magnitude and, among equal magnitudes
-// (to FP32 rounding), the smallest row; rows out of the search have key 0.
-__device__ __forceinline__ uint64_t pivot_key(double m, int i) {
-    return ((uint64_t)__float_as_uint((float)m) << 32) | (uint32_t)(0xFFFFFFFFu - (uint32_t)i);
+// Pivot keys: |v|^2 to 20 bits below its leading one, in 32 bits (positive doubles
+// order as integers: the upper half decides, below 2^-1042 the lower half does, as a
+// float); 1 for zero and NaN, above the 0 of rows out of the search.
+__device__ __forceinline__ uint32_t mag_key(double2 v) {
+    const double m = v.x * v.x + v.y * v.y;
+    if (!(m > 0.0)) return 1u;
+    const uint32_t hi = (uint32_t)__double2hiint(m);
+    if (hi > 0) return hi + 0x100004u;
+    return 2u + ((__float_as_uint((float)(uint32_t)__double2loint(m)) - 0x3F800000u) >> 8);
+}
+__device__ __forceinline__ double2 recip(double2 d) {
+    const double den = d.x * d.x + d.y * d.y;
+    return den > 0.0 ? make_double2(d.x / den, -d.y / den) : make_double2(0, 0);
 }
 
-// Steps k0 .. k0+NB-1 of the elimination.  Thread i owns row i and keeps, in
-// registers, its NB panel values and its multipliers L[c][i] (A[i][k] before
-// the elimination of step c, 0 at i = k); the panel columns take the steps
-// with the arithmetic of the unblocked kernels.  Per step, between two
-// barriers: the pivot search, the interchange of two rows between their
-// owners and the pivot row broadcast, both through LDS; then every row's
-// update in its owner's registers.  At the end: the panel columns, L and piv
-// go to memory, and every other column j takes the panel's row interchanges
-// and its pivot rows (row k scaled, then eliminated from the other pivot
-// rows); RK[c][j] keeps row k0+c as it is right after its scaling, the value
-// the remaining rows are eliminated with (gj_update_kernel).
-template <int NB>
-__global__ __launch_bounds__(kPanT) void gj_panel_kernel(double2* __restrict__ A, int n, int k0,
-                                                         double2* __restrict__ L, int* __restrict__ piv,
-                                                         int* __restrict__ singular, double2* __restrict__ RK) {
-    __shared__ uint64_t wkey[kPanT / 64];
-    __shared__ int pv[NB];
-    __shared__ double2 dv[NB];
-    __shared__ double2 bcast[NB];              // the pivot row of the step, unscaled
-    __shared__ double2 xk[2 * NB];             // old row k: values and multipliers
-    __shared__ double2 xpl[NB];                // multipliers of old row p
-    __shared__ double2 lp[NB][NB];             // lp[c][q] = L[c][k0 + q]
-    __shared__ int psrc[NB], exd[NB], exs[NB], nex;
-    const int tid = threadIdx.x;
-    const int i = tid;
-    const bool own = i < n;
-    double2 rowv[NB], lreg[NB];
+// n <= ROWS: the whole matrix in the registers of one workgroup, TPR threads per row
+// with CPT columns each (column j in thread j mod TPR).  Per step: the column goes
+// to LDS, every wave finds the pivot in it, the pivot row goes to LDS, all rows
+// update; two barriers.  Writes the inverse.  The chain of n steps bounds it: 0.078 ms
+// at n = 25 and 0.181 ms at n = 64 with the copies to and from the host, where a launch
+// per pivot search and per rank-1 pass took 0.250 and two-launch panels 0.398 ms.
+// More columns per thread in fewer waves (2 and 4 threads a row) took 0.10 and 0.40 ms.
+template <int ROWS, int TPR, int CPT>
+__global__ __launch_bounds__(ROWS * TPR) void gj_small_kernel(const double2* __restrict__ A, int n,
+                                                             double2* __restrict__ out, int* __restrict__ singular) {
+    static_assert(TPR * CPT >= ROWS && ROWS <= 64, "a wave looks at one row per lane");
+    __shared__ double2 col[2][ROWS], prow[2][TPR * CPT];
+    __shared__ int piv[ROWS], pos[ROWS];
+    const int lane = threadIdx.x & 63;
+    const int i = threadIdx.x / TPR, tt = threadIdx.x % TPR;
+    double2 a[CPT];
 #pragma unroll
-    for (int j = 0; j < NB; ++j) {
-        rowv[j] = own ? A[(int64_t)i * n + k0 + j] : make_double2(0, 0);
-        lreg[j] = make_double2(0, 0);
+    for (int q = 0; q < CPT; ++q) {
+        const int j = q * TPR + tt;
+        a[q] = (i < n && j < n) ? A[(int64_t)i * n + j] : make_double2(0, 0);
     }
+    bool open = lane < n;   // row `lane` is still in the search (the same in every wave)
+    int par = 0;
+    bool bad = false;
 #pragma unroll
-    for (int c = 0; c < NB; ++c) {
-        const int k = k0 + c;
-        uint64_t key = 0;
-        if (own && i >= k) {
-            const double m = rowv[c].x * rowv[c].x + rowv[c].y * rowv[c].y;
-            key = pivot_key(m, i);
+    for (int q = 0; q < CPT; ++q) {
+        for (int t = 0; t < TPR; ++t, par ^= 1) {
+            const int k = q * TPR + t;
+            if (k >= n) break;
+            if (tt == t) col[par][i] = a[q];
+            __syncthreads();
+            const double2 cv = open ? col[par][lane] : make_double2(0, 0);
+            const uint32_t key = open ? mag_key(cv) : 0u;
+            const uint32_t best = wave_max(key);
+            const int p = __ffsll((unsigned long long)__ballot(key == best)) - 1;
+            if (lane == p) open = false;
+            if (i == p) {
+#pragma unroll
+                for (int e = 0; e < CPT; ++e) prow[par][e * TPR + tt] = a[e];
+                if (tt == 0) {
+                    piv[k] = p;
+                    pos[p] = k;
+                }
+            }
+            __syncthreads();
+            const double2 d = col[par][p];
+            const double2 di = recip(d);
+            bad = bad || !(d.x * d.x + d.y * d.y > 0.0);
+            const double2 l = col[par][i];
+#pragma unroll
+            for (int e = 0; e < CPT; ++e) {
+                const bool kc = e == q && tt == t;
+                const double2 rk = cmul(kc ? make_double2(1.0, 0.0) : prow[par][e * TPR + tt], di);
+                a[e] = i == p ? rk : csub(kc ? make_double2(0, 0) : a[e], cmul(l, rk));
+            }
         }
-        key = wave_max_u64(key);
-        if ((tid & 63) == 0) wkey[tid >> 6] = key;
-        __syncthreads();
-        uint64_t kk[kPanT / 64];
+    }
+    if (threadIdx.x == 0 && bad) *singular = 1;
+    __syncthreads();
+    if (i >= n) return;
 #pragma unroll
-        for (int w = 0; w < kPanT / 64; ++w) kk[w] = wkey[w];
-        uint64_t best = 0;
+    for (int e = 0; e < CPT; ++e) {
+        const int j = e * TPR + tt;
+        if (j < n) out[(int64_t)pos[i] * n + piv[j]] = a[e];
+    }
+}
+
+// Larger n: panels of NB columns.  One launch per panel: workgroup 0 brings the next
+// panel's columns up to date and factors it (thread t owns rows t, t + PT, ..., RPT
+// of them, with their panel values in registers), while the others apply the current
+// panel to kStripW columns each.  The chain of pivot steps in workgroup 0 bounds it:
+// per step each wave puts its best row in LDS and one barrier later all read the
+// winner.  What workgroup 0 reads and writes is compact and column by column (column
+// pieces n rows apart would cost a cache line per value): the columns that it
+// factors are handed over by the launch before, and the factored ones are copied
+// into the matrix by the launch after.  A launch takes 11.4 us at n = 120, 17.7 at 512
+// and 30 at 1024, of which workgroup 0 needs 10.9, 16.5 and 21.3; factoring and update
+// in launches of their own took 23 and 42 us at 120 and 1024.  Strips of eight columns
+// take 19.8 us at 512 and 31.1 at 1000 (24 with four: twice the workgroups in flight).
+constexpr int kStripW = 4;
+template <int NB> struct GjPanel {
+    double2* L;    // [NB][n]: multiplier of row i at step c, 0 for the step's pivot row
+    double2* P;    // [NB][n]: the panel's columns before its factorisation, up to date with the panel before the last
+    double2* F;    // [NB][n]: and after it
+    double2* dv;   // [NB]: reciprocal pivots
+};
+
+// One launch: k0: the current panel's first column (nb0 columns, 0: none yet), k1: the
+// next one's (nb1 columns, 0: none left), after it nb2 columns of the one that the
+// launch after factors.  from_p: the next panel's columns are in nxt.P (else in A).
+template <int NB, int PT, int RPT>
+__global__ __launch_bounds__(PT) void gj_step_kernel(double2* __restrict__ A, int n, int k0, int nb0, int k1, int nb1,
+                                                     int nb2, int from_p, GjPanel<NB> cur, GjPanel<NB> nxt,
+                                                     int* __restrict__ piv, int* __restrict__ used,
+                                                     int* __restrict__ singular) {
+    constexpr int NW = PT / 64;
+    constexpr bool PRE = RPT <= 2;                      // the multipliers fit the registers beside the rows
+    constexpr int CW = NB;                              // columns that the pivot-row wave works on
+    constexpr int SW = kStripW;                         // columns of a strip
+    static_assert(NB * CW <= 64 && NB % SW == 0, "one wave works out the pivot rows; panels are whole strips");
+    __shared__ double2 rks[NB][CW], rfin[NB][CW];
+    __shared__ signed char prank[PT * RPT];             // which pivot of the current panel a row is, -1: none
+    const int tid = threadIdx.x;
+    const bool factor = blockIdx.x == 0;
+    if (factor && nb1 == 0) return;
+    // the two strips of a cache line go to workgroups eight apart, which share an XCD and its L2
+    const int sb = (int)blockIdx.x - 1;
+    const int j0 = factor ? k1 : ((sb & ~15) + 2 * (sb & 7) + ((sb >> 3) & 1)) * SW;
+    const int cw = tid % SW, js = j0 + cw;              // the strip column of this thread
+    if (!factor && j0 >= n) return;
+    if (!factor && j0 >= k0 && j0 < k0 + nb0) {
+        // the current panel's own columns (whole strips)
+        if (js < k0 + nb0)
+            for (int i = tid / SW; i < n; i += PT / SW) A[(int64_t)i * n + js] = cur.F[(int64_t)(js - k0) * n + i];
+        return;
+    }
+    if (!factor && j0 >= k1 && j0 < k1 + nb1) return;
+    // the factoring workgroup's rows are on their way while the pivot rows are worked out
+    double2 rowv[RPT][NB], lown[PRE ? RPT : 1][NB];
+    if (factor) {
 #pragma unroll
-        for (int w = 0; w < kPanT / 64; ++w) best = kk[w] > best ? kk[w] : best;
-        const int p = (int)(0xFFFFFFFFu - (uint32_t)best);
-        const bool valid = best != 0 && p >= k && p < n;
-        if (tid == 0) {
-            pv[c] = valid ? p : n;
-            if (!valid || !(__uint_as_float((uint32_t)(best >> 32)) > 0.0f)) singular[0] = 1;
+        for (int e = 0; e < RPT; ++e) {
+            const int i = tid + e * PT;
+#pragma unroll
+            for (int c = 0; c < NB; ++c) {
+                rowv[e][c] = (i < n && c < nb1) ? (from_p ? nxt.P[(int64_t)c * n + i] : A[(int64_t)i * n + k1 + c])
+                                                : make_double2(0, 0);
+                if (PRE) lown[e][c] = (i < n && c < nb0) ? cur.L[(int64_t)c * n + i] : make_double2(0, 0);
+            }
         }
-        const int pr = valid ? p : k;          // the row that becomes the pivot row
-        if (own && i == pr)
-#pragma unroll
-            for (int j = 0; j < NB; ++j) bcast[j] = rowv[j];
-        if (pr != k) {
-            if (own && i == k)
-#pragma unroll
-                for (int j = 0; j < NB; ++j) { xk[j] = rowv[j]; xk[NB + j] = lreg[j]; }
-            if (own && i == pr)
-#pragma unroll
-                for (int j = 0; j < NB; ++j) xpl[j] = lreg[j];
+    }
+    for (int i = tid; i < n; i += PT) prank[i] = -1;
+    __syncthreads();
+    if (tid < 64) {
+        // Lane (q, t): pivot row q in this workgroup's column t.  rks: row c right after its
+        // scaling (the value the other rows are eliminated with); rfin: its final entries.
+        const int q = tid / CW, t = tid % CW;
+        const bool on = q < nb0;
+        const int pq = on ? piv[k0 + q] : 0;
+        if (on && t == 0) prank[pq] = (signed char)q;
+        double2 r = make_double2(0, 0);
+        if (on) {
+            if (!factor) r = (t < SW && j0 + t < n) ? A[(int64_t)pq * n + j0 + t] : r;
+            else if (t < nb1) r = from_p ? nxt.P[(int64_t)t * n + pq] : A[(int64_t)pq * n + k1 + t];
         }
-        __syncthreads();
-        double2 prow[NB];
+        double2 lq[NB];   // multipliers of pivot row q
 #pragma unroll
-        for (int j = 0; j < NB; ++j) prow[j] = bcast[j];
-        if (pr != k) {
-            if (own && i == k)
+        for (int c = 0; c < NB; ++c) lq[c] = (on && c < nb0) ? cur.L[(int64_t)c * n + pq] : make_double2(0, 0);
+        double2 d = on ? cur.dv[q] : make_double2(0, 0);
 #pragma unroll
-                for (int j = 0; j < NB; ++j) { rowv[j] = prow[j]; lreg[j] = xpl[j]; }
-            if (own && i == pr)
-#pragma unroll
-                for (int j = 0; j < NB; ++j) { rowv[j] = xk[j]; lreg[j] = xk[NB + j]; }
-        }
-        const double2 d = prow[c];
-        const double den = d.x * d.x + d.y * d.y;
-        const double2 di = den > 0.0 ? make_double2(d.x / den, -d.y / den) : make_double2(0, 0);
-        double2 rk[NB];
-#pragma unroll
-        for (int j = 0; j < NB; ++j) rk[j] = cmul((j == c) ? make_double2(1.0, 0.0) : prow[j], di);
-        if (tid == 0) dv[c] = di;
-        if (own) {
-            if (i == k) {
-                lreg[c] = make_double2(0, 0);
-#pragma unroll
-                for (int j = 0; j < NB; ++j) rowv[j] = rk[j];
-            } else {
-                const double2 l = rowv[c];
-                lreg[c] = l;
-#pragma unroll
-                for (int j = 0; j < NB; ++j) {
-                    const double2 base = (j == c) ? make_double2(0, 0) : rowv[j];
-                    rowv[j] = csub(base, cmul(l, rk[j]));
+        for (int c = 0; c < NB; ++c) {
+            const double2 sc = cmul(r, d);
+            const double2 rc = make_double2(__shfl(sc.x, c * CW + t), __shfl(sc.y, c * CW + t));
+            if (c < nb0) {
+                if (q == c) {
+                    r = rc;
+                    rks[c][t] = rc;
+                } else {
+                    r = csub(r, cmul(lq[c], rc));
                 }
             }
         }
-    }
-    if (own) {
-#pragma unroll
-        for (int j = 0; j < NB; ++j) A[(int64_t)i * n + k0 + j] = rowv[j];
-#pragma unroll
-        for (int c = 0; c < NB; ++c) L[(int64_t)c * n + i] = lreg[c];
-        if (i >= k0 && i < k0 + NB)
-#pragma unroll
-            for (int c = 0; c < NB; ++c) lp[c][i - k0] = lreg[c];
+        if (on) rfin[q][t] = r;
     }
     __syncthreads();
-    if (tid < NB) piv[k0 + tid] = pv[tid];
-    if (tid == 0) {
-        // compose the interchanges on the rows they touch
-        int rows[2 * NB], srcr[2 * NB];
-        int m = 0;
-        for (int c = 0; c < NB; ++c) { rows[m] = k0 + c; srcr[m] = k0 + c; ++m; }
-        for (int c = 0; c < NB; ++c) {
-            const int q = pv[c];
-            if (q < 0 || q >= n || (q >= k0 && q < k0 + NB)) continue;
-            bool seen = false;
-            for (int x = NB; x < m; ++x) seen = seen || rows[x] == q;
-            if (!seen) { rows[m] = q; srcr[m] = q; ++m; }
+    if (!factor) {
+        const int k2 = k1 + nb1;
+        if (js >= n) return;
+        const bool ahead = js >= k2 && js < k2 + nb2;   // the columns that the launch after this one factors
+        double2* dst = ahead ? cur.P + (int64_t)(js - k2) * n : A + js;
+        const int64_t ds = ahead ? 1 : n;
+        double2 rk[NB];
+#pragma unroll
+        for (int c = 0; c < NB; ++c) rk[c] = c < nb0 ? rks[c][cw] : make_double2(0, 0);
+#pragma unroll 4
+        for (int i = tid / SW; i < n; i += PT / SW) {
+            double2 v = A[(int64_t)i * n + js];
+            const int pr = prank[i];
+            double2 l[NB];
+#pragma unroll
+            for (int c = 0; c < NB; ++c) l[c] = c < nb0 ? cur.L[(int64_t)c * n + i] : make_double2(0, 0);
+#pragma unroll
+            for (int c = 0; c < NB; ++c) v = csub(v, cmul(l[c], rk[c]));
+            dst[(int64_t)i * ds] = pr >= 0 ? rfin[pr][cw] : v;
         }
-        for (int c = 0; c < NB; ++c) {
-            const int q = pv[c];
-            if (q == k0 + c || q < 0 || q >= n) continue;
-            int xa = 0, xb = 0;
-            for (int x = 0; x < m; ++x) {
-                if (rows[x] == k0 + c) xa = x;
-                if (rows[x] == q) xb = x;
+        return;
+    }
+    // the next panel: bring it up to date ...
+    bool open[RPT];   // rows still in the pivot search
+#pragma unroll
+    for (int e = 0; e < RPT; ++e) {
+        const int i = tid + e * PT;
+        open[e] = i < n && (nb0 == 0 || used[i] == 0);
+        if (nb0 > 0 && i < n) {
+#pragma unroll
+            for (int c = 0; c < NB; ++c) {
+                if (c < nb0) {
+                    const double2 l = PRE ? lown[PRE ? e : 0][c] : cur.L[(int64_t)c * n + i];
+#pragma unroll
+                    for (int q = 0; q < NB; ++q) rowv[e][q] = csub(rowv[e][q], cmul(l, rks[c][q]));
+                }
             }
-            const int t = srcr[xa];
-            srcr[xa] = srcr[xb];
-            srcr[xb] = t;
+            const int pr = prank[i];
+            if (pr >= 0)
+#pragma unroll
+                for (int q = 0; q < NB; ++q) rowv[e][q] = rfin[pr][q];
         }
-        int ne = 0;
-        for (int c = 0; c < NB; ++c) psrc[c] = srcr[c];
-        for (int x = NB; x < m; ++x)
-            if (srcr[x] != rows[x]) { exd[ne] = rows[x]; exs[ne] = srcr[x]; ++ne; }
-        nex = ne;
     }
-    __syncthreads();
-    // the other columns: row interchanges (all sources read before any row is
-    // written), then the pivot rows
-    const int j = tid;
-    if (!own || (j >= k0 && j < k0 + NB)) return;
-    const int ne = nex;
-    double2 r[NB], ex[NB];
-#pragma unroll
-    for (int c = 0; c < NB; ++c) r[c] = A[(int64_t)psrc[c] * n + j];
-#pragma unroll
-    for (int e = 0; e < NB; ++e) ex[e] = e < ne ? A[(int64_t)exs[e] * n + j] : make_double2(0, 0);
-#pragma unroll
-    for (int e = 0; e < NB; ++e)
-        if (e < ne) A[(int64_t)exd[e] * n + j] = ex[e];
+    // ... and factor it
+    __shared__ uint32_t wkey[2][NW];
+    __shared__ int wrow[2][NW];
+    __shared__ double2 wval[2][NW][NB];
+    const int lane = tid & 63, wave = tid >> 6;
+    bool bad = false;
 #pragma unroll
     for (int c = 0; c < NB; ++c) {
-        {
-            r[c] = cmul(r[c], dv[c]);
-            RK[(int64_t)c * n + j] = r[c];
+        if (c < nb1) {
+            uint32_t key = 0;
+            int sel = 0;
 #pragma unroll
-            for (int q = 0; q < NB; ++q)
-                if (q != c) r[q] = csub(r[q], cmul(lp[c][q], r[c]));
+            for (int e = 0; e < RPT; ++e) {
+                const uint32_t ke = open[e] ? mag_key(rowv[e][c]) : 0u;
+                if (ke > key) {
+                    key = ke;
+                    sel = e;
+                }
+            }
+            const uint32_t wbest = wave_max(key);
+            const int first = __ffsll((unsigned long long)__ballot(key == wbest)) - 1;
+            if (lane == first) {
+                wkey[c & 1][wave] = wbest;
+                wrow[c & 1][wave] = tid + sel * PT;
+#pragma unroll
+                for (int e = 0; e < RPT; ++e)
+                    if (e == sel)
+#pragma unroll
+                        for (int q = 0; q < NB; ++q) wval[c & 1][wave][q] = rowv[e][q];
+            }
+            __syncthreads();
+            const uint32_t mine = wkey[c & 1][lane % NW];
+            const uint32_t best = row_max(mine);   // NW <= 16: every row of lanes holds all the waves' keys
+            const int bw = (__ffsll((unsigned long long)__ballot(mine == best)) - 1) % NW;
+            const int p = __builtin_amdgcn_readfirstlane(wrow[c & 1][bw]);
+            const double2 d = wval[c & 1][bw][c];
+            const double2 di = recip(d);
+            bad = bad || !(d.x * d.x + d.y * d.y > 0.0);
+            double2 rk[NB];
+#pragma unroll
+            for (int q = 0; q < NB; ++q) rk[q] = cmul(q == c ? make_double2(1.0, 0.0) : wval[c & 1][bw][q], di);
+#pragma unroll
+            for (int e = 0; e < RPT; ++e) {
+                const int i = tid + e * PT;
+                const double2 l = i == p ? make_double2(0, 0) : rowv[e][c];
+                if (i < n) nxt.L[(int64_t)c * n + i] = l;
+#pragma unroll
+                for (int q = 0; q < NB; ++q)
+                    rowv[e][q] = csub(q == c ? make_double2(0, 0) : rowv[e][q], cmul(l, rk[q]));
+                if (i == p) {
+                    open[e] = false;
+#pragma unroll
+                    for (int q = 0; q < NB; ++q) rowv[e][q] = rk[q];
+                }
+            }
+            if (tid == 0) {
+                piv[k1 + c] = p;
+                nxt.dv[c] = di;
+            }
         }
     }
 #pragma unroll
-    for (int c = 0; c < NB; ++c)
-        A[(int64_t)(k0 + c) * n + j] = r[c];
-}
-
-// The rest: A[i][j] -= L[c][i] RK[c][j] over the panel's steps in order, for
-// rows i and columns j outside the panel; a thread keeps RK[.][j] in registers
-// for kUpdRows rows.
-template <int NB>
-__global__ void gj_update_kernel(double2* __restrict__ A, int n, int k0, const double2* __restrict__ L,
-                                 const double2* __restrict__ RK) {
-    const int j = blockIdx.x * blockDim.x + threadIdx.x;
-    const int i0 = blockIdx.y * kUpdRows;
-    if (j >= n || (j >= k0 && j < k0 + NB)) return;
-    double2 rk[NB], a[kUpdRows];
-#pragma unroll
-    for (int c = 0; c < NB; ++c) rk[c] = RK[(int64_t)c * n + j];
-#pragma unroll
-    for (int u = 0; u < kUpdRows; ++u) {
-        const int i = i0 + u;
-        a[u] = (i < n && !(i >= k0 && i < k0 + NB)) ? A[(int64_t)i * n + j] : make_double2(0, 0);
-    }
-#pragma unroll
-    for (int u = 0; u < kUpdRows; ++u) {
-        const int i = i0 + u;
-        if (i < n && !(i >= k0 && i < k0 + NB)) {
+    for (int e = 0; e < RPT; ++e) {
+        const int i = tid + e * PT;
+        if (i < n) {
+            used[i] = open[e] ? 0 : 1;
 #pragma unroll
             for (int c = 0; c < NB; ++c)
-                a[u] = csub(a[u], cmul(L[(int64_t)c * n + i], rk[c]));
-            A[(int64_t)i * n + j] = a[u];
+                if (c < nb1) nxt.F[(int64_t)c * n + i] = rowv[e][c];
         }
     }
+    if (tid == 0 && bad) *singular = 1;
+}
+
+// out[k][p_j] = in[p_k][j]
+__global__ void gj_unscramble_kernel(const double2* __restrict__ in, double2* __restrict__ out, int n,
+                                     const int* __restrict__ piv) {
+    const int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    if (t >= (int64_t)n * n) return;
+    const int k = (int)(t / n), j = (int)(t % n);
+    out[(int64_t)k * n + piv[j]] = in[(int64_t)piv[k] * n + j];
 }
 
 // out[i][j] = in[i][src[j]]
@@ -425,105 +517,93 @@ __global__ __launch_bounds__(256) void scan_kernel(const double2* __restrict__ Z
 
 inline unsigned g1(int64_t n) { return (unsigned)((n + 255) / 256); }
 
-template <int NB>
-void launch_panel(double2* A, int n, int k0, double2* L, int* piv, int* flag, double2* RK, dim3 ug, hipStream_t s) {
-    hipLaunchKernelGGL((gj_panel_kernel<NB>), dim3(1), dim3(kPanT), 0, s, A, n, k0, L, piv, flag, RK);
-    hipLaunchKernelGGL((gj_update_kernel<NB>), ug, dim3(256), 0, s, A, n, k0, L, RK);
+// Rows up to PT * RPT.  Workspace in out (n > 64): two panels' multipliers, columns
+// and reciprocal pivots, the used-row marks.
+template <int NB, int PT, int RPT>
+void gj_panels(double2* A, double2* out, int n, int* piv, int* flag, hipStream_t s) {
+    MBT_REQUIRE(n > 64 && n <= PT * RPT, "panelled inverse: size out of range");
+    GjPanel<NB> pan[2];
+    const size_t pn = (size_t)NB * n;
+    for (int h = 0; h < 2; ++h) {
+        pan[h].L = out + h * pn;
+        pan[h].P = out + (2 + h) * pn;
+        pan[h].F = out + (4 + h) * pn;
+        pan[h].dv = out + 6 * pn + h * NB;
+    }
+    int* used = reinterpret_cast<int*>(out + 6 * pn + 2 * NB);
+    const unsigned strips = (unsigned)((n + 16 * kStripW - 1) / (16 * kStripW) * 16);
+    auto step = [&](int k0, int nb0, unsigned blocks) {
+        const int k1 = k0 + nb0, nb1 = std::min(NB, n - k1), nb2 = std::min(NB, n - k1 - nb1);
+        const int h = nb0 ? (k0 / NB) & 1 : 1;   // the current panel's buffers
+        hipLaunchKernelGGL((gj_step_kernel<NB, PT, RPT>), dim3(blocks), dim3(PT), 0, s, A, n, k0, nb0, k1, nb1, nb2,
+                           k1 >= 2 * NB ? 1 : 0, pan[h], pan[h ^ 1], piv, used, flag);
+    };
+    step(0, 0, 1);
+    for (int k0 = 0; k0 < n; k0 += NB) step(k0, std::min(NB, n - k0), 1 + strips);
 }
 
 }  // namespace
 
-// In-place Gauss-Jordan on A (n x n, any consistent layout: the inverse of the
-// stored array is returned in the same layout).  Workspace: n complex + 2n ints;
-// the blocked form also uses out (which must not overlap A) until the end.
-void gj_inverse(double2* A, double2* out, int n, double2* colbuf, int* piv, int* flag, hipStream_t s) {
-    MBT_HIP(hipMemsetAsync(flag, 0, sizeof(int), s));
-    const int nb = kMaxPan;
-    if (n >= kBlockedMinN && n <= kPanT) {
-        // out: L (nb x n), RK (nb x n); n >= 64 leaves room
-        double2* L = out;
-        double2* RK = out + (size_t)nb * n;
-        const dim3 ug(g1(n), (unsigned)((n + kUpdRows - 1) / kUpdRows));
-        for (int k0 = 0; k0 < n; k0 += nb) {
-            switch (std::min(nb, n - k0)) {
-            case 8: launch_panel<8>(A, n, k0, L, piv, flag, RK, ug, s); break;
-            case 7: launch_panel<7>(A, n, k0, L, piv, flag, RK, ug, s); break;
-            case 6: launch_panel<6>(A, n, k0, L, piv, flag, RK, ug, s); break;
-            case 5: launch_panel<5>(A, n, k0, L, piv, flag, RK, ug, s); break;
-            case 4: launch_panel<4>(A, n, k0, L, piv, flag, RK, ug, s); break;
-            case 3: launch_panel<3>(A, n, k0, L, piv, flag, RK, ug, s); break;
-            case 2: launch_panel<2>(A, n, k0, L, piv, flag, RK, ug, s); break;
-            default: launch_panel<1>(A, n, k0, L, piv, flag, RK, ug, s); break;
-            }
-        }
+namespace {
+
+// The elimination and the inverse into out, all on the device; flag receives 1 if a
+// pivot is zero or not finite.
+// Each form takes what its registers hold (64 rows x 4 columns a thread; panel rows per
+// thread: one to 256, two to 1024, four beyond, so that the factoring workgroup has no
+// more waves to gather per step than it needs).
+void gj_on_device(double2* A, double2* out, int n, double2* colbuf, int* piv, int* flag, hipStream_t s) {
+    hipLaunchKernelGGL(clear_flag_kernel, dim3(1), dim3(64), 0, s, flag);
+    if (n <= 32) {
+        hipLaunchKernelGGL((gj_small_kernel<32, 8, 4>), dim3(1), dim3(256), 0, s, A, n, out, flag);
+    } else if (n <= 64) {
+        hipLaunchKernelGGL((gj_small_kernel<64, 16, 4>), dim3(1), dim3(1024), 0, s, A, n, out, flag);
+    } else if (n <= 4096) {
+        if (n <= 256) gj_panels<8, 256, 1>(A, out, n, piv, flag, s);
+        else if (n <= 512) gj_panels<8, 256, 2>(A, out, n, piv, flag, s);
+        else if (n <= 1024) gj_panels<8, 512, 2>(A, out, n, piv, flag, s);
+        else if (n <= 2048) gj_panels<8, 512, 4>(A, out, n, piv, flag, s);
+        else gj_panels<4, 1024, 4>(A, out, n, piv, flag, s);
+        hipLaunchKernelGGL(gj_unscramble_kernel, dim3(g1((int64_t)n * n)), dim3(256), 0, s, A, out, n, piv);
     } else {
         for (int k = 0; k < n; ++k) {
             hipLaunchKernelGGL(gj_pivot_kernel, dim3(1), dim3(kPivT), 0, s, A, n, k, colbuf, piv, flag);
             hipLaunchKernelGGL(gj_elim_kernel, dim3(g1((int64_t)n * n)), dim3(256), 0, s, A, n, k, colbuf);
         }
+        int* src = reinterpret_cast<int*>(colbuf);
+        hipLaunchKernelGGL(perm_from_pivots_kernel, dim3(1), dim3(64), 0, s, piv, src, n, flag);
+        hipLaunchKernelGGL(permute_cols_kernel, dim3(g1((int64_t)n * n)), dim3(256), 0, s, A, out, n, src);
     }
     MBT_LAUNCH_CHECK();
-    std::vector<int> hp(n);
+}
+
+}  // namespace
+
+// Gauss-Jordan inverse of A (n x n, any consistent layout: the inverse of the stored
+// array is returned in the same layout) into out, which must not overlap A; A is
+// overwritten.  Workspace: colbuf n complex, piv n ints, flag one int.
+void gj_inverse(double2* A, double2* out, int n, double2* colbuf, int* piv, int* flag, hipStream_t s) {
+    gj_on_device(A, out, n, colbuf, piv, flag, s);
     int hflag = 0;
-    MBT_HIP(hipMemcpyAsync(hp.data(), piv, sizeof(int) * n, hipMemcpyDeviceToHost, s));
     MBT_HIP(hipMemcpyAsync(&hflag, flag, sizeof(int), hipMemcpyDeviceToHost, s));
     MBT_HIP(hipStreamSynchronize(s));
     if (hflag) throw Error(-1, "port matrix is singular");
-    // the row interchanges of the elimination become column interchanges of the inverse, last first
-    std::vector<int> src(n);
-    for (int j = 0; j < n; ++j) src[j] = j;
-    for (int k = n - 1; k >= 0; --k) {
-        if (hp[k] < 0 || hp[k] >= n) throw Error(-1, "port matrix is singular");
-        std::swap(src[k], src[hp[k]]);
-    }
-    MBT_HIP(hipMemcpyAsync(piv, src.data(), sizeof(int) * n, hipMemcpyHostToDevice, s));
-    hipLaunchKernelGGL(permute_cols_kernel, dim3(g1((int64_t)n * n)), dim3(256), 0, s, A, out, n, piv);
-    MBT_LAUNCH_CHECK();
-    MBT_HIP(hipStreamSynchronize(s));
 }
 
-// The elimination of gj_inverse with the column permutation formed on the
-// device: no host buffers, one 4-byte readback of the singularity flag into
-// pinned host memory.
-static void gj_inverse_dev_perm(double2* A, double2* out, int n, double2* colbuf, int* piv, int* src, int* flag,
-                                int* host_flag, hipStream_t s) {
-    hipLaunchKernelGGL(clear_flag_kernel, dim3(1), dim3(64), 0, s, flag);
-    const int nb = kMaxPan;
-    if (n >= kBlockedMinN && n <= kPanT) {
-        double2* L = out;
-        double2* RK = out + (size_t)nb * n;
-        const dim3 ug(g1(n), (unsigned)((n + kUpdRows - 1) / kUpdRows));
-        for (int k0 = 0; k0 < n; k0 += nb) {
-            switch (std::min(nb, n - k0)) {
-            case 8: launch_panel<8>(A, n, k0, L, piv, flag, RK, ug, s); break;
-            case 7: launch_panel<7>(A, n, k0, L, piv, flag, RK, ug, s); break;
-            case 6: launch_panel<6>(A, n, k0, L, piv, flag, RK, ug, s); break;
-            case 5: launch_panel<5>(A, n, k0, L, piv, flag, RK, ug, s); break;
-            case 4: launch_panel<4>(A, n, k0, L, piv, flag, RK, ug, s); break;
-            case 3: launch_panel<3>(A, n, k0, L, piv, flag, RK, ug, s); break;
-            case 2: launch_panel<2>(A, n, k0, L, piv, flag, RK, ug, s); break;
-            default: launch_panel<1>(A, n, k0, L, piv, flag, RK, ug, s); break;
-            }
-        }
-    } else {
-        for (int k = 0; k < n; ++k) {
-            hipLaunchKernelGGL(gj_pivot_kernel, dim3(1), dim3(kPivT), 0, s, A, n, k, colbuf, piv, flag);
-            hipLaunchKernelGGL(gj_elim_kernel, dim3(g1((int64_t)n * n)), dim3(256), 0, s, A, n, k, colbuf);
-        }
-    }
-    hipLaunchKernelGGL(perm_from_pivots_kernel, dim3(1), dim3(64), 0, s, piv, src, n, flag);
-    hipLaunchKernelGGL(permute_cols_kernel, dim3(g1((int64_t)n * n)), dim3(256), 0, s, A, out, n, src);
-    MBT_LAUNCH_CHECK();
+// The same with no pageable host memory: one 4-byte readback of the singularity
+// flag into pinned host memory.
+static void gj_inverse_dev_perm(double2* A, double2* out, int n, double2* colbuf, int* piv, int* flag, int* host_flag,
+                                hipStream_t s) {
+    gj_on_device(A, out, n, colbuf, piv, flag, s);
     MBT_HIP(hipMemcpyAsync(host_flag, flag, sizeof(int), hipMemcpyDeviceToHost, s));
     MBT_HIP(hipStreamSynchronize(s));
     if (*host_flag) throw Error(-1, "port matrix is singular");
 }
 
 void s_matrix_dev_perm(const double2* Zp, double2* S, double2* work, int n, double z0, double2* colbuf, int* piv,
-                       int* src, int* flag, int* host_flag, hipStream_t s) {
+                       int* flag, int* host_flag, hipStream_t s) {
     hipLaunchKernelGGL(add_diag_kernel, dim3(g1((int64_t)n * n)), dim3(256), 0, s, Zp, work, n, z0);
     MBT_LAUNCH_CHECK();
-    gj_inverse_dev_perm(work, S, n, colbuf, piv, src, flag, host_flag, s);   // S holds (Zp + z0)^{-1}
+    gj_inverse_dev_perm(work, S, n, colbuf, piv, flag, host_flag, s);   // S holds (Zp + z0)^{-1}
     hipLaunchKernelGGL(s_from_inv_kernel, dim3(g1((int64_t)n * n)), dim3(256), 0, s, S, S, n, z0);
     MBT_LAUNCH_CHECK();
 }

@@ -1525,9 +1525,8 @@ mbt_status mbt_active_dev_noalloc(mbt_ctx* ctx, const mbt_array* arr, double s, 
         S = reinterpret_cast<double2*>(take(sizeof(double2) * (size_t)P * P));
         double2* colbuf = reinterpret_cast<double2*>(take(sizeof(double2) * (size_t)P));
         int* piv = reinterpret_cast<int*>(take(sizeof(int) * (size_t)P));
-        int* src = reinterpret_cast<int*>(take(sizeof(int) * (size_t)P));
         int* flag = reinterpret_cast<int*>(take(sizeof(int)));
-        s_matrix_dev_perm(Zp, S, work, P, z0, colbuf, piv, src, flag, ctx->main->host_count, str);
+        s_matrix_dev_perm(Zp, S, work, P, z0, colbuf, piv, flag, ctx->main->host_count, str);
     }
     scans(g, 2.0 * M_PI * s, Zp, S, c, theta_dev, phi_dev, nscan, z0, static_cast<double2*>(Za_dev),
           static_cast<double2*>(Gamma_dev), Gamma_wave_dev ? static_cast<double2*>(Gamma_wave_dev) : nullptr, str);
