@@ -202,16 +202,17 @@ __global__ __launch_bounds__(ROWS * TPR) void gj_small_kernel(const double2* __r
 // Larger n: panels of NB columns.  One launch per panel: workgroup 0 brings the next
 // panel's columns up to date and factors it (thread t owns rows t, t + PT, ..., RPT
 // of them, with their panel values in registers), while the others apply the current
-// panel to kStripW columns each.  The chain of pivot steps in workgroup 0 bounds it:
+// panel to SW columns each.  The chain of pivot steps in workgroup 0 bounds it:
 // per step each wave puts its best row in LDS and one barrier later all read the
 // winner.  What workgroup 0 reads and writes is compact and column by column (column
 // pieces n rows apart would cost a cache line per value): the columns that it
 // factors are handed over by the launch before, and the factored ones are copied
 // into the matrix by the launch after.  A launch takes 11.4 us at n = 120, 17.7 at 512
-// and 30 at 1024, of which workgroup 0 needs 10.9, 16.5 and 21.3; factoring and update
-// in launches of their own took 23 and 42 us at 120 and 1024.  Strips of eight columns
-// take 19.8 us at 512 and 31.1 at 1000 (24 with four: twice the workgroups in flight).
-constexpr int kStripW = 4;
+// and 24 at 1000 and 1024, of which workgroup 0 needs 10.9, 16.5 and 21.3; factoring
+// and update in launches of their own took 23 and 42 us at 120 and 1024.  A CU holds one
+// such workgroup: strips of four columns keep all of a launch resident up to 1024
+// rows (eight take 19.8 us at 512, half the chip idle; a 257th workgroup, the next
+// panel's strips among them, 30 us at 1024), strips of eight up to 2048.
 template <int NB> struct GjPanel {
     double2* L;    // [NB][n]: multiplier of row i at step c, 0 for the step's pivot row
     double2* P;    // [NB][n]: the panel's columns before its factorisation, up to date with the panel before the last
@@ -222,7 +223,7 @@ template <int NB> struct GjPanel {
 // One launch: k0: the current panel's first column (nb0 columns, 0: none yet), k1: the
 // next one's (nb1 columns, 0: none left), after it nb2 columns of the one that the
 // launch after factors.  from_p: the next panel's columns are in nxt.P (else in A).
-template <int NB, int PT, int RPT>
+template <int NB, int PT, int RPT, int SW>
 __global__ __launch_bounds__(PT) void gj_step_kernel(double2* __restrict__ A, int n, int k0, int nb0, int k1, int nb1,
                                                      int nb2, int from_p, GjPanel<NB> cur, GjPanel<NB> nxt,
                                                      int* __restrict__ piv, int* __restrict__ used,
@@ -230,16 +231,18 @@ __global__ __launch_bounds__(PT) void gj_step_kernel(double2* __restrict__ A, in
     constexpr int NW = PT / 64;
     constexpr bool PRE = RPT <= 2;                      // the multipliers fit the registers beside the rows
     constexpr int CW = NB;                              // columns that the pivot-row wave works on
-    constexpr int SW = kStripW;                         // columns of a strip
     static_assert(NB * CW <= 64 && NB % SW == 0, "one wave works out the pivot rows; panels are whole strips");
     __shared__ double2 rks[NB][CW], rfin[NB][CW];
     __shared__ signed char prank[PT * RPT];             // which pivot of the current panel a row is, -1: none
     const int tid = threadIdx.x;
     const bool factor = blockIdx.x == 0;
     if (factor && nb1 == 0) return;
-    // the two strips of a cache line go to workgroups eight apart, which share an XCD and its L2
+    // strips in a cache line's pairs eight workgroups apart, which share an XCD and its L2;
+    // those of the next panel are left out
     const int sb = (int)blockIdx.x - 1;
-    const int j0 = factor ? k1 : ((sb & ~15) + 2 * (sb & 7) + ((sb >> 3) & 1)) * SW;
+    int strip = SW == 4 ? (sb & ~15) + 2 * (sb & 7) + ((sb >> 3) & 1) : sb;
+    if (strip >= k1 / SW) strip += (nb1 + SW - 1) / SW;
+    const int j0 = factor ? k1 : strip * SW;
     const int cw = tid % SW, js = j0 + cw;              // the strip column of this thread
     if (!factor && j0 >= n) return;
     if (!factor && j0 >= k0 && j0 < k0 + nb0) {
@@ -248,7 +251,6 @@ __global__ __launch_bounds__(PT) void gj_step_kernel(double2* __restrict__ A, in
             for (int i = tid / SW; i < n; i += PT / SW) A[(int64_t)i * n + js] = cur.F[(int64_t)(js - k0) * n + i];
         return;
     }
-    if (!factor && j0 >= k1 && j0 < k1 + nb1) return;
     // the factoring workgroup's rows are on their way while the pivot rows are worked out
     double2 rowv[RPT][NB], lown[PRE ? RPT : 1][NB];
     if (factor) {
@@ -519,7 +521,7 @@ inline unsigned g1(int64_t n) { return (unsigned)((n + 255) / 256); }
 
 // Rows up to PT * RPT.  Workspace in out (n > 64): two panels' multipliers, columns
 // and reciprocal pivots, the used-row marks.
-template <int NB, int PT, int RPT>
+template <int NB, int PT, int RPT, int SW>
 void gj_panels(double2* A, double2* out, int n, int* piv, int* flag, hipStream_t s) {
     MBT_REQUIRE(n > 64 && n <= PT * RPT, "panelled inverse: size out of range");
     GjPanel<NB> pan[2];
@@ -531,15 +533,16 @@ void gj_panels(double2* A, double2* out, int n, int* piv, int* flag, hipStream_t
         pan[h].dv = out + 6 * pn + h * NB;
     }
     int* used = reinterpret_cast<int*>(out + 6 * pn + 2 * NB);
-    const unsigned strips = (unsigned)((n + 16 * kStripW - 1) / (16 * kStripW) * 16);
-    auto step = [&](int k0, int nb0, unsigned blocks) {
+    auto step = [&](int k0, int nb0) {
         const int k1 = k0 + nb0, nb1 = std::min(NB, n - k1), nb2 = std::min(NB, n - k1 - nb1);
         const int h = nb0 ? (k0 / NB) & 1 : 1;   // the current panel's buffers
-        hipLaunchKernelGGL((gj_step_kernel<NB, PT, RPT>), dim3(blocks), dim3(PT), 0, s, A, n, k0, nb0, k1, nb1, nb2,
-                           k1 >= 2 * NB ? 1 : 0, pan[h], pan[h ^ 1], piv, used, flag);
+        const int strips = nb0 ? (n + SW - 1) / SW - (nb1 + SW - 1) / SW : 0;
+        hipLaunchKernelGGL((gj_step_kernel<NB, PT, RPT, SW>), dim3(1 + (SW == 4 ? (strips + 15) / 16 * 16 : strips)),
+                           dim3(PT), 0, s, A, n, k0, nb0, k1, nb1, nb2, k1 >= 2 * NB ? 1 : 0, pan[h], pan[h ^ 1], piv,
+                           used, flag);
     };
-    step(0, 0, 1);
-    for (int k0 = 0; k0 < n; k0 += NB) step(k0, std::min(NB, n - k0), 1 + strips);
+    step(0, 0);
+    for (int k0 = 0; k0 < n; k0 += NB) step(k0, std::min(NB, n - k0));
 }
 
 }  // namespace
@@ -558,11 +561,11 @@ void gj_on_device(double2* A, double2* out, int n, double2* colbuf, int* piv, in
     } else if (n <= 64) {
         hipLaunchKernelGGL((gj_small_kernel<64, 16, 4>), dim3(1), dim3(1024), 0, s, A, n, out, flag);
     } else if (n <= 4096) {
-        if (n <= 256) gj_panels<8, 256, 1>(A, out, n, piv, flag, s);
-        else if (n <= 512) gj_panels<8, 256, 2>(A, out, n, piv, flag, s);
-        else if (n <= 1024) gj_panels<8, 512, 2>(A, out, n, piv, flag, s);
-        else if (n <= 2048) gj_panels<8, 512, 4>(A, out, n, piv, flag, s);
-        else gj_panels<4, 1024, 4>(A, out, n, piv, flag, s);
+        if (n <= 256) gj_panels<8, 256, 1, 4>(A, out, n, piv, flag, s);
+        else if (n <= 512) gj_panels<8, 256, 2, 4>(A, out, n, piv, flag, s);
+        else if (n <= 1024) gj_panels<8, 512, 2, 4>(A, out, n, piv, flag, s);
+        else if (n <= 2048) gj_panels<8, 512, 4, 8>(A, out, n, piv, flag, s);
+        else gj_panels<4, 1024, 4, 4>(A, out, n, piv, flag, s);
         hipLaunchKernelGGL(gj_unscramble_kernel, dim3(g1((int64_t)n * n)), dim3(256), 0, s, A, out, n, piv);
     } else {
         for (int k = 0; k < n; ++k) {
