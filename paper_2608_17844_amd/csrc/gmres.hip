@@ -492,7 +492,9 @@ __device__ __forceinline__ void report_count(unsigned long long* counter, unsign
 // memory, a second kernel for the coefficients and a third for the count took
 // 24 + 8 + 5 us and the host waited for a copy before the update could start.
 constexpr int kStepR = 16;
-constexpr int kStepRows = 32;   // row threads per RHS
+constexpr int kStepRows = 32;                  // row threads per RHS
+constexpr int kStepSum = kStepRows - 64 / kStepR;   // those outside wave 0
+constexpr int kStepOwn = (kMaxVec + kStepSum - 1) / kStepSum;
 __global__ __launch_bounds__(kStepR * kStepRows) void dcgs2_step_kernel(GmresState st, double2* __restrict__ Hraw,
                                                                        const double2* __restrict__ red, int R, int k,
                                                                        int m, int coef, double* __restrict__ inv_nu,
@@ -511,21 +513,53 @@ __global__ __launch_bounds__(kStepR * kStepRows) void dcgs2_step_kernel(GmresSta
     const bool act = valid && st.active[r] != 0;
     const int64_t ldH = (int64_t)(m + 1) * R;
     double2* Hc = Hraw + (int64_t)(k > 0 ? k - 1 : 0) * ldH;
-    if (act)
+    // the scalars of the recurrence, under way with the column
+    double alpha = 0, beta0 = 0, bnorm = 0;
+    double2 gj = make_double2(0, 0);
+    int iters = 0;
+    if (ti == 0 && valid) {
+        alpha = red[(int64_t)(2 * k) * R + r].x;
+        if (k == 0) beta0 = st.beta[r];
+        else gj = st.g[(int64_t)(k - 1) * R + r];
+        bnorm = st.bnorm[r];
+        iters = st.iters[r];
+    }
+    if (valid)
         for (int i = ti; i < k; i += kStepRows) {
             const double2 s = red[(int64_t)i * R + r];
-            S[i][rr] = s;
-            Z[i][rr] = red[(int64_t)(k + i) * R + r];
+            const double2 z = red[(int64_t)(k + i) * R + r];
             const double2 h = cadd(Hc[(int64_t)i * R + r], s);
-            Hc[(int64_t)i * R + r] = h;
-            HC[i][rr] = h;
-            HJ[i][rr] = h;
             if (i < k - 1) {
                 cs[i][rr] = st.cs[(int64_t)i * R + r];
                 sn[i][rr] = st.sn[(int64_t)i * R + r];
             }
+            S[i][rr] = s;
+            Z[i][rr] = z;
+            if (act) Hc[(int64_t)i * R + r] = h;
+            HC[i][rr] = h;
+            HJ[i][rr] = h;
         }
     __syncthreads();
+    // Wave 0 runs the recurrence; the rows of t (all but its last term, which needs the
+    // recurrence's nu) are summed by the others meanwhile: row i by row thread 4 + i mod kStepSum.
+    const int own = ti - 64 / kStepR;
+    double2 t[kStepOwn], sz = make_double2(0, 0);
+    if (own >= 0 && valid && coef) {
+#pragma unroll
+        for (int e = 0; e < kStepOwn; ++e) {
+            const int i = own + e * kStepSum;
+            t[e] = make_double2(0, 0);
+            if (i > k) continue;
+            const double2* Hi = Hraw + (int64_t)i * R + r;
+#pragma unroll 8
+            for (int l = (i > 0 ? i - 1 : 0); l < k - 1; ++l)   // Hbar is upper Hessenberg: H[i][l] = 0 for l < i-1
+                t[e] = cadd(t[e], cmul(Hi[(int64_t)l * ldH], S[l][rr]));
+            if (i == k) {
+                for (int l = 0; l < k; ++l) sz = cadd(sz, cmulc(S[l][rr], Z[l][rr]));
+                sz = csub(red[(int64_t)(2 * k + 1) * R + r], sz);
+            }
+        }
+    }
     if (ti == 0) {
         double inu = 0.0;
         if (act) {
@@ -534,13 +568,12 @@ __global__ __launch_bounds__(kStepR * kStepRows) void dcgs2_step_kernel(GmresSta
                 const double2 s = S[i][rr];
                 ss += s.x * s.x + s.y * s.y;
             }
-            const double alpha = red[(int64_t)(2 * k) * R + r].x;
             // nu^2 by Pythagoras loses its relative accuracy as ss -> alpha: below
             // 1e-12 alpha the candidate lies in the span of the basis (breakdown)
             const double nu = (alpha - ss > 1e-12 * alpha) ? sqrt(alpha - ss) : 0.0;
             bool stop = false;
             if (k == 0) {
-                st.g[r] = make_double2(st.beta[r] * nu, 0.0);
+                st.g[r] = make_double2(beta0 * nu, 0.0);
             } else {
                 HC[k][rr] = make_double2(nu, 0.0);
                 Hc[(int64_t)k * R + r] = make_double2(nu, 0.0);
@@ -561,25 +594,24 @@ __global__ __launch_bounds__(kStepR * kStepRows) void dcgs2_step_kernel(GmresSta
                     c = 0.0;
                     sv = make_double2(1.0, 0.0);
                 } else {
-                    const double t = hypot(a1, nu);
-                    c = a1 / t;
-                    sv = make_double2(h1v.x / a1 * nu / t, h1v.y / a1 * nu / t);
+                    const double d = hypot(a1, nu);
+                    c = a1 / d;
+                    sv = make_double2(h1v.x / a1 * nu / d, h1v.y / a1 * nu / d);
                 }
                 st.cs[(int64_t)j * R + r] = c;
                 st.sn[(int64_t)j * R + r] = sv;
                 HJ[j][rr] = cadd(make_double2(c * h1v.x, c * h1v.y), make_double2(sv.x * nu, sv.y * nu));
                 HJ[k][rr] = make_double2(0, 0);
-                const double2 gj = st.g[(int64_t)j * R + r];
                 const double2 gn = make_double2(-(sv.x * gj.x + sv.y * gj.y), -(sv.x * gj.y - sv.y * gj.x));
                 st.g[(int64_t)j * R + r] = make_double2(c * gj.x, c * gj.y);
                 st.g[(int64_t)(j + 1) * R + r] = gn;
-                st.iters[r] += 1;
+                st.iters[r] = iters + 1;
                 st.kcyc[r] = k;
                 const double res = hypot(gn.x, gn.y);
                 if (!(nu == nu) || isinf(nu) || !(res == res)) {
                     st.flag[r] = 1;
                     stop = true;
-                } else if (res <= st.tol * st.bnorm[r] || nu == 0.0 || k == m) {
+                } else if (res <= st.tol * bnorm || nu == 0.0 || k == m) {
                     stop = true;
                 }
             }
@@ -597,33 +629,28 @@ __global__ __launch_bounds__(kStepR * kStepRows) void dcgs2_step_kernel(GmresSta
         for (int q = 0; q < kStepR; ++q) n += inus[q] != 0.0 ? 1 : 0;
         report_count(counter, n, gridDim.x, host_slot, gen);
     }
-    if (!coef || !valid) return;
+    if (!coef || !valid || own < 0) return;
     const double in = inus[rr];
-    for (int i = ti; i <= k; i += kStepRows) {
+#pragma unroll
+    for (int e = 0; e < kStepOwn; ++e) {
+        const int i = own + e * kStepSum;
+        if (i > k) continue;
         if (in == 0.0) {
             if (i < k) cs_out[(int64_t)i * R + r] = make_double2(0, 0);
             cc_out[(int64_t)i * R + r] = make_double2(0, 0);
             continue;
         }
-        double2 t = make_double2(0, 0);
-        const double2* Hi = Hraw + (int64_t)i * R + r;
-#pragma unroll 8
-        for (int l = (i > 0 ? i - 1 : 0); l < k - 1; ++l)   // Hbar is upper Hessenberg: H[i][l] = 0 for l < i-1
-            t = cadd(t, cmul(Hi[(int64_t)l * ldH], S[l][rr]));
-        if (k > 0) t = cadd(t, cmul(HC[i][rr], S[k - 1][rr]));
+        if (k > 0) t[e] = cadd(t[e], cmul(HC[i][rr], S[k - 1][rr]));
         double2 h;
         if (i < k) {
-            const double2 d = csub(Z[i][rr], t);
+            const double2 d = csub(Z[i][rr], t[e]);
             h = make_double2(d.x * in, d.y * in);
             cs_out[(int64_t)i * R + r] = S[i][rr];
         } else {
-            double2 sz = make_double2(0, 0);
-            for (int l = 0; l < k; ++l) sz = cadd(sz, cmulc(S[l][rr], Z[l][rr]));
-            const double2 q = csub(red[(int64_t)(2 * k + 1) * R + r], sz);
-            h = make_double2((q.x * in - t.x) * in, (q.y * in - t.y) * in);
+            h = make_double2((sz.x * in - t[e].x) * in, (sz.y * in - t[e].y) * in);
         }
         Hraw[(int64_t)k * ldH + (int64_t)i * R + r] = h;
-        cc_out[(int64_t)i * R + r] = make_double2(t.x * in + h.x, t.y * in + h.y);
+        cc_out[(int64_t)i * R + r] = make_double2(t[e].x * in + h.x, t[e].y * in + h.y);
     }
 }
 
