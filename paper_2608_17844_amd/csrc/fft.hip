@@ -344,7 +344,12 @@ __global__ __launch_bounds__((LdsFft<T, LX, LY, W>::NT)) void fft_fwd_lds_kernel
 }
 
 // Inverse (mirror): the two y-parities of an x-parity are summed after their
-// column transforms, so the rows are transformed once per x-parity.
+// column transforms, so the rows are transformed once per x-parity.  The first
+// x-parity's rows wait for the second's in registers, or (TWO, grids of 64x32 and
+// 32x64) in Y itself, written and read back by the same thread: at 1,024 threads a
+// thread has 128 registers, and keeping the rows there spilled 42 of them (128x64
+// grid, 40x24 lattice, 1,984 columns: 130 -> 104 us; where nothing spills the trip
+// through Y costs 10 to 20 us, 98 -> 119 at 32x32).
 template <typename T, int LX, int LY, int W>
 __global__ __launch_bounds__((LdsFft<T, LX, LY, W>::NT)) void fft_inv_lds_kernel(const cplx<T>* __restrict__ Yh,
                                                                               cplx<T>* __restrict__ Y, int nx, int ny,
@@ -363,7 +368,10 @@ __global__ __launch_bounds__((LdsFft<T, LX, LY, W>::NT)) void fft_inv_lds_kernel
     constexpr int QN = NT / W;
     // the last pass over x leaves each thread the same eight elements for both x-parities
     constexpr int RXL = RX2 > 1 ? RX2 : RX1, RYL = RY2 > 1 ? RY2 : RY1;
-    C out[8 / RXL][RXL];
+    constexpr bool TWO = LX * LY == 2048;
+    static_assert(!TWO || RX2 > 1, "rows of two register passes");
+    C out[TWO ? 1 : 8 / RXL][RXL];
+    auto yat = [&](int ix, int iy) -> C& { return Y[(int64_t)(iy * nx + ix) * B + c]; };
 #pragma unroll
     for (int be = 0; be < 2; ++be) {
         C acc[8 / RYL][RYL];
@@ -451,13 +459,19 @@ __global__ __launch_bounds__((LdsFft<T, LX, LY, W>::NT)) void fft_inv_lds_kernel
                     for (int n2 = 0; n2 < RX2; ++n2) u[n2] = tile[sy * RS + (k1 * RX2 + n2) * W + w];
                     dft<C, RX2, true>(u);
 #pragma unroll
-                    for (int k2 = 0; k2 < RX2; ++k2)
-                        out[j][k2] = be ? cadd(out[j][k2], cmul(u[k2], cconj(twx[k1 + RX1 * k2]))) : u[k2];
+                    for (int k2 = 0; k2 < RX2; ++k2) {
+                        const int ix = k1 + RX1 * k2, iy = F::yel(sy);
+                        if constexpr (TWO) {
+                            if (cv && ix < nx) yat(ix, iy) = be ? cadd(yat(ix, iy), cmul(u[k2], cconj(twx[ix]))) : u[k2];
+                        } else {
+                            out[j][k2] = be ? cadd(out[j][k2], cmul(u[k2], cconj(twx[ix]))) : u[k2];
+                        }
+                    }
                 }
             }
         }
     }
-    if (!cv) return;
+    if (!cv || TWO) return;
     if constexpr (RX2 > 1) {
 #pragma unroll
         for (int j = 0; j < 8 / RX2; ++j) {
@@ -465,7 +479,7 @@ __global__ __launch_bounds__((LdsFft<T, LX, LY, W>::NT)) void fft_inv_lds_kernel
 #pragma unroll
             for (int k2 = 0; k2 < RX2; ++k2) {
                 const int ix = k1 + RX1 * k2;
-                if (ix < nx && iy < ny) Y[(int64_t)(iy * nx + ix) * B + c] = out[j][k2];
+                if (ix < nx && iy < ny) yat(ix, iy) = out[TWO ? 0 : j][k2];
             }
         }
     } else {
@@ -474,7 +488,7 @@ __global__ __launch_bounds__((LdsFft<T, LX, LY, W>::NT)) void fft_inv_lds_kernel
             const int iy = F::yel(q0 + j * QN);
 #pragma unroll
             for (int k1 = 0; k1 < RX1; ++k1)
-                if (k1 < nx && iy < ny) Y[(int64_t)(iy * nx + k1) * B + c] = out[j][k1];
+                if (k1 < nx && iy < ny) yat(k1, iy) = out[j][k1];
         }
     }
 }
