@@ -11,21 +11,20 @@
 // closed form at each test point (coplanar potential integrals of Wilton et al.,
 // IEEE TAP 1984), the remainder (exp(-jkR) - 1)/(4 pi R) by the rule.
 //
-// One workgroup per lattice offset.  The source triangles are taken in chunks
-// of U (the chunk's moments fill at most 64 KB of LDS).  Phase 1: a thread per
+// Workgroups per lattice offset and share of its test triangles, which are
+// taken in chunks of U (the chunk's moments fill at most 64 KB of LDS).  Phase 1: a thread per
 // (test triangle t, source triangle u) integrates over the 7 x 7 point pairs
 // the six moments, taken about the test triangle's centroid c_t,
 //   m0 = <<G>>, mr = <<(r - c_t) G>> (two components), mp = <<r' G>> (two
 //   components) and mrp = <<(r - c_t) . r' G>>,
 // once per triangle pair (a triangle carries up to three RWG functions, so
 // moments per function would repeat this work about 2.6 times on the bowtie).
-// Phase 2: a thread per (test basis m, source basis q) combines, for each of q's
-// triangles in the chunk, the moments of m's two triangles (v_m and v_q the
-// free vertices, d_m = v_m - c_t):
+// Phase 2: a thread per (edge m of a triangle t of the chunk, source basis q) combines
+// the moments of t and q's two triangles (v_m and v_q the free vertices,
+// d_m = v_m - c_t):
 //   <<(r - v_m) . (r' - v_q) G>> = mrp - d_m . mp - v_q . (mr - d_m m0),
-// writing the T+ contribution of q (its lower-index triangle, always in an
-// earlier or the same chunk) and adding the T- one, in a fixed order, so the
-// block is deterministic.  The work is FP64 transcendental-bound.
+// and adds t's share of the entry to a zeroed block: two shares an entry (m's two
+// triangles), whose sum does not depend on their order, so the block is deterministic.
 // Blocks two or more lattice steps apart use the same rule on test and source
 // side, so T[-d] = T[d]^T for them (Galerkin reciprocity of the discrete
 // operator): only one of each such pair is integrated and the other is its
@@ -53,6 +52,7 @@ struct RwgDev {
     const double* area;
     const double2* tcen;   // nt: triangle centroids
     const int* btri;
+    const int* tedge;      // 3 per triangle: 2m + (0: T+ of basis m, 1: T-), -1: no basis
     const double2* bfree;
     const double2* bdel;   // 2M: free vertex minus the centroid of its triangle
     const double* blen;
@@ -61,12 +61,34 @@ struct RwgDev {
 constexpr int kPairVals = 6;                      // m0, mr (x, y), mp (x, y), mrp per triangle pair
 constexpr int kPairLdsBytes = 64 * 1024;          // LDS for one chunk of pair moments
 
-// exp(-jkR)/(4 pi R)
-__device__ __forceinline__ double2 green_full(double k, double R) {
-    double s, c;
-    sincos(k * R, &s, &c);
-    const double f = kInv4Pi / R;
-    return make_double2(c * f, -s * f);
+// sqrt(x) and its reciprocal for normal x: Goldschmidt's coupled iteration from the
+// hardware's reciprocal root, with a last residual step for each.
+__device__ __forceinline__ void sqrt_recip(double x, double& root, double& inv) {
+    const double y = __builtin_amdgcn_rsq(x);
+    double g = x * y, h = 0.5 * y;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const double r = fma(-h, g, 0.5);
+        g = fma(g, r, g);
+        h = fma(h, r, h);
+    }
+    g = fma(fma(-g, g, x), h, g);
+    const double z = h + h;
+    inv = fma(z, fma(-g, z, 1.0), z);
+    root = g;
+}
+
+// exp(-jkR)/(4 pi R), R2 = R^2 > 0, k / pi = kp + kl.  The phase is reduced in half
+// turns, exactly, and the rounding error of the product (and of kp) enters to first
+// order: its error is that of R alone.
+__device__ __forceinline__ double2 green_full(double kp, double kl, double R2) {
+    double R, inv, s, c;
+    sqrt_recip(R2, R, inv);
+    const double x = kp * R;
+    const double d = M_PI * fma(kl, R, fma(kp, R, -x));
+    sincospi(x, &s, &c);
+    const double f = kInv4Pi * inv;
+    return make_double2(fma(-s, d, c) * f, -fma(c, d, s) * f);
 }
 
 // (exp(-jkR) - 1)/(4 pi R) = -(k / 4 pi) (sin x / x)(sin x + j cos x), x = kR/2 (finite at R = 0)
@@ -121,21 +143,36 @@ __device__ void static_potentials(const double2* v, double2 rho, double& S0, dou
     }
 }
 
-__global__ __launch_bounds__(256) void rwg_fill_kernel(RwgDev d, int nt, int M, int U, int nx, int ny, double ldx,
-                                                       double ldy, double k, double2* __restrict__ T) {
-    extern __shared__ double2 pm[];   // [t][u - u0][kPairVals]
+// NEAR: the offsets at most one step away (a launch of its own: the closed forms take
+// twice the registers), else the others that are integrated.  blockIdx.y takes every
+// gridDim.y-th chunk.  FP64 arithmetic bounds it.  On a 64x64 lattice of the bowtie (96
+// functions) the far launch takes 8.3 ms; with the library's sincos, square root and
+// division, every chunk looking through all M^2 entries and both kinds of offsets in one
+// kernel of 231 registers the fill took 16.9, and 0.98 instead of 0.18 ms on 8x8, where
+// one workgroup per offset left the chip idle.
+constexpr int kFillT = 512;
+template <bool NEAR>
+__global__ __launch_bounds__(kFillT, NEAR ? 2 : 4) void rwg_fill_kernel(RwgDev d, int nt, int M, int U, int nx, int ny, double ldx,
+                                                          double ldy, double k, double kp, double kl,
+                                                          double2* __restrict__ T) {
+    extern __shared__ double2 pm[];   // [t - t0][u][kPairVals]
     const int nox = 2 * nx - 1;
-    const int off = blockIdx.x;
-    const int ox = off % nox - (nx - 1), oy = off / nox - (ny - 1);
+    // near: the offsets -1..1 of each axis that the lattice has
+    const int nnx = min(nx, 2) * 2 - 1, nny = min(ny, 2) * 2 - 1;
+    const int ox = NEAR ? (int)blockIdx.x % nnx - nnx / 2 : (int)blockIdx.x % nox - (nx - 1);
+    const int oy = NEAR ? (int)blockIdx.x / nnx - nny / 2 : (int)blockIdx.x / nox - (ny - 1);
+    const int off = (oy + ny - 1) * nox + ox + nx - 1;
     // the test element sits at lattice offset (ox, oy) from the source element at the origin
     const double sx = ox * ldx, sy = oy * ldy;
-    const bool near = ox >= -1 && ox <= 1 && oy >= -1 && oy <= 1;
-    if (!near && (oy < 0 || (oy == 0 && ox < 0))) return;   // the transpose of T[-d], filled afterwards
+    if (!NEAR) {
+        if (ox >= -1 && ox <= 1 && oy >= -1 && oy <= 1) return;
+        if (oy < 0 || (oy == 0 && ox < 0)) return;   // the transpose of T[-d], filled afterwards
+    }
     double2* Tb = T + (int64_t)off * M * M;
-    for (int u0 = 0; u0 < nt; u0 += U) {
-        const int nu = min(U, nt - u0);
+    for (int t0 = blockIdx.y * U; t0 < nt; t0 += gridDim.y * U) {
+        const int nu = min(U, nt - t0);
         for (int task = threadIdx.x; task < nt * nu; task += blockDim.x) {
-            const int t = task / nu, u = u0 + task - (task / nu) * nu;
+            const int u = task % nt, t = t0 + task / nt;
             const double2 ct = d.tcen[t];
             double2 rs[kRwgQ];
             double ws[kRwgQ];
@@ -145,7 +182,7 @@ __global__ __launch_bounds__(256) void rwg_fill_kernel(RwgDev d, int nt, int M, 
                 ws[j] = d.qw[u * kRwgQ + j];
             }
             double2 tvu[3];
-            if (near) {
+            if (NEAR) {
 #pragma unroll
                 for (int j = 0; j < 3; ++j) tvu[j] = d.tv[u * 3 + j];
             }
@@ -158,14 +195,14 @@ __global__ __launch_bounds__(256) void rwg_fill_kernel(RwgDev d, int nt, int M, 
 #pragma unroll
                 for (int j = 0; j < kRwgQ; ++j) {
                     const double dx = rox - rs[j].x, dy = roy - rs[j].y;
-                    const double R = sqrt(dx * dx + dy * dy);
-                    const double2 G = near ? green_rem(k, R) : green_full(k, R);
+                    const double R2 = dx * dx + dy * dy;
+                    const double2 G = NEAR ? green_rem(k, sqrt(R2)) : green_full(kp, kl, R2);
                     const double2 wg = make_double2(ws[j] * G.x, ws[j] * G.y);
                     g0 = cadd(g0, wg);
                     g1x = cadd(g1x, make_double2(rs[j].x * wg.x, rs[j].x * wg.y));
                     g1y = cadd(g1y, make_double2(rs[j].y * wg.x, rs[j].y * wg.y));
                 }
-                if (near) {
+                if (NEAR) {
                     double S0;
                     double2 S1;
                     static_potentials(tvu, make_double2(rox, roy), S0, S1);
@@ -182,7 +219,7 @@ __global__ __launch_bounds__(256) void rwg_fill_kernel(RwgDev d, int nt, int M, 
                 mpy = cadd(mpy, make_double2(wo * g1y.x, wo * g1y.y));
                 mrp = cadd(mrp, make_double2(wo * (ax * g1x.x + ay * g1y.x), wo * (ax * g1x.y + ay * g1y.y)));
             }
-            double2* a = pm + ((int64_t)t * U + (u - u0)) * kPairVals;
+            double2* a = pm + (int64_t)task * kPairVals;
             a[0] = m0;
             a[1] = mrx;
             a[2] = mry;
@@ -191,55 +228,62 @@ __global__ __launch_bounds__(256) void rwg_fill_kernel(RwgDev d, int nt, int M, 
             a[5] = mrp;
         }
         __syncthreads();
-        for (int e = threadIdx.x; e < M * M; e += blockDim.x) {
-            const int m = e / M, qb = e - (e / M) * M;
-            const double lmq = d.blen[m] * d.blen[qb];
+        for (int e = threadIdx.x; e < nu * 3 * M; e += blockDim.x) {
+            const int q = e % M, tl = e / M / 3;
+            const int me = d.tedge[3 * t0 + e / M];
+            if (me < 0) continue;
+            const int m = me >> 1, side = me & 1;
+            const double lmq = d.blen[m] * d.blen[q];
+            const double At = d.area[t0 + tl];
+            const double2 dm = d.bdel[me];
+            double2 sum = make_double2(0, 0);
 #pragma unroll
             for (int tau = 0; tau < 2; ++tau) {
-                const int u = d.btri[2 * qb + tau];
-                if (u < u0 || u >= u0 + nu) continue;
+                const int u = d.btri[2 * q + tau];
                 const double Au = d.area[u];
-                const double2 vq = d.bfree[2 * qb + tau];
-                double2 sum = make_double2(0, 0);
-#pragma unroll
-                for (int side = 0; side < 2; ++side) {
-                    const int t = d.btri[2 * m + side];
-                    const double At = d.area[t];
-                    const double2 dm = d.bdel[2 * m + side];
-                    const double2* a = pm + ((int64_t)t * U + (u - u0)) * kPairVals;
-                    const double2 hvx = csub(a[1], make_double2(dm.x * a[0].x, dm.x * a[0].y));
-                    const double2 hvy = csub(a[2], make_double2(dm.y * a[0].x, dm.y * a[0].y));
-                    const double2 hw = make_double2(a[5].x - (dm.x * a[3].x + dm.y * a[4].x),
-                                                    a[5].y - (dm.x * a[3].y + dm.y * a[4].y));
-                    const double2 A = make_double2(hw.x - (vq.x * hvx.x + vq.y * hvy.x),
-                                                   hw.y - (vq.x * hvx.y + vq.y * hvy.y));
-                    // j k eta A / (4 At Au) - j (eta / k) m0 / (At Au)
-                    const double cv = k * kEta / (4.0 * At * Au), cs = kEta / (k * At * Au);
-                    const double re = -(cv * A.y - cs * a[0].y);
-                    const double im = cv * A.x - cs * a[0].x;
-                    const double sg = (side == tau) ? lmq : -lmq;
-                    sum.x += sg * re;
-                    sum.y += sg * im;
-                }
-                if (tau == 0) Tb[e] = sum;
-                else Tb[e] = cadd(Tb[e], sum);
+                const double2 vq = d.bfree[2 * q + tau];
+                const double2* a = pm + ((int64_t)tl * nt + u) * kPairVals;
+                const double2 hvx = csub(a[1], make_double2(dm.x * a[0].x, dm.x * a[0].y));
+                const double2 hvy = csub(a[2], make_double2(dm.y * a[0].x, dm.y * a[0].y));
+                const double2 hw = make_double2(a[5].x - (dm.x * a[3].x + dm.y * a[4].x),
+                                                a[5].y - (dm.x * a[3].y + dm.y * a[4].y));
+                const double2 A = make_double2(hw.x - (vq.x * hvx.x + vq.y * hvy.x),
+                                               hw.y - (vq.x * hvx.y + vq.y * hvy.y));
+                // j k eta A / (4 At Au) - j (eta / k) m0 / (At Au)
+                const double cv = k * kEta / (4.0 * At * Au), cs = kEta / (k * At * Au);
+                const double re = -(cv * A.y - cs * a[0].y);
+                const double im = cv * A.x - cs * a[0].x;
+                const double sg = (side == tau) ? lmq : -lmq;
+                sum.x += sg * re;
+                sum.y += sg * im;
             }
+            atomicAdd(&Tb[(int64_t)m * M + q].x, sum.x);
+            atomicAdd(&Tb[(int64_t)m * M + q].y, sum.y);
         }
         __syncthreads();
     }
 }
 
-// T[d] = T[-d]^T for the far offsets that the fill kernel skipped (one row p per thread block)
-__global__ __launch_bounds__(128) void rwg_mirror_kernel(int M, int nx, int ny, double2* __restrict__ T) {
+// T[d] = T[-d]^T for the far offsets that the fill kernel skipped, a tile of the block per
+// workgroup through LDS (read straight down the columns it took 1.6 ms
+// at 64x64 elements, 0.45 so)
+constexpr int kMirT = 32;
+__global__ __launch_bounds__(256) void rwg_mirror_kernel(int M, int nx, int ny, double2* __restrict__ T) {
+    __shared__ double2 tile[kMirT][kMirT + 1];
     const int nox = 2 * nx - 1;
     const int off = blockIdx.x;
     const int ox = off % nox - (nx - 1), oy = off / nox - (ny - 1);
     const bool near = ox >= -1 && ox <= 1 && oy >= -1 && oy <= 1;
     if (near || !(oy < 0 || (oy == 0 && ox < 0))) return;
     const int mirror = (-oy + (ny - 1)) * nox + (-ox + (nx - 1));
-    const int p = blockIdx.y;
-    for (int q = threadIdx.x; q < M; q += blockDim.x)
-        T[((int64_t)off * M + p) * M + q] = T[((int64_t)mirror * M + q) * M + p];
+    const int nm = (M + kMirT - 1) / kMirT;
+    const int p0 = (int)blockIdx.y / nm * kMirT, q0 = (int)blockIdx.y % nm * kMirT;
+    const int tx = threadIdx.x % kMirT, ty = threadIdx.x / kMirT;
+    for (int j = ty; j < kMirT; j += 256 / kMirT)
+        if (q0 + j < M && p0 + tx < M) tile[j][tx] = T[((int64_t)mirror * M + q0 + j) * M + p0 + tx];
+    __syncthreads();
+    for (int j = ty; j < kMirT; j += 256 / kMirT)
+        if (p0 + j < M && q0 + tx < M) T[((int64_t)off * M + p0 + j) * M + q0 + tx] = tile[tx][j];
 }
 
 }  // namespace
@@ -360,9 +404,16 @@ void rwg_fill_blocks(const Geom& g, const RwgMesh& h, double k, double2* T, hipS
     const size_t b_tc = sizeof(double2) * tcen.size(), b_bt = sizeof(int) * h.btri.size();
     const size_t b_bf = sizeof(double2) * h.bfree.size(), b_bd = sizeof(double2) * bdel.size();
     const size_t b_bl = sizeof(double) * h.blen.size();
+    std::vector<int> tedge(3 * (size_t)nt, -1);
+    for (int i = 0; i < 2 * M; ++i) {
+        int* e = tedge.data() + 3 * (size_t)h.btri[i];
+        while (*e >= 0) ++e;   // a triangle has three edges, each of one basis at most
+        *e = i;
+    }
+    const size_t b_te = sizeof(int) * tedge.size();
     auto up = [](size_t b) { return (b + 255) & ~(size_t)255; };
     DBuf buf;
-    buf.alloc(up(b_qp) + up(b_qw) + up(b_tv) + up(b_ar) + up(b_tc) + up(b_bt) + up(b_bf) + up(b_bd) + up(b_bl));
+    buf.alloc(up(b_qp) + up(b_qw) + up(b_tv) + up(b_ar) + up(b_tc) + up(b_bt) + up(b_bf) + up(b_bd) + up(b_bl) + up(b_te));
     char* p = buf.as<char>();
     RwgDev d;
     auto put = [&](const void* src, size_t b) {
@@ -380,13 +431,34 @@ void rwg_fill_blocks(const Geom& g, const RwgMesh& h, double k, double2* T, hipS
     d.bfree = reinterpret_cast<const double2*>(put(h.bfree.data(), b_bf));
     d.bdel = reinterpret_cast<const double2*>(put(bdel.data(), b_bd));
     d.blen = reinterpret_cast<const double*>(put(h.blen.data(), b_bl));
-    // source triangles per chunk: the chunk's pair moments fit the LDS allowance
-    const int U = std::max(1, std::min(nt, kPairLdsBytes / (nt * kPairVals * (int)sizeof(double2))));
+    d.tedge = reinterpret_cast<const int*>(put(tedge.data(), b_te));
+    // test triangles per chunk: the chunk's pair moments fit the LDS allowance, and the passes of
+    // the workgroup over the pairs are as few as they can be
+    const int most = std::max(1, std::min(nt, kPairLdsBytes / (nt * kPairVals * (int)sizeof(double2))));
+    auto passes = [&](int u) {
+        auto of = [&](int n) { return (nt * n + kFillT - 1) / kFillT; };
+        return nt / u * of(u) + of(nt % u);
+    };
+    int U = most;
+    for (int u = most - 1; u >= 1; --u)
+        if (passes(u) < passes(U)) U = u;
+    const int nchunk = (nt + U - 1) / U;
     const size_t lds = sizeof(double2) * (size_t)nt * U * kPairVals;
-    hipLaunchKernelGGL(rwg_fill_kernel, dim3((unsigned)g.noff()), dim3(256), lds, s, d, nt, M, U, g.nx, g.ny, g.dx,
-                       g.dy, k, T);
+    const double kp = k / M_PI;
+    const double kl = (double)((long double)k / 3.14159265358979323846264338327950288L - (long double)kp);
+    // four workgroups per CU or more: fewer, and the fill waits for one workgroup's chain of points
+    const int64_t half = g.noff() / 2 + 1;
+    const int share = (int)std::min<int64_t>(nchunk, (1023 + half) / half);
+    const int near = (2 * std::min(g.nx, 2) - 1) * (2 * std::min(g.ny, 2) - 1);
+    zero_d(T, (int64_t)g.noff() * M * M, s);
+    hipLaunchKernelGGL((rwg_fill_kernel<true>), dim3((unsigned)near, (unsigned)nchunk), dim3(kFillT), lds, s, d, nt, M, U,
+                       g.nx, g.ny, g.dx, g.dy, k, kp, kl, T);
+    hipLaunchKernelGGL((rwg_fill_kernel<false>), dim3((unsigned)g.noff(), (unsigned)share), dim3(kFillT), lds, s, d, nt, M,
+                       U, g.nx, g.ny, g.dx, g.dy, k, kp, kl, T);
     MBT_LAUNCH_CHECK();
-    hipLaunchKernelGGL(rwg_mirror_kernel, dim3((unsigned)g.noff(), (unsigned)M), dim3(128), 0, s, M, g.nx, g.ny, T);
+    const int nm = (M + kMirT - 1) / kMirT;
+    hipLaunchKernelGGL(rwg_mirror_kernel, dim3((unsigned)g.noff(), (unsigned)(nm * nm)), dim3(256), 0, s, M, g.nx, g.ny,
+                       T);
     MBT_LAUNCH_CHECK();
     // the tables are freed when this returns: wait for the kernel
     MBT_HIP(hipStreamSynchronize(s));
