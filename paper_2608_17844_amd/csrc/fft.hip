@@ -614,9 +614,11 @@ __global__ __launch_bounds__((LX > LY ? LX : LY) * W) void fft_fwd_reg_kernel(co
 // column w) inverse-transforms the row and accumulates the x-parity with its
 // twiddle; only rows iy < ny and columns ix < nx are written.  NTL: the
 // spectrum is read with non-temporal loads (it is consumed once, so it need not
-// displace the lines that the next kernel reads from L2).
-template <typename T, int LX, int LY, int W, bool NTL = false>
-__global__ __launch_bounds__((LX > LY ? LX : LY) * W) void fft_inv_reg_kernel(const cplx<T>* __restrict__ Yh,
+// displace the lines that the next kernel reads from L2).  PAR = 2 gives each
+// x-parity threads and a tile of its own; the odd parity's rows join the even one's
+// through its tile.
+template <typename T, int LX, int LY, int W, bool NTL = false, int PAR = 1>
+__global__ __launch_bounds__((LX > LY ? LX : LY) * W * PAR) void fft_inv_reg_kernel(const cplx<T>* __restrict__ Yh,
                                                                               cplx<T>* __restrict__ Y, int nx, int ny,
                                                                               int64_t B, const cplx<T>* __restrict__ twx,
                                                                               const cplx<T>* __restrict__ twy) {
@@ -625,15 +627,18 @@ __global__ __launch_bounds__((LX > LY ? LX : LY) * W) void fft_inv_reg_kernel(co
     // rows of the tile are padded by one W-slot so that the rows that one
     // half-wave touches at once fall on different LDS banks
     constexpr int RS = LX * W + W;
-    __shared__ C tile[LY * RS];
-    const int w = threadIdx.x % W, r = threadIdx.x / W;
+    constexpr int NT1 = (LX > LY ? LX : LY) * W;   // threads of a parity
+    __shared__ C tiles[PAR][LY * RS];
+    const int w = threadIdx.x % W, r = (PAR == 1 ? threadIdx.x : threadIdx.x % NT1) / W;
     const int64_t c = xcd_block(blockIdx.x, gridDim.x) * W + w;
     const bool cv = c < B;
     C out[LX];
 #pragma unroll
     for (int ix = 0; ix < LX; ++ix) out[ix] = mk<T>(0, 0);
 #pragma unroll
-    for (int be = 0; be < 2; ++be) {
+    for (int be0 = 0; be0 < 2 / PAR; ++be0) {
+        const int be = PAR == 1 ? be0 : (int)threadIdx.x / NT1;
+        C* tile = tiles[PAR == 1 ? 0 : be];
         if (r < LX) {
             C acc[LY];
 #pragma unroll
@@ -666,9 +671,23 @@ __global__ __launch_bounds__((LX > LY ? LX : LY) * W) void fft_inv_reg_kernel(co
             for (int b = 0; b < LX; ++b) h[b] = tile[r * RS + b * W + w];
             fft_reg<T, LX, true>(h, twx);
 #pragma unroll
-            for (int ix = 0; ix < LX; ++ix) out[ix] = cadd(out[ix], (be && ix) ? cmul(h[ix], cconj(twx[ix])) : h[ix]);
+            for (int ix = 0; ix < LX; ++ix) {
+                if constexpr (PAR == 1) {
+                    out[ix] = cadd(out[ix], (be && ix) ? cmul(h[ix], cconj(twx[ix])) : h[ix]);
+                } else {
+                    const C v = (be && ix) ? cmul(h[ix], cconj(twx[ix])) : h[ix];
+                    if (be) tile[r * RS + ix * W + w] = v;   // a slot that this thread read
+                    else out[ix] = v;
+                }
+            }
         }
         __syncthreads();
+    }
+    if constexpr (PAR == 2) {
+        if (threadIdx.x >= NT1) return;
+        if (r < LY)
+#pragma unroll
+            for (int ix = 0; ix < LX; ++ix) out[ix] = cadd(out[ix], tiles[PAR - 1][r * RS + ix * W + w]);
     }
     if (cv && r < ny) {
 #pragma unroll
@@ -949,6 +968,14 @@ template <typename T> constexpr int tile_w(int lx, int ly) {
 // smallest grid (a whole wave), two on the largest (the tile has to fit the LDS)
 constexpr int lds_w(int lx, int ly) { return lx * ly <= 64 ? 8 : lx * ly <= 2048 ? 4 : 2; }
 
+// FP32 register transforms of fewer tiles of 16 columns than this run in tiles of four
+// (the inverse with a thread for each x-parity as well): a launch that occupies a
+// quarter of the CUs waits for what one of them can load and store.  At 6 tiles of a
+// 64x64 grid the inverse takes 18.6 instead of 29 us and the forward transform 14.6 instead
+// of 19; at 113 tiles of a 32x32 grid tiles of four are slower (11.1 against 10.5 us) and
+// lose more where other streams share the chip.
+constexpr int64_t kFewTiles = 64;
+
 template <typename T, bool FWD, int LX, int LY>
 void launch_fft_t(const Geom& g, const cplx<T>* in, cplx<T>* out, int64_t B, const cplx<T>* twx, const cplx<T>* twy,
                   cplx<T>* scratch, hipStream_t s) {
@@ -959,16 +986,21 @@ void launch_fft_t(const Geom& g, const cplx<T>* in, cplx<T>* out, int64_t B, con
         MBT_REQUIRE(scratch != nullptr, "fft: FP32 transforms on a 128-point axis need scratch");
         launch_two_pass<FWD, LX, LY, kFmtNone>(g, in, out, B, twx, twy, scratch, s);
     } else if constexpr (sizeof(T) == 4) {
-        constexpr int NT = (LX > LY ? LX : LY) * W;
-        if (FWD)
-            hipLaunchKernelGGL((fft_fwd_reg_kernel<T, LX, LY, W, kFmtNone>), dim3((unsigned)blocks), dim3(NT), 0, s, in,
-                               (void*)out, g.nx, g.ny, B, twx, twy);
-        else
-            // the inverse reads four times what it writes and reads each spectrum
-            // value once: full-width tiles with non-temporal loads measured ahead of
-            // half-width tiles (two workgroups per CU) with either kind of load
-            hipLaunchKernelGGL((fft_inv_reg_kernel<T, LX, LY, W, true>), dim3((unsigned)blocks), dim3(NT), 0, s, in, out,
-                               g.nx, g.ny, B, twx, twy);
+        auto go = [&](auto wc, auto pc) {
+            constexpr int WN = decltype(wc)::value, PAR = decltype(pc)::value, NT = (LX > LY ? LX : LY) * WN;
+            const unsigned nb = (unsigned)((B + WN - 1) / WN);
+            if (FWD)
+                hipLaunchKernelGGL((fft_fwd_reg_kernel<T, LX, LY, WN, kFmtNone>), dim3(nb), dim3(NT), 0, s, in, (void*)out,
+                                   g.nx, g.ny, B, twx, twy);
+            else
+                // the inverse reads four times what it writes and reads each spectrum
+                // value once: full-width tiles with non-temporal loads measured ahead of
+                // half-width tiles (two workgroups per CU) with either kind of load
+                hipLaunchKernelGGL((fft_inv_reg_kernel<T, LX, LY, WN, true, PAR>), dim3(nb), dim3(NT * PAR), 0, s, in, out,
+                                   g.nx, g.ny, B, twx, twy);
+        };
+        if (blocks < kFewTiles) go(std::integral_constant<int, 4>{}, std::integral_constant<int, 2>{});
+        else go(std::integral_constant<int, W>{}, std::integral_constant<int, 1>{});
     } else {
         constexpr int WL = lds_w(LX, LY);
         const dim3 lds_blocks((unsigned)((B + WL - 1) / WL)), lds_threads(LdsFft<T, LX, LY, WL>::NT);

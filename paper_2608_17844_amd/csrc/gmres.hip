@@ -487,10 +487,12 @@ __device__ __forceinline__ void report_count(unsigned long long* counter, unsign
 // c = t/nu + h; the coefficients of a RHS that stops are zero (coef = 0: no
 // update follows).  The per-RHS recurrence is a chain of O(k) dependent
 // operations, which bounds the kernel: its inputs are staged in LDS by all
-// threads, and one thread per RHS runs it from there.  At 128 RHS and up to 32
-// vectors it takes 11.8 us on average, where a thread per RHS walking global
-// memory, a second kernel for the coefficients and a third for the count took
-// 24 + 8 + 5 us and the host waited for a copy before the update could start.
+// threads with the recurrence's scalars under way beside them, and one thread per RHS
+// runs it from there while the other waves sum the coefficients' rows.  At 128 RHS and
+// up to 32 vectors it takes 9.2 us on average (11.8 with the loads where they are
+// needed and the sums at the end), where a thread per RHS walking global memory, a
+// second kernel for the coefficients and a third for the count took 24 + 8 + 5 us and
+// the host waited for a copy before the update could start.
 constexpr int kStepR = 16;
 constexpr int kStepRows = 32;                  // row threads per RHS
 constexpr int kStepSum = kStepRows - 64 / kStepR;   // those outside wave 0
@@ -693,6 +695,127 @@ void launch_dcgs2_dots_rpl(const TV* V, int64_t vs, int k, int i0, int nv, const
         launch_dcgs2_dots_cfg<TB, TV, 8, 8, RPL, HASW>(V, vs, k, i0, nv, u, w, N, R, rpc, nchunk, partial, s);
 }
 
+// The dot sweep of a short row (R <= 64 columns): a lane per column leaves most of a
+// wave idle, so here a wave takes GV = 64 / 2^lgc vectors at once (2^lgc >= R lanes
+// each), and the rows of a stage are GV times as many.  Per (vector, column) it adds
+// the rows of the chunk in order as dcgs2_dots_kernel does, so the sums are the same.
+// The rows come one group of loads after another, which bounds it.  Packed basis, up
+// to 50 vectors: 11,625 rows of 8 columns in 23 us (58 with a lane per two columns), 3,072
+// of 32 in 8.7 (13); 16 rows a group measured the same.
+constexpr int kNarW = 4;          // waves
+constexpr int kNarStage = 512;    // staged values of u and of w
+constexpr int kNarRows = 8;       // rows whose loads a lane issues together
+template <typename T> struct NarRaw { using type = Raw<T, 1>; };
+template <> struct NarRaw<p24x2> { using type = Raw<p24x2, 2>; };
+template <typename TB, typename TV, bool HASW>
+__global__ __launch_bounds__(kNarW * 64) void dcgs2_dots_narrow_kernel(const TV* __restrict__ V, int64_t vstride, int k,
+                                                                      const TB* __restrict__ u,
+                                                                      const TB* __restrict__ w, int64_t N, int R,
+                                                                      int lgc, int64_t rows_per_chunk,
+                                                                      double2* __restrict__ partial) {
+    using RV = typename NarRaw<TV>::type;
+    constexpr int NST = kNarStage / (kNarW * 64);
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int c = lane & ((1 << lgc) - 1);
+    const int j = (((int)blockIdx.y * kNarW + wave) << (6 - lgc)) + (lane >> lgc);   // this lane's vector
+    const int64_t chunk = blockIdx.x;
+    const int64_t n0 = chunk * rows_per_chunk;
+    const int64_t n1 = min(N, n0 + rows_per_chunk);
+    const int nred = 2 * k + 2;
+    const int srows = kNarStage >> lgc;   // rows of a stage
+    const bool live = c < R && j < k;
+    const bool ab_here = blockIdx.y == 0 && wave == 0 && c < R && (lane >> lgc) == 0;
+    double2 as = make_double2(0, 0), az = as, aa = as, ab = as;
+    __shared__ Raw<TB, 1> su[2][kNarStage];
+    __shared__ Raw<TB, 1> sw[HASW ? 2 : 1][HASW ? kNarStage : 1];
+    Raw<TB, 1> pu[NST], pw[HASW ? NST : 1];
+    auto fetch = [&](int64_t nb) {
+#pragma unroll
+        for (int q = 0; q < NST; ++q) {
+            const int i = threadIdx.x + q * kNarW * 64;
+            const int64_t n = nb + (i >> lgc);
+            const int col = i & ((1 << lgc) - 1);
+            if (n < n1 && col < R) {
+                pu[q].load(u + n * R + col);
+                if (HASW) pw[q].load(w + n * R + col);
+            } else {
+                pu[q].zero();
+                if (HASW) pw[q].zero();
+            }
+        }
+    };
+    RV va[kNarRows], vb[kNarRows];
+    const TV* Vj = V + (int64_t)j * vstride;
+    auto load_v = [&](int64_t n, RV(&v)[kNarRows]) {
+#pragma unroll
+        for (int q = 0; q < kNarRows; ++q) {
+            if (live && n + q < n1) v[q].load(Vj + vofs<TV>((n + q) * R + c));
+            else v[q].zero();
+        }
+    };
+    // the group of rows from n on (row rr of its stage), in cur, while the next one's loads go to nxt
+    auto group = [&](int64_t n, RV(&cur)[kNarRows], RV(&nxt)[kNarRows]) {
+        const int rr = (int)(n - n0) % srows;
+        const int buf = (int)((n - n0) / srows) & 1;
+        if (rr == 0) {
+#pragma unroll
+            for (int q = 0; q < NST; ++q) {
+                const int i = threadIdx.x + q * kNarW * 64;
+                su[buf][i] = pu[q];
+                if (HASW) sw[buf][i] = pw[q];
+            }
+            __syncthreads();
+            fetch(n + srows);
+        }
+        load_v(n + kNarRows, nxt);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int q = 0; q < kNarRows; ++q) {
+            const int i = ((rr + q) << lgc) + c;
+            const double2 vv = cur[q].get(c & 1);
+            as = cfmac(as, vv, su[buf][i].get(0));
+            if (HASW) az = cfmac(az, vv, sw[buf][i].get(0));
+        }
+        if (ab_here)
+#pragma unroll
+            for (int q = 0; q < kNarRows; ++q) {
+                const int i = ((rr + q) << lgc) + c;
+                const double2 uv = su[buf][i].get(0);
+                aa.x = nfma(aa.x, uv);
+                if (HASW) ab = cfmac(ab, uv, sw[buf][i].get(0));
+            }
+    };
+    fetch(n0);
+    load_v(n0, va);
+    for (int64_t n = n0; n < n1; n += 2 * kNarRows) {
+        group(n, va, vb);
+        if (n + kNarRows < n1) group(n + kNarRows, vb, va);
+    }
+    if (live) {
+        partial[(chunk * nred + j) * R + c] = as;
+        partial[(chunk * nred + k + j) * R + c] = az;
+    }
+    if (ab_here) {
+        partial[(chunk * nred + 2 * k) * R + c] = aa;
+        partial[(chunk * nred + 2 * k + 1) * R + c] = ab;
+    }
+}
+
+template <typename TB, typename TV, bool HASW>
+void launch_dcgs2_dots_narrow(const TV* V, int64_t vs, int k, const TB* u, const TB* w, int64_t N, int R, int64_t rpc,
+                              int nchunk, double2* partial, hipStream_t s) {
+    int lgc = 0;
+    while ((1 << lgc) < R) ++lgc;
+    // a stage has a multiple of kNarRows rows
+    MBT_REQUIRE(lgc <= 6 && (kNarStage >> lgc) % kNarRows == 0, "narrow dot sweep: row too long");
+    const int per = kNarW << (6 - lgc);   // vectors of a workgroup
+    hipLaunchKernelGGL((dcgs2_dots_narrow_kernel<TB, TV, HASW>),
+                       dim3((unsigned)nchunk, (unsigned)std::max(1, (k + per - 1) / per)), dim3(kNarW * 64), 0, s, V, vs, k,
+                       u, w, N, R, lgc, rpc, partial);
+    MBT_LAUNCH_CHECK();
+}
+
 // Row-split update sweep: each wave owns RB consecutive rows of 64 RHS columns
 // and walks all k basis vectors itself, so there is no cross-wave reduction and
 // no workgroup barrier; the per-RHS coefficients are re-read (from L2) for each
@@ -702,20 +825,22 @@ template <typename TB, int RB, int VU>
 __global__ __launch_bounds__(256) void dcgs2_update_rows_kernel(const TB* __restrict__ V, int64_t vstride, int k,
                                                                 TB* u, TB* w, const double2* __restrict__ cs_,
                                                                 const double2* __restrict__ cc_,
-                                                                const double* __restrict__ inv_nu_, int64_t N, int R,
-                                                                int Rt, const unsigned long long* __restrict__ live) {
+                                                                const double* __restrict__ inv_nu_, int64_t total,
+                                                                int R, int Rt,
+                                                                const unsigned long long* __restrict__ live) {
     if ((uint32_t)*live == 0) return;   // every RHS has stopped (the host may not know yet)
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
     const int r = blockIdx.x * 64 + lane;
     const int64_t n0 = ((int64_t)blockIdx.y * 4 + wave) * RB;
-    if (r >= R || n0 >= N) return;
+    if (r >= R || n0 * R + r >= total) return;
     // folded rows (R = F * Rt columns per row): column r is RHS r mod Rt
     const int rt = r % Rt;
     const double2* cs = cs_ + rt;
     const double2* cc = cc_ + rt;
     const double* inv_nu = inv_nu_ + rt;
-    const int nr = (int)min<int64_t>(RB, N - n0);
+    int nr = RB;   // rows that have this column (the last row may be shorter)
+    while ((n0 + nr - 1) * R + r >= total) --nr;
     double2 a[RB], c[RB];
 #pragma unroll
     for (int j = 0; j < RB; ++j) a[j] = c[j] = make_double2(0, 0);
@@ -784,20 +909,22 @@ __global__ __launch_bounds__(256) void dcgs2_update_rows24_kernel(const p24x2* _
                                                                   float2* u, const float2* __restrict__ w,
                                                                   p24x2* __restrict__ vk, const double2* __restrict__ cs_,
                                                                   const double2* __restrict__ cc_,
-                                                                  const double* __restrict__ inv_nu_, int64_t N, int R,
-                                                                  int Rt, const unsigned long long* __restrict__ live) {
+                                                                  const double* __restrict__ inv_nu_, int64_t total,
+                                                                  int R, int Rt,
+                                                                  const unsigned long long* __restrict__ live) {
     if ((uint32_t)*live == 0) return;
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
     const int r0 = 2 * (blockIdx.x * 64 + lane);
     const int64_t n0 = ((int64_t)blockIdx.y * 4 + wave) * RB;
-    if (r0 >= R || n0 >= N) return;
+    if (r0 >= R || n0 * R + r0 >= total) return;
     // folded rows (R = F * Rt columns per row, Rt even): columns r0, r0+1 are RHS r0 mod Rt and the next
     const int rt = r0 % Rt;
     const double2* cs = cs_ + rt;
     const double2* cc = cc_ + rt;
     const double* inv_nu = inv_nu_ + rt;
-    const int nr = (int)min<int64_t>(RB, N - n0);
+    int nr = RB;   // rows that have this column (the last row may be shorter)
+    while ((n0 + nr - 1) * R + r0 >= total) --nr;
     const int64_t rw = R / 2;   // packed words per row
     double2 a[RB][2], c[RB][2];
 #pragma unroll
@@ -883,16 +1010,30 @@ __global__ __launch_bounds__(256) void dcgs2_update_rows24_kernel(const p24x2* _
 // wave alone on its CU, waiting one memory latency per vector, so below kFewWaves
 // waves of eight rows it takes two rows and four vectors at a time instead.
 constexpr int64_t kFewWaves = 2048;
-inline bool few_waves(int64_t N, int64_t lanes) { return ((N + 7) / 8) * ((lanes + 63) / 64) < kFewWaves; }
+
+// These sweeps treat every column of a row alike and know a column's RHS by its place
+// mod Rt, so rows shorter than half a wave (lanes of them: a column or a packed word
+// each) are joined: `join` rows make one, the last of which may be shorter.  At 11,625
+// rows of 8 columns the packed update takes 8 instead of 33 us.
+inline int join_rows(int64_t lanes) { return lanes > 32 ? 1 : (int)(64 / lanes); }
+inline bool few_waves(int64_t N, int64_t lanes) {
+    const int join = join_rows(lanes);
+    N = (N + join - 1) / join;
+    return ((N + 7) / 8) * ((lanes * join + 63) / 64) < kFewWaves;
+}
 
 template <int RB, int VU>
 void launch_dcgs2_update24_rb(const p24x2* V, int64_t vs, int k, float2* u, const float2* w, p24x2* vk,
                               const double2* cs, const double2* cc, const double* inv_nu, int64_t N, int R, int Rt,
                               const unsigned long long* live, hipStream_t s) {
+    const int64_t total = N * R;
+    const int join = join_rows(R / 2);
+    N = (N + join - 1) / join;
+    R *= join;
     const int64_t gy = (N + 4 * RB - 1) / (4 * RB);
     MBT_REQUIRE(gy < 65536, "dcgs2 update: too many row blocks");
     hipLaunchKernelGGL((dcgs2_update_rows24_kernel<RB, VU>), dim3((unsigned)((R / 2 + 63) / 64), (unsigned)gy), dim3(256),
-                       0, s, V, vs, k, u, w, vk, cs, cc, inv_nu, N, R, Rt, live);
+                       0, s, V, vs, k, u, w, vk, cs, cc, inv_nu, total, R, Rt, live);
     MBT_LAUNCH_CHECK();
 }
 
@@ -912,14 +1053,15 @@ void launch_dcgs2_update24(const p24x2* V, int64_t vs, int k, float2* u, const f
 template <typename TV, int RPL, int RB, int VU>
 __global__ __launch_bounds__(256) void solution_update_kernel(const TV* __restrict__ V, int64_t vstride, int steps,
                                                               const double2* __restrict__ y_, double2* __restrict__ x,
-                                                              int64_t N, int R, int Rt) {
+                                                              int64_t total, int R, int Rt) {
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
     const int r0 = (blockIdx.x * 64 + lane) * RPL;
     const int64_t n0 = ((int64_t)blockIdx.y * 4 + wave) * RB;
-    if (r0 >= R || n0 >= N) return;
+    if (r0 >= R || n0 * R + r0 >= total) return;
     const double2* y = y_ + r0 % Rt;   // folded rows: column r0 is RHS r0 mod Rt
-    const int nr = (int)min<int64_t>(RB, N - n0);
+    int nr = RB;   // rows that have this column (the last row may be shorter)
+    while ((n0 + nr - 1) * R + r0 >= total) --nr;
     double2 acc[RB][RPL];
 #pragma unroll
     for (int j = 0; j < RB; ++j)
@@ -972,10 +1114,14 @@ __global__ __launch_bounds__(256) void solution_update_kernel(const TV* __restri
 template <typename TV, int RPL, int RB, int VU>
 void launch_solution_update_rb(const TV* V, int64_t vs, int steps, const double2* y, double2* x, int64_t N, int R,
                                int Rt, hipStream_t s) {
+    const int64_t total = N * R;
+    const int join = join_rows(R / RPL);
+    N = (N + join - 1) / join;
+    R *= join;
     const int64_t gy = (N + 4 * RB - 1) / (4 * RB);
     MBT_REQUIRE(gy < 65536, "solution update: too many row blocks");
     hipLaunchKernelGGL((solution_update_kernel<TV, RPL, RB, VU>), dim3((unsigned)((R / RPL + 63) / 64), (unsigned)gy),
-                       dim3(256), 0, s, V, vs, steps, y, x, N, R, Rt);
+                       dim3(256), 0, s, V, vs, steps, y, x, total, R, Rt);
     MBT_LAUNCH_CHECK();
 }
 
@@ -992,6 +1138,13 @@ void launch_solution_update(const TV* V, int64_t vs, int steps, const double2* y
 template <typename TB, typename TV>
 void launch_dcgs2_dots(const TV* V, int64_t vs, int k, const TB* u, const TB* w, int64_t N, int R, int64_t rpc,
                        int nchunk, double2* partial, hipStream_t s) {
+    // half a wave's lanes or fewer in use (a lane owns two columns where FP32 rows are even)
+    const bool pairs = sizeof(TB) == 8 && R % 2 == 0;
+    if (R <= (pairs ? 64 : 32) && (pairs || std::is_same<TV, TB>::value)) {
+        if (w) launch_dcgs2_dots_narrow<TB, TV, true>(V, vs, k, u, w, N, R, rpc, nchunk, partial, s);
+        else launch_dcgs2_dots_narrow<TB, TV, false>(V, vs, k, u, w, N, R, rpc, nchunk, partial, s);
+        return;
+    }
     if constexpr (sizeof(TB) == 8) {
         if (R % 2 == 0) {
             // FP32 pairs of RHS per lane (16-byte accesses) fit the register budget up to 32
@@ -1016,10 +1169,14 @@ template <typename TB, int RB, int VU>
 void launch_dcgs2_update_rb(const TB* V, int64_t vs, int k, TB* u, TB* w, const double2* cs, const double2* cc,
                             const double* inv_nu, int64_t N, int R, int Rt, const unsigned long long* live,
                             hipStream_t s) {
+    const int64_t total = N * R;
+    const int join = join_rows(R);
+    N = (N + join - 1) / join;
+    R *= join;
     const int64_t gy = (N + 4 * RB - 1) / (4 * RB);
     MBT_REQUIRE(gy < 65536, "dcgs2 update: too many row blocks");
     hipLaunchKernelGGL((dcgs2_update_rows_kernel<TB, RB, VU>), dim3((unsigned)((R + 63) / 64), (unsigned)gy), dim3(256), 0,
-                       s, V, vs, k, u, w, cs, cc, inv_nu, N, R, Rt, live);
+                       s, V, vs, k, u, w, cs, cc, inv_nu, total, R, Rt, live);
     MBT_LAUNCH_CHECK();
 }
 
