@@ -211,7 +211,7 @@ __global__ __launch_bounds__(ROWS * TPR) void gj_small_kernel(const double2* __r
 // and 24 at 1000 and 1024, of which workgroup 0 needs 10.9, 16.5 and 21.3; factoring
 // and update in launches of their own took 23 and 42 us at 120 and 1024.  A CU holds one
 // such workgroup: strips of four columns keep all of a launch resident up to 1024
-// rows (eight take 19.8 us at 512, half the chip idle; a 257th workgroup, the next
+// rows (eight take 19.8 us at 512 rows, half the chip idle; a 257th workgroup, the next
 // panel's strips among them, 30 us at 1024), strips of eight up to 2048.
 template <int NB> struct GjPanel {
     double2* L;    // [NB][n]: multiplier of row i at step c, 0 for the step's pivot row
@@ -251,7 +251,16 @@ __global__ __launch_bounds__(PT) void gj_step_kernel(double2* __restrict__ A, in
             for (int i = tid / SW; i < n; i += PT / SW) A[(int64_t)i * n + js] = cur.F[(int64_t)(js - k0) * n + i];
         return;
     }
-    // the factoring workgroup's rows are on their way while the pivot rows are worked out
+    // the factoring workgroup's rows, and the first of a strip's, are on their way while the pivot
+    // rows are worked out (strips: 1500 rows 18.4 -> 16.5 ms, 2304 90 -> 80, copies included)
+    constexpr int VPRE = RPT <= 2 ? RPT * SW : 4;
+    double2 vpre[VPRE];
+    if (!factor && js < n)
+#pragma unroll
+        for (int e = 0; e < VPRE; ++e) {
+            const int i = tid / SW + e * (PT / SW);
+            vpre[e] = i < n ? A[(int64_t)i * n + js] : make_double2(0, 0);
+        }
     double2 rowv[RPT][NB], lown[PRE ? RPT : 1][NB];
     if (factor) {
 #pragma unroll
@@ -308,9 +317,7 @@ __global__ __launch_bounds__(PT) void gj_step_kernel(double2* __restrict__ A, in
         double2 rk[NB];
 #pragma unroll
         for (int c = 0; c < NB; ++c) rk[c] = c < nb0 ? rks[c][cw] : make_double2(0, 0);
-#pragma unroll 4
-        for (int i = tid / SW; i < n; i += PT / SW) {
-            double2 v = A[(int64_t)i * n + js];
+        auto put = [&](int i, double2 v) {
             const int pr = prank[i];
             double2 l[NB];
 #pragma unroll
@@ -318,7 +325,13 @@ __global__ __launch_bounds__(PT) void gj_step_kernel(double2* __restrict__ A, in
 #pragma unroll
             for (int c = 0; c < NB; ++c) v = csub(v, cmul(l[c], rk[c]));
             dst[(int64_t)i * ds] = pr >= 0 ? rfin[pr][cw] : v;
-        }
+        };
+#pragma unroll
+        for (int e = 0; e < VPRE; ++e)
+            if (tid / SW + e * (PT / SW) < n) put(tid / SW + e * (PT / SW), vpre[e]);
+        if constexpr (VPRE < RPT * SW)
+#pragma unroll 4
+            for (int i = tid / SW + VPRE * (PT / SW); i < n; i += PT / SW) put(i, A[(int64_t)i * n + js]);
         return;
     }
     // the next panel: bring it up to date ...
@@ -552,8 +565,9 @@ namespace {
 // The elimination and the inverse into out, all on the device; flag receives 1 if a
 // pivot is zero or not finite.
 // Each form takes what its registers hold (64 rows x 4 columns a thread; panel rows per
-// thread: one to 256, two to 1024, four beyond, so that the factoring workgroup has no
-// more waves to gather per step than it needs).
+// thread: one to 512, two to 1024, four beyond, so that the factoring workgroup has no
+// more waves to gather per step than it needs; with the copies 512 rows take 2.98 ms at
+// two rows a thread and 2.80 at one, 1024 the same with 1,024 threads).
 void gj_on_device(double2* A, double2* out, int n, double2* colbuf, int* piv, int* flag, hipStream_t s) {
     hipLaunchKernelGGL(clear_flag_kernel, dim3(1), dim3(64), 0, s, flag);
     if (n <= 32) {
@@ -562,7 +576,7 @@ void gj_on_device(double2* A, double2* out, int n, double2* colbuf, int* piv, in
         hipLaunchKernelGGL((gj_small_kernel<64, 16, 4>), dim3(1), dim3(1024), 0, s, A, n, out, flag);
     } else if (n <= 4096) {
         if (n <= 256) gj_panels<8, 256, 1, 4>(A, out, n, piv, flag, s);
-        else if (n <= 512) gj_panels<8, 256, 2, 4>(A, out, n, piv, flag, s);
+        else if (n <= 512) gj_panels<8, 512, 1, 4>(A, out, n, piv, flag, s);
         else if (n <= 1024) gj_panels<8, 512, 2, 4>(A, out, n, piv, flag, s);
         else if (n <= 2048) gj_panels<8, 512, 4, 8>(A, out, n, piv, flag, s);
         else gj_panels<4, 1024, 4, 4>(A, out, n, piv, flag, s);
