@@ -117,15 +117,40 @@ __device__ __forceinline__ uint32_t wave_max(uint32_t key) {
     return best;
 }
 
-// Pivot keys: |v|^2 to 20 bits below its leading one, in 32 bits (positive doubles
-// order as integers: the upper half decides, below 2^-1042 the lower half does, as a
-// float); 1 for zero and NaN, above the 0 of rows out of the search.
-__device__ __forceinline__ uint32_t mag_key(double2 v) {
+// Pivot keys: |v|^2 in FP64 (positive doubles order as integers), one up; 1 for zero and
+// NaN, above the 0 of rows out of the search.
+__device__ __forceinline__ uint64_t mag_key(double2 v) {
     const double m = v.x * v.x + v.y * v.y;
-    if (!(m > 0.0)) return 1u;
-    const uint32_t hi = (uint32_t)__double2hiint(m);
-    if (hi > 0) return hi + 0x100004u;
-    return 2u + ((__float_as_uint((float)(uint32_t)__double2loint(m)) - 0x3F800000u) >> 8);
+    return m > 0.0 ? (uint64_t)__double_as_longlong(m) + 1 : 1;
+}
+// The lanes that hold the largest key of the wave.  The upper halves decide almost always;
+// the lower ones are compared when several lanes share the largest upper half.  Called by
+// all 64 lanes.
+__device__ __forceinline__ uint64_t wave_best(uint64_t key) {
+    const uint32_t hi = (uint32_t)(key >> 32);
+    const uint32_t best = wave_max(hi);
+    uint64_t at = __ballot(hi == best);
+    if (at & (at - 1)) {
+        const uint32_t lo = hi == best ? (uint32_t)key : 0u;
+        const uint32_t low = wave_max(lo);
+        at = __ballot(hi == best && lo == low);
+    }
+    return at;
+}
+// The same where lane i holds key i mod NW, NW <= 16 (every sixteen lanes hold them all): the
+// keys that are the largest.
+template <int NW> __device__ __forceinline__ uint32_t row_best(uint64_t key) {
+    static_assert(16 % NW == 0, "sixteen lanes hold whole sets of keys");
+    constexpr uint32_t set = (1u << NW) - 1;
+    const uint32_t hi = (uint32_t)(key >> 32);
+    const uint32_t best = row_max(hi);
+    uint32_t at = (uint32_t)__ballot(hi == best) & set;
+    if (at & (at - 1)) {
+        const uint32_t lo = hi == best ? (uint32_t)key : 0u;
+        const uint32_t low = row_max(lo);
+        at = (uint32_t)__ballot(hi == best && lo == low) & set;
+    }
+    return at;
 }
 __device__ __forceinline__ double2 recip(double2 d) {
     const double den = d.x * d.x + d.y * d.y;
@@ -164,9 +189,7 @@ __global__ __launch_bounds__(ROWS * TPR) void gj_small_kernel(const double2* __r
             if (tt == t) col[par][i] = a[q];
             __syncthreads();
             const double2 cv = open ? col[par][lane] : make_double2(0, 0);
-            const uint32_t key = open ? mag_key(cv) : 0u;
-            const uint32_t best = wave_max(key);
-            const int p = __ffsll((unsigned long long)__ballot(key == best)) - 1;
+            const int p = __ffsll((unsigned long long)wave_best(open ? mag_key(cv) : 0)) - 1;
             if (lane == p) open = false;
             if (i == p) {
 #pragma unroll
@@ -356,7 +379,7 @@ __global__ __launch_bounds__(PT) void gj_step_kernel(double2* __restrict__ A, in
         }
     }
     // ... and factor it
-    __shared__ uint32_t wkey[2][NW];
+    __shared__ uint64_t wkey[2][NW];
     __shared__ int wrow[2][NW];
     __shared__ double2 wval[2][NW][NB];
     const int lane = tid & 63, wave = tid >> 6;
@@ -364,20 +387,19 @@ __global__ __launch_bounds__(PT) void gj_step_kernel(double2* __restrict__ A, in
 #pragma unroll
     for (int c = 0; c < NB; ++c) {
         if (c < nb1) {
-            uint32_t key = 0;
+            uint64_t key = 0;
             int sel = 0;
 #pragma unroll
             for (int e = 0; e < RPT; ++e) {
-                const uint32_t ke = open[e] ? mag_key(rowv[e][c]) : 0u;
+                const uint64_t ke = open[e] ? mag_key(rowv[e][c]) : 0;
                 if (ke > key) {
                     key = ke;
                     sel = e;
                 }
             }
-            const uint32_t wbest = wave_max(key);
-            const int first = __ffsll((unsigned long long)__ballot(key == wbest)) - 1;
+            const int first = __ffsll((unsigned long long)wave_best(key)) - 1;
             if (lane == first) {
-                wkey[c & 1][wave] = wbest;
+                wkey[c & 1][wave] = key;
                 wrow[c & 1][wave] = tid + sel * PT;
 #pragma unroll
                 for (int e = 0; e < RPT; ++e)
@@ -386,9 +408,7 @@ __global__ __launch_bounds__(PT) void gj_step_kernel(double2* __restrict__ A, in
                         for (int q = 0; q < NB; ++q) wval[c & 1][wave][q] = rowv[e][q];
             }
             __syncthreads();
-            const uint32_t mine = wkey[c & 1][lane % NW];
-            const uint32_t best = row_max(mine);   // NW <= 16: every row of lanes holds all the waves' keys
-            const int bw = (__ffsll((unsigned long long)__ballot(mine == best)) - 1) % NW;
+            const int bw = __ffs((int)row_best<NW>(wkey[c & 1][lane % NW])) - 1;
             const int p = __builtin_amdgcn_readfirstlane(wrow[c & 1][bw]);
             const double2 d = wval[c & 1][bw][c];
             const double2 di = recip(d);

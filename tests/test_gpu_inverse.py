@@ -32,3 +32,35 @@ def test_inverse_at_the_edges_of_its_forms(ctx, n):
     A[:, n // 2] = 0.0
     with pytest.raises(mbt.MbtError):
         mbt.mbt_dbg_inverse(ctx, A)
+
+
+def _real_gauss_jordan_entries(c, swapped):
+    """Entries (0, 0) and (n-1, 0) of the inverse of the identity with c at (n-1, 0), as
+    row-wise Gauss-Jordan elimination rounds them: the pivot of column 0 is row n-1 (swapped) or
+    row 0.  Reciprocals are d / d^2; every other operation is one product."""
+    if not swapped:
+        return np.float64(1.0), -np.float64(c)
+    d = np.float64(c) / (np.float64(c) * np.float64(c))
+    e = -d / (d * d)
+    return -(d * e), e
+
+
+@pytest.mark.parametrize("n", [2, 33, 65, 300, 600, 1100, 2100])
+def test_pivot_between_nearly_equal_rows(ctx, n):
+    """Two candidates whose squares differ by less than 2^-24 of themselves: the larger one
+    is the pivot, at a lower row as at a higher one, which the rounding of the inverse shows."""
+    from paper_2608_17844_amd import mbt
+    print("n=%d" % n, flush=True)
+    rng = np.random.default_rng(7)
+    tried = {True: 0, False: 0}
+    while min(tried.values()) < 3:
+        swapped = bool(rng.integers(2))
+        c = np.float64(1.0) + (1 if swapped else -1) * rng.integers(1, 1 << 27) * 2.0 ** -52
+        want = _real_gauss_jordan_entries(c, swapped)
+        if want == _real_gauss_jordan_entries(c, not swapped):
+            continue
+        A = np.eye(n, dtype=complex)
+        A[n - 1, 0] = c
+        X = mbt.mbt_dbg_inverse(ctx, A.T).T   # columns are the rows of the elimination
+        assert (X[0, 0], X[n - 1, 0]) == want, (c, swapped)
+        tried[swapped] += 1
