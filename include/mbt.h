@@ -467,6 +467,10 @@ mbt_status mbt_dbg_solve(mbt_ctx* ctx, const mbt_array* arr, double freq_ratio, 
  * Gauss-Jordan with partial pivoting in FP64. */
 mbt_status mbt_dbg_inverse(mbt_ctx* ctx, const double* A, int32_t n, double* Ainv);
 
+/* The RWG fill's Green's function exp(-jkR)/(4 pi R) of separate elements at n
+ * squared distances R2 > 0 (host): n complex values G. */
+mbt_status mbt_dbg_green(mbt_ctx* ctx, double k, const double* R2, int64_t n, double* G);
+
 #ifdef __cplusplus
 }
 #endif

@@ -1772,4 +1772,21 @@ mbt_status mbt_dbg_inverse(mbt_ctx* ctx, const double* A, int32_t n, double* Ain
     API_END
 }
 
+mbt_status mbt_dbg_green(mbt_ctx* ctx, double k, const double* R2, int64_t n, double* G) {
+    API_BEGIN
+    MBT_REQUIRE(ctx && R2 && G && n >= 1 && n <= (1 << 30), "bad argument");
+    for (int64_t i = 0; i < n; ++i) MBT_REQUIRE(R2[i] > 0.0, "squared distances must be positive");
+    std::lock_guard<std::mutex> lk(ctx->api_mu);
+    DevScope ds(ctx->device);
+    hipStream_t str = ctx->main->stream;
+    DBuf Rd, Gd;
+    Rd.alloc(sizeof(double) * n);
+    Gd.alloc(sizeof(double2) * n);
+    MBT_HIP(hipMemcpyAsync(Rd.p, R2, sizeof(double) * n, hipMemcpyHostToDevice, str));
+    rwg_green(k, Rd.as<double>(), n, Gd.as<double2>(), str);
+    MBT_HIP(hipMemcpyAsync(G, Gd.p, sizeof(double2) * n, hipMemcpyDeviceToHost, str));
+    MBT_HIP(hipStreamSynchronize(str));
+    API_END
+}
+
 }  // extern "C"

@@ -33,4 +33,7 @@ RwgMesh rwg_from_mesh(const mbt_rwg_mesh& mesh);
 // at wavenumber k (1/wavelength units of the mesh).
 void rwg_fill_blocks(const Geom& g, const RwgMesh& mesh, double k, double2* T, hipStream_t s);
 
+// The fill's exp(-jkR)/(4 pi R) of separate elements at n squared distances (device arrays).
+void rwg_green(double k, const double* R2, int64_t n, double2* G, hipStream_t s);
+
 }  // namespace mbt

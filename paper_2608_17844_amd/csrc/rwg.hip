@@ -61,9 +61,10 @@ struct RwgDev {
 constexpr int kPairVals = 6;                      // m0, mr (x, y), mp (x, y), mrp per triangle pair
 constexpr int kPairLdsBytes = 64 * 1024;          // LDS for one chunk of pair moments
 
-// sqrt(x) and its reciprocal for normal x: Goldschmidt's coupled iteration from the
-// hardware's reciprocal root, with a last residual step for each.
-__device__ __forceinline__ void sqrt_recip(double x, double& root, double& inv) {
+// sqrt(x) = root + tail and half its reciprocal (to a few last bits) for normal x:
+// Goldschmidt's coupled iteration from the hardware's reciprocal root; the tail is the
+// residual step that would round into the root.
+__device__ __forceinline__ void sqrt_half(double x, double& root, double& tail, double& half) {
     const double y = __builtin_amdgcn_rsq(x);
     double g = x * y, h = 0.5 * y;
 #pragma unroll
@@ -72,23 +73,28 @@ __device__ __forceinline__ void sqrt_recip(double x, double& root, double& inv) 
         g = fma(g, r, g);
         h = fma(h, r, h);
     }
-    g = fma(fma(-g, g, x), h, g);
-    const double z = h + h;
-    inv = fma(z, fma(-g, z, 1.0), z);
+    tail = fma(-g, g, x) * h;
     root = g;
+    half = h;
 }
 
 // exp(-jkR)/(4 pi R), R2 = R^2 > 0, k / pi = kp + kl.  The phase is reduced in half
-// turns, exactly, and the rounding error of the product (and of kp) enters to first
-// order: its error is that of R alone.
+// turns, exactly; what R, the product kp R and kp itself leave out of it enters to first
+// order, beside the sine and cosine.  1/R is taken of R with its tail, in one rounding.
+// Three roundings reach the result (sine or cosine, 1/R, their product).  Its rms error is
+// 0.97 to 1.03e-16 at every distance; with a rounded square root, sincos(k R) and a
+// division it is 1.00e-16 below kR = 0.6, 2.0e-16 at 2 to 6 and 5.8e-15 at 60 to 200.
 __device__ __forceinline__ double2 green_full(double kp, double kl, double R2) {
-    double R, inv, s, c;
-    sqrt_recip(R2, R, inv);
+    double R, e, h, s, c;
+    sqrt_half(R2, R, e, h);
     const double x = kp * R;
-    const double d = M_PI * fma(kl, R, fma(kp, R, -x));
+    const double d = M_PI * fma(kl, R, fma(kp, e, fma(kp, R, -x)));
     sincospi(x, &s, &c);
-    const double f = kInv4Pi * inv;
-    return make_double2(fma(-s, d, c) * f, -fma(c, d, s) * f);
+    const double z = h + h;
+    double f = kInv4Pi * z;
+    f = fma(fma(-f, e, fma(-f, R, kInv4Pi)), z, f);
+    const double t = d * f;
+    return make_double2(fma(c, f, -s * t), -fma(s, f, c * t));
 }
 
 // (exp(-jkR) - 1)/(4 pi R) = -(k / 4 pi) (sin x / x)(sin x + j cos x), x = kR/2 (finite at R = 0)
@@ -146,7 +152,7 @@ __device__ void static_potentials(const double2* v, double2 rho, double& S0, dou
 // NEAR: the offsets at most one step away (a launch of its own: the closed forms take
 // twice the registers), else the others that are integrated.  blockIdx.y takes every
 // gridDim.y-th chunk.  FP64 arithmetic bounds it.  On a 64x64 lattice of the bowtie (96
-// functions) the far launch takes 8.3 ms; with the library's sincos, square root and
+// functions) the far launch takes 8.0 ms; with the library's sincos, square root and
 // division, every chunk looking through all M^2 entries and both kinds of offsets in one
 // kernel of 231 registers the fill took 16.9, and 0.98 instead of 0.18 ms on 8x8, where
 // one workgroup per offset left the chip idle.
@@ -388,6 +394,24 @@ RwgMesh rwg_from_mesh(const mbt_rwg_mesh& ms) {
     return h;
 }
 
+static void split_phase(double k, double& kp, double& kl) {
+    kp = k / M_PI;
+    kl = (double)((long double)k / 3.14159265358979323846264338327950288L - (long double)kp);
+}
+
+static __global__ void green_kernel(double kp, double kl, const double* __restrict__ R2, int64_t n,
+                                    double2* __restrict__ G) {
+    const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    if (i < n) G[i] = green_full(kp, kl, R2[i]);
+}
+
+void rwg_green(double k, const double* R2, int64_t n, double2* G, hipStream_t s) {
+    double kp, kl;
+    split_phase(k, kp, kl);
+    hipLaunchKernelGGL(green_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, kp, kl, R2, n, G);
+    MBT_LAUNCH_CHECK();
+}
+
 void rwg_fill_blocks(const Geom& g, const RwgMesh& h, double k, double2* T, hipStream_t s) {
     const int nt = h.nt, M = h.M;
     MBT_REQUIRE(M == g.M, "mesh and geometry disagree on the number of bases");
@@ -444,8 +468,8 @@ void rwg_fill_blocks(const Geom& g, const RwgMesh& h, double k, double2* T, hipS
         if (passes(u) < passes(U)) U = u;
     const int nchunk = (nt + U - 1) / U;
     const size_t lds = sizeof(double2) * (size_t)nt * U * kPairVals;
-    const double kp = k / M_PI;
-    const double kl = (double)((long double)k / 3.14159265358979323846264338327950288L - (long double)kp);
+    double kp, kl;
+    split_phase(k, kp, kl);
     // four workgroups per CU or more: fewer, and the fill waits for one workgroup's chain of points
     const int64_t half = g.noff() / 2 + 1;
     const int share = (int)std::min<int64_t>(nchunk, (1023 + half) / half);

@@ -149,6 +149,7 @@ def lib():
             "mbt_dbg_solve": (S, [_vp, _vp, ctypes.c_double, ctypes.POINTER(mbt_solve_opts), _dp, ctypes.c_int32,
                                   _dp, _ip, ctypes.POINTER(mbt_stats)]),
             "mbt_dbg_inverse": (S, [_vp, _dp, ctypes.c_int32, _dp]),
+            "mbt_dbg_green": (S, [_vp, ctypes.c_double, _dp, ctypes.c_int64, _dp]),
             "mbt_active_dev_noalloc": (S, [_vp, _vp, ctypes.c_double, _vp, ctypes.c_int32, _vp, _vp, ctypes.c_int32,
                                            ctypes.c_double, _vp, _vp, _vp, _vp]),
             "mbt_predict": (S, [_vp, ctypes.POINTER(mbt_lattice), _dp, ctypes.c_int32, ctypes.c_double,
@@ -174,7 +175,7 @@ def exported_symbols() -> list:
         "mbt_port_admittance", "mbt_port_admittance_dev", "mbt_port_impedance", "mbt_solve", "mbt_active",
         "mbt_server_create", "mbt_server_submit", "mbt_server_wait", "mbt_result_free", "mbt_server_clock",
         "mbt_server_destroy", "mbt_dbg_fill_blocks", "mbt_dbg_matvec", "mbt_dbg_precond_apply",
-        "mbt_dbg_precond_blocks", "mbt_dbg_solve", "mbt_dbg_inverse", "mbt_prof_start", "mbt_prof_read",
+        "mbt_dbg_precond_blocks", "mbt_dbg_solve", "mbt_dbg_inverse", "mbt_dbg_green", "mbt_prof_start", "mbt_prof_read",
         "mbt_predict", "mbt_predict_xi_s", "mbt_active_dev_noalloc", "mbt_array_create_margin",
         "mbt_array_create_rwg", "mbt_scan_solve",
     ]
@@ -525,6 +526,13 @@ def mbt_dbg_inverse(ctx: int, A: np.ndarray) -> np.ndarray:
     Af = np.asfortranarray(A, dtype=np.complex128)
     out = np.zeros_like(Af, order="F")
     _check(lib().mbt_dbg_inverse(ctx, _cd(Af), Af.shape[0], _cd(out)))
+    return out
+
+
+def mbt_dbg_green(ctx: int, k: float, R2: np.ndarray) -> np.ndarray:
+    R2 = np.ascontiguousarray(R2, dtype=np.float64)
+    out = np.zeros(R2.size, dtype=np.complex128)
+    _check(lib().mbt_dbg_green(ctx, k, _cd(R2), R2.size, _cd(out)))
     return out
 
 
