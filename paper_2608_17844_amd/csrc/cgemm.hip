@@ -51,7 +51,12 @@ template <typename T, int CPL> struct ColPack { cplx<T> c[CPL]; };
 // bins (RTW 4 / 2 / 1, us): FP64, 1024 columns 770 / 766 / 833, 128 columns 157 /
 // 114 / 117; FP32, 1024 columns 400 / 423 / 499, 128 columns 77 / 63 / 69; 8,192
 // bins of 64 columns: FP64 220 / 133 / 123, FP32 112 / 74 / 68.
-template <typename T, int MP, bool HERM, int CPL, int RTW>
+// AF: the fragments' loads are issued ahead of those of the first columns.
+// With a whole block of more than eight bases per wave (64 loads at 31) that is
+// the faster order (FP32, 31 bases, 1,024 columns: 408 against 418 us; 15 bases, 200:
+// 35.9 against 37.7); with fewer fragments the columns go first (FP64, 7 bases,
+// 512 columns of 16,384 bins: 374 against 384).
+template <typename T, int MP, bool HERM, int CPL, int RTW, bool AF>
 __global__ __launch_bounds__(256) void cgemm_kernel(const cplx<T>* __restrict__ A, int64_t strideA,
                                                     const cplx<T>* __restrict__ X, cplx<T>* __restrict__ Y, int M,
                                                     int R, int groups, int tpw) {
@@ -69,8 +74,13 @@ __global__ __launch_bounds__(256) void cgemm_kernel(const cplx<T>* __restrict__ 
     const int grp = blockIdx.x % groups;
     const int ntiles = (R + WT - 1) / WT;
     const int rt0 = (wave % RG) * RTW;   // this wave's first row tile
-    const int t0 = grp * tpw + wave / RG;
-    const int t1 = min((grp + 1) * tpw, ntiles);
+    // A wave's tiles are CTW apart, so the workgroup's are adjacent (FP32, 31 bases, 750 columns:
+    // 360 us against 405 with adjacent tiles per wave); for FP32 blocks of up to eight bases
+    // adjacent tiles per wave are the faster order (7 bases, 512 columns of 16,384 bins: 180 -> 173)
+    constexpr bool NEXT = RTW == NRT && !AF && sizeof(T) == 4;
+    constexpr int STEP = NEXT ? 1 : CTW;
+    const int t0 = grp * tpw + (NEXT ? wave * (tpw / CTW) : wave / RG);
+    const int t1 = min(NEXT ? t0 + tpw / CTW : (grp + 1) * tpw, ntiles);
     if (t0 >= t1) return;
 
     const C* Ab = A + b * strideA;
@@ -99,7 +109,7 @@ __global__ __launch_bounds__(256) void cgemm_kernel(const cplx<T>* __restrict__ 
             }
         }
     };
-    load(t0, bcur);
+    if constexpr (!AF) load(t0, bcur);
 
     // A fragments: lane li supplies row li of the tile; K slot q = 4s + g.
     // The accumulator of row i sits in lane group i%4, register i/4 for the
@@ -133,8 +143,9 @@ __global__ __launch_bounds__(256) void cgemm_kernel(const cplx<T>* __restrict__ 
             aim[t][s] = odd ? c.x : -c.y;
         }
     }
-    for (int tile = t0; tile < t1; tile += CTW) {
-        if (tile + CTW < t1) load(tile + CTW, bnext);
+    if constexpr (AF) load(t0, bcur);
+    for (int tile = t0; tile < t1; tile += STEP) {
+        if (tile + STEP < t1) load(tile + STEP, bnext);
         V acc[RTW][CPL];
 #pragma unroll
         for (int t = 0; t < RTW; ++t)
@@ -177,35 +188,54 @@ void launch_mp_rtw(const cplx<T>* A, int64_t strideA, const cplx<T>* X, cplx<T>*
                    int op, hipStream_t s) {
     constexpr int CTW = 4 * RTW / (MP / 8);
     const int ntiles = (R + 16 * CPL - 1) / (16 * CPL);
-    // A workgroup takes up to eight rounds of CTW tiles (four with RTW = 4, the same tiles), which amortises
-    // its fragments (16 bases: four, or two of a long row: its blocks are small), in groups of the same
-    // length: at 187 columns in FP64, 12 tiles as 8 + 4 take 119 us and as one group 95.
+    // A workgroup takes up to eight rounds of CTW tiles, which amortises its fragments, in
+    // groups of the same length: at 187 columns in FP64, 12 tiles as 8 + 4 take 119 us and as
+    // one group 95.  Whole blocks (RTW = 4) have four times the tiles in flight: groups of
+    // four or three rounds where the row fills them (31 bases, 750 columns: 351 us in two
+    // groups of three rounds, 380 in one of six; 1,024: 402 and 408), else up to eight (600
+    // columns, five rounds: 271 in one group, 319 in two).  16 bases: four, or two of a long
+    // row (its blocks are small); up to 8 bases eight (FP64, 7 bases, 512 columns of 16,384
+    // bins: 374 us in rounds of two, 327 of eight).
     const int rounds = (ntiles + CTW - 1) / CTW;
-    const int most = MP == 32 ? (RTW == 4 ? 4 : 8) : (rounds <= 4 ? 4 : 2);
+    const bool whole = rounds * CTW - ntiles <= 1;   // the last round has its tiles, or all but one
+    const int most = MP == 32 ? (RTW < 4 || !whole ? 8 : rounds % 4 == 0 ? 4 : rounds % 3 == 0 ? 3 : 8)
+                     : M <= 8 ? 8 : rounds <= 4 ? 4 : 2;
     const int groups0 = (rounds + most - 1) / most;
     const int tpw = (rounds + groups0 - 1) / groups0 * CTW;
     const int groups = (ntiles + tpw - 1) / tpw;
     const int64_t blocks = nbatch * groups;
     MBT_REQUIRE(blocks < (1LL << 31), "cgemm: grid too large");
-    if (op == 0)
-        hipLaunchKernelGGL((cgemm_kernel<T, MP, false, CPL, RTW>), dim3((unsigned)blocks), dim3(256), 0, s, A, strideA,
-                           X, Y, M, R, groups, tpw);
-    else
-        hipLaunchKernelGGL((cgemm_kernel<T, MP, true, CPL, RTW>), dim3((unsigned)blocks), dim3(256), 0, s, A, strideA, X,
-                           Y, M, R, groups, tpw);
+    auto go = [&](auto af) {
+        constexpr bool AF = decltype(af)::value;
+        if (op == 0)
+            hipLaunchKernelGGL((cgemm_kernel<T, MP, false, CPL, RTW, AF>), dim3((unsigned)blocks), dim3(256), 0, s, A,
+                               strideA, X, Y, M, R, groups, tpw);
+        else
+            hipLaunchKernelGGL((cgemm_kernel<T, MP, true, CPL, RTW, AF>), dim3((unsigned)blocks), dim3(256), 0, s, A,
+                               strideA, X, Y, M, R, groups, tpw);
+    };
+    if constexpr (RTW == MP / 8) {
+        if (M > 8) go(std::true_type{});
+        else go(std::false_type{});
+    } else {
+        go(std::false_type{});
+    }
     MBT_LAUNCH_CHECK();
 }
 
 // Row tiles per wave by the length of a row in tiles (of 16 or 32 columns): as few as
 // the row needs to occupy the waves, and FP32 blocks, which fit the registers, whole
-// from eight tiles on.
+// from eight tiles on; of single columns (odd R) they need half the registers and are
+// whole from three tiles on (31 bases, 55 columns: 45.7 us in halves, 40.8 whole; 25:
+// 27.8 in quarters, 24.6 in halves).
 template <typename T, int MP, int CPL>
 void launch_mp_cpl(const cplx<T>* A, int64_t strideA, const cplx<T>* X, cplx<T>* Y, int M, int R, int64_t nbatch,
                    int op, hipStream_t s) {
     const int ntiles = (R + 16 * CPL - 1) / (16 * CPL);
     if constexpr (MP == 32) {
-        if (ntiles <= (sizeof(T) == 8 ? 4 : 2)) launch_mp_rtw<T, MP, CPL, 1>(A, strideA, X, Y, M, R, nbatch, op, s);
-        else if (sizeof(T) == 8 || ntiles < 8) launch_mp_rtw<T, MP, CPL, 2>(A, strideA, X, Y, M, R, nbatch, op, s);
+        constexpr bool F32 = sizeof(T) == 4, ODD = F32 && CPL == 1;
+        if (!ODD && ntiles <= (F32 ? 2 : 4)) launch_mp_rtw<T, MP, CPL, 1>(A, strideA, X, Y, M, R, nbatch, op, s);
+        else if (!F32 || ntiles < (ODD ? 3 : 8)) launch_mp_rtw<T, MP, CPL, 2>(A, strideA, X, Y, M, R, nbatch, op, s);
         else if constexpr (sizeof(T) == 4) launch_mp_rtw<T, MP, CPL, 4>(A, strideA, X, Y, M, R, nbatch, op, s);
     } else {
         if (ntiles <= 2) launch_mp_rtw<T, MP, CPL, 1>(A, strideA, X, Y, M, R, nbatch, op, s);
