@@ -965,8 +965,14 @@ template <typename T> constexpr int tile_w(int lx, int ly) {
     return w > 16 ? 16 : (w < 1 ? 1 : w);
 }
 // Columns per workgroup of the LDS-exchanged transforms: four; eight on the
-// smallest grid (a whole wave), two on the largest (the tile has to fit the LDS)
-constexpr int lds_w(int lx, int ly) { return lx * ly <= 64 ? 8 : lx * ly <= 2048 ? 4 : 2; }
+// smallest grid (a whole wave), two on the largest (the tile has to fit the LDS) and in
+// the forward transform of 64x128 points, whose last pass stores eight values a thread
+// beside sixteen held ones: four columns are 1,024 threads of 128 registers, 62 of them
+// spilled (24x40 lattice, 1,984 columns 117 us, 7,936 512; two columns 89 and 331).  The
+// last pass of 128x64 points stores four at a time and spills 6 (40x24, 1,984: 76 us).
+constexpr int lds_w(bool fwd, int lx, int ly) {
+    return lx * ly <= 64 ? 8 : lx * ly <= 2048 && !(fwd && lx == 32 && ly == 64) ? 4 : 2;
+}
 
 // FP32 register transforms of fewer tiles of 16 columns than this run in tiles of four
 // (the inverse with a thread for each x-parity as well): a launch that occupies a
@@ -1002,7 +1008,7 @@ void launch_fft_t(const Geom& g, const cplx<T>* in, cplx<T>* out, int64_t B, con
         if (blocks < kFewTiles) go(std::integral_constant<int, 4>{}, std::integral_constant<int, 2>{});
         else go(std::integral_constant<int, W>{}, std::integral_constant<int, 1>{});
     } else {
-        constexpr int WL = lds_w(LX, LY);
+        constexpr int WL = lds_w(FWD, LX, LY);
         const dim3 lds_blocks((unsigned)((B + WL - 1) / WL)), lds_threads(LdsFft<T, LX, LY, WL>::NT);
         if constexpr (FWD && LX == 64 && LY == 64) {
             // two columns per workgroup either way; here the LDS-exchanged form, whose sixteen waves store
