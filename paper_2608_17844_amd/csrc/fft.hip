@@ -974,13 +974,17 @@ constexpr int lds_w(bool fwd, int lx, int ly) {
     return lx * ly <= 64 ? 8 : lx * ly <= 2048 && !(fwd && lx == 32 && ly == 64) ? 4 : 2;
 }
 
-// FP32 register transforms of fewer tiles of 16 columns than this run in tiles of four
-// (the inverse with a thread for each x-parity as well): a launch that occupies a
-// quarter of the CUs waits for what one of them can load and store.  At 6 tiles of a
-// 64x64 grid the inverse takes 18.6 instead of 29 us and the forward transform 14.6 instead
-// of 19; at 113 tiles of a 32x32 grid tiles of four are slower (11.1 against 10.5 us) and
-// lose more where other streams share the chip.
-constexpr int64_t kFewTiles = 64;
+// FP32 register transforms of few tiles of 16 columns run in tiles of four (the inverse
+// with a thread for each x-parity as well): a launch that occupies a quarter of the CUs
+// waits for what one of them can load and store.  The inverse, of fewer than 64 tiles: at 6
+// tiles of a 64x64 grid 18.6 instead of 29 us, on every grid 0.5 to 0.9 of the time up to
+// 1,000 columns; at 113 tiles of a 32x32 grid tiles of four are slower (11.1 against 10.5
+// us) and lose more where other streams share the chip.  The forward transform, of fewer
+// than 48 tiles and on x-axes of 32 points or more: at 6 tiles of a 64x64 grid 14.6 instead
+// of 19 us, at 700 columns 18 instead of 21, at 1,000 as long; on x-axes of 16 points its rows
+// leave half of a small tile's threads without a line (16x64 grid, 250 columns: 12.1
+// against 10.4 us).
+template <bool FWD, int LX> constexpr int64_t few_tiles() { return !FWD ? 64 : LX >= 16 ? 48 : 0; }
 
 template <typename T, bool FWD, int LX, int LY>
 void launch_fft_t(const Geom& g, const cplx<T>* in, cplx<T>* out, int64_t B, const cplx<T>* twx, const cplx<T>* twy,
@@ -1005,7 +1009,7 @@ void launch_fft_t(const Geom& g, const cplx<T>* in, cplx<T>* out, int64_t B, con
                 hipLaunchKernelGGL((fft_inv_reg_kernel<T, LX, LY, WN, true, PAR>), dim3(nb), dim3(NT * PAR), 0, s, in, out,
                                    g.nx, g.ny, B, twx, twy);
         };
-        if (blocks < kFewTiles) go(std::integral_constant<int, 4>{}, std::integral_constant<int, 2>{});
+        if (blocks < few_tiles<FWD, LX>()) go(std::integral_constant<int, 4>{}, std::integral_constant<int, 2>{});
         else go(std::integral_constant<int, W>{}, std::integral_constant<int, 1>{});
     } else {
         constexpr int WL = lds_w(FWD, LX, LY);
