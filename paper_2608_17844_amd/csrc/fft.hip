@@ -345,12 +345,15 @@ __global__ __launch_bounds__((LdsFft<T, LX, LY, W>::NT)) void fft_fwd_lds_kernel
 
 // Inverse (mirror): the two y-parities of an x-parity are summed after their
 // column transforms, so the rows are transformed once per x-parity.  The first
-// x-parity's rows wait for the second's in registers, or (TWO, grids of 64x32 and
-// 32x64) in Y itself, written and read back by the same thread: at 1,024 threads a
-// thread has 128 registers, and keeping the rows there spilled 42 of them (128x64
-// grid, 40x24 lattice, 1,984 columns: 130 -> 104 us; where nothing spills the trip
-// through Y costs 10 to 20 us, 98 -> 119 at 32x32).
-template <typename T, int LX, int LY, int W>
+// x-parity's rows wait for the second's in registers, or (TWO) in Y itself, written
+// and read back by the same thread: at 1,024 threads (grids of 128x64 points and more) a
+// thread has 128 registers, and keeping the rows there spills 37 to 42 of them.  The trip
+// through Y costs with the lattice's share of the grid, the spills do not: 128x64 points,
+// 1,984 columns, 40x24 elements 124 -> 101 us, 64x32 (all of it) 140 -> 129; 64x128 points, 24x40
+// 112 -> 100, 32x64 127 -> 128; 128x128 points, 3,072 columns, 52x52 elements 417 -> 414 us
+// (48x48, 3,584: 495 -> 477; 36x64, 1,000: 128 -> 121), 64x48 430 -> 438, 64x64 461 -> 475.  Where
+// nothing spills the trip costs 10 to 20 us (98 -> 119 at 64x64 points).
+template <typename T, int LX, int LY, int W, bool TWO>
 __global__ __launch_bounds__((LdsFft<T, LX, LY, W>::NT)) void fft_inv_lds_kernel(const cplx<T>* __restrict__ Yh,
                                                                               cplx<T>* __restrict__ Y, int nx, int ny,
                                                                               int64_t B, const cplx<T>* __restrict__ twx,
@@ -368,7 +371,6 @@ __global__ __launch_bounds__((LdsFft<T, LX, LY, W>::NT)) void fft_inv_lds_kernel
     constexpr int QN = NT / W;
     // the last pass over x leaves each thread the same eight elements for both x-parities
     constexpr int RXL = RX2 > 1 ? RX2 : RX1, RYL = RY2 > 1 ? RY2 : RY1;
-    constexpr bool TWO = LX * LY == 2048;
     static_assert(!TWO || RX2 > 1, "rows of two register passes");
     C out[TWO ? 1 : 8 / RXL][RXL];
     auto yat = [&](int ix, int iy) -> C& { return Y[(int64_t)(iy * nx + ix) * B + c]; };
@@ -1026,8 +1028,19 @@ void launch_fft_t(const Geom& g, const cplx<T>* in, cplx<T>* out, int64_t B, con
             // against transforming each parity grid in place: 545 -> 461 us on the 128x128 grid (3,072
             // columns), 152 -> 127 on 128x64 (1,984); against the register transform, half of whose threads
             // have no line in one of the passes where the axes differ: 47 -> 42 us on 64x32 (5,797)
-            hipLaunchKernelGGL((fft_inv_lds_kernel<T, LX, LY, WL>), lds_blocks, lds_threads, 0, s, in, out, g.nx, g.ny, B,
-                               twx, twy);
+            auto go = [&](auto tc) {
+                hipLaunchKernelGGL((fft_inv_lds_kernel<T, LX, LY, WL, decltype(tc)::value>), lds_blocks, lds_threads, 0, s,
+                                   in, out, g.nx, g.ny, B, twx, twy);
+            };
+            // the kernels that spill take the trip through Y, on the largest grid up to two thirds of it
+            if constexpr (LX * LY == 2048) {
+                go(std::true_type{});
+            } else if constexpr (LX * LY == 4096) {
+                if (3 * g.nx * g.ny <= 2 * LX * LY) go(std::true_type{});
+                else go(std::false_type{});
+            } else {
+                go(std::false_type{});
+            }
         } else {
             // the register transform with fewer columns per workgroup (a row of 32 values fills 128
             // registers), two workgroups per CU: it reads most of its bytes and needs no exchange between

@@ -40,3 +40,21 @@ def test_operator_on_grid(ctx, lx, ly):
                     assert np.all(np.abs(y - ref) <= c * u * mag), (R, op, prec)
     finally:
         mbt.mbt_array_destroy(a)
+
+
+@pytest.mark.parametrize("nx,ny", [(64, 64), (53, 52), (52, 52), (64, 32), (32, 64)])
+def test_operator_by_share_of_the_grid(ctx, nx, ny):
+    """The largest grids filled to both sides of the share at which the FP64 inverse
+    transform changes the place where its first x-parity waits, and filled whole."""
+    from paper_2608_17844_amd import mbt
+    lat, dip = W.Lattice(nx, ny, 0.5, 0.5), W.Dipole(0.5, 0.005, 1)
+    print("lattice", nx, ny, flush=True)
+    a = mbt.mbt_array_create_dipole(ctx, dip, lat)
+    try:
+        Z = mom.fill_dense(lat, dip, 1.0)
+        x = W.random_vectors(Z.shape[0], 3, seed=4)
+        c = 16 * (np.log2(4 * 64 * 64) + 1)
+        y = mbt.mbt_dbg_matvec(ctx, a, 1.0, x)
+        assert np.all(np.abs(y - Z @ x) <= c * 2.0 ** -53 * (np.abs(Z) @ np.abs(x)))
+    finally:
+        mbt.mbt_array_destroy(a)
