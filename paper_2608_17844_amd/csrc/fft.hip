@@ -87,77 +87,61 @@ template <> struct Split<16> { static constexpr int R1 = 4, R2 = 4; };
 template <> struct Split<32> { static constexpr int R1 = 8, R2 = 4; };
 template <> struct Split<64> { static constexpr int R1 = 8, R2 = 8; };
 
-// In-LDS FFTs of length L along one axis of a tile.  FFT f = (o, w) has its
+// In-LDS forward FFTs of length L along one axis of a tile.  FFT f = (o, w) has its
 // element i at tile[o*ostride + i*stride + w], o < nouter, w < W.
 // Four-step: L = R1*R2, n = n1*R2 + n2, k = k1 + R1*k2;
 //   pass 1: for each n2, DFT_R1 over n1, times W_L^{n2 k1}, stored in place;
 //   pass 2: for each k1, DFT_R2 over n2, stored at k1 + R1*k2.
 // tw is the twiddle table of the full grid P = 2L: W_L^m = tw[2m].
 // OUTER_FAST orders work items so that neighbouring lanes step the smaller stride.
-template <typename T, int L, bool INV, bool OUTER_FAST, int NT, int nouter, int ostride, int stride, int W>
+template <typename T, int L, bool OUTER_FAST, int NT, int nouter, int ostride, int stride, int W>
 __device__ __forceinline__ void lds_fft_axis(cplx<T>* tile, const cplx<T>* __restrict__ tw) {
     using C = cplx<T>;
     constexpr int R1 = Split<L>::R1, R2 = Split<L>::R2;
+    static_assert(R2 > 1, "two register passes");
     const int tid = threadIdx.x;
-    if constexpr (R2 == 1) {
-        const int items = nouter * W;
-        for (int it = tid; it < items; it += NT) {
-            const int w = it % W, o = it / W;
+    const int items1 = nouter * W * R2;
+    for (int it = tid; it < items1; it += NT) {
+        int w = it % W, rest = it / W, o, n2;
+        if (OUTER_FAST) { o = rest % nouter; n2 = rest / nouter; }
+        else { n2 = rest % R2; o = rest / R2; }
+        C* base = tile + o * ostride + w;
+        C v[R1];
+#pragma unroll
+        for (int n1 = 0; n1 < R1; ++n1) v[n1] = base[(n1 * R2 + n2) * stride];
+        dft<C, R1, false>(v);
+#pragma unroll
+        for (int k1 = 0; k1 < R1; ++k1)
+            base[(k1 * R2 + n2) * stride] = (k1 == 0 || n2 == 0) ? v[k1] : cmul(v[k1], tw[(2 * n2 * k1) % (2 * L)]);
+    }
+    __syncthreads();
+    const int items2 = nouter * W * R1;
+    constexpr int MAXIT = (nouter * W * R1 + NT - 1) / NT;
+    C reg[MAXIT][R2];
+#pragma unroll
+    for (int i = 0; i < MAXIT; ++i) {
+        const int it = tid + i * NT;
+        if (it < items2) {
+            int w = it % W, rest = it / W, o, k1;
+            if (OUTER_FAST) { o = rest % nouter; k1 = rest / nouter; }
+            else { k1 = rest % R1; o = rest / R1; }
+            const C* base = tile + o * ostride + w;
+#pragma unroll
+            for (int n2 = 0; n2 < R2; ++n2) reg[i][n2] = base[(k1 * R2 + n2) * stride];
+            dft<C, R2, false>(reg[i]);
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < MAXIT; ++i) {
+        const int it = tid + i * NT;
+        if (it < items2) {
+            int w = it % W, rest = it / W, o, k1;
+            if (OUTER_FAST) { o = rest % nouter; k1 = rest / nouter; }
+            else { k1 = rest % R1; o = rest / R1; }
             C* base = tile + o * ostride + w;
-            C v[R1];
 #pragma unroll
-            for (int n = 0; n < R1; ++n) v[n] = base[n * stride];
-            dft<C, R1, INV>(v);
-#pragma unroll
-            for (int n = 0; n < R1; ++n) base[n * stride] = v[n];
-        }
-    } else {
-        const int items1 = nouter * W * R2;
-        for (int it = tid; it < items1; it += NT) {
-            int w = it % W, rest = it / W, o, n2;
-            if (OUTER_FAST) { o = rest % nouter; n2 = rest / nouter; }
-            else { n2 = rest % R2; o = rest / R2; }
-            C* base = tile + o * ostride + w;
-            C v[R1];
-#pragma unroll
-            for (int n1 = 0; n1 < R1; ++n1) v[n1] = base[(n1 * R2 + n2) * stride];
-            dft<C, R1, INV>(v);
-#pragma unroll
-            for (int k1 = 0; k1 < R1; ++k1) {
-                C t = tw[(2 * n2 * k1) % (2 * L)];
-                if (INV) t.y = -t.y;
-                base[(k1 * R2 + n2) * stride] = (k1 == 0 || n2 == 0) ? v[k1] : cmul(v[k1], t);
-            }
-        }
-        __syncthreads();
-        const int items2 = nouter * W * R1;
-        constexpr int MAXIT = (nouter * W * R1 + NT - 1) / NT;
-        C reg[MAXIT][R2];
-#pragma unroll
-        for (int i = 0; i < MAXIT; ++i) {
-            const int it = tid + i * NT;
-            if (it < items2) {
-                int w = it % W, rest = it / W, o, k1;
-                if (OUTER_FAST) { o = rest % nouter; k1 = rest / nouter; }
-                else { k1 = rest % R1; o = rest / R1; }
-                const C* base = tile + o * ostride + w;
-#pragma unroll
-                for (int n2 = 0; n2 < R2; ++n2) reg[i][n2] = base[(k1 * R2 + n2) * stride];
-                dft<C, R2, INV>(reg[i]);
-            }
-        }
-        __syncthreads();
-#pragma unroll
-        for (int i = 0; i < MAXIT; ++i) {
-            const int it = tid + i * NT;
-            if (it < items2) {
-                int w = it % W, rest = it / W, o, k1;
-                if (OUTER_FAST) { o = rest % nouter; k1 = rest / nouter; }
-                else { k1 = rest % R1; o = rest / R1; }
-                C* base = tile + o * ostride + w;
-#pragma unroll
-                for (int k2 = 0; k2 < R2; ++k2) base[(k1 + R1 * k2) * stride] = reg[i][k2];
-            }
+            for (int k2 = 0; k2 < R2; ++k2) base[(k1 + R1 * k2) * stride] = reg[i][k2];
         }
     }
 }
@@ -198,9 +182,9 @@ __global__ __launch_bounds__(kNT) void fft_fwd_pad_kernel(const cplx<T>* __restr
             }
         }
         __syncthreads();
-        lds_fft_axis<T, LX, false, false, kNT, LY, LX * W, W, W>(tile, twx);
+        lds_fft_axis<T, LX, false, kNT, LY, LX * W, W, W>(tile, twx);
         __syncthreads();
-        lds_fft_axis<T, LY, false, true, kNT, LX, W, LX * W, W>(tile, twy);
+        lds_fft_axis<T, LY, true, kNT, LX, W, LX * W, W>(tile, twy);
         __syncthreads();
         for (int t = threadIdx.x; t < NTILE; t += kNT) {
             const int w = t % W, b = (t / W) % LX, a = t / (W * LX);
@@ -960,8 +944,8 @@ void launch_embed_axis(int P, const double2* in, double2* out, int n, int64_t nl
 // columns per workgroup of the FP64 register transforms
 constexpr int kRegW64 = 4;
 
-// Columns per workgroup of the FP32 register transforms: 16 (128 contiguous bytes
-// per lattice point)
+// Columns per workgroup of the FP32 register transforms, 16 (128 contiguous bytes per
+// lattice point), and of the FP64 forward transform of 128x128 points, 2 (a 128 KB tile)
 template <typename T> constexpr int tile_w(int lx, int ly) {
     int w = (int)(131072 / (lx * ly * (int)sizeof(cplx<T>)));
     return w > 16 ? 16 : (w < 1 ? 1 : w);
