@@ -1793,43 +1793,65 @@ GmresResult gmres_batched(const std::function<void(const TB*, TB*)>& apply, cons
 // on.
 namespace {
 
-constexpr int kDotWaves = 8;
+constexpr int kDotSums = 8;
 // MODE 0: sum conj(a) b; 1: sum a b; 2: sum a b and sum |a|^2.  Partials
-// [chunk][v][r]; a chunk's rows are dealt to the workgroup's waves (row n0 + j to
-// wave j mod kDotWaves) and the waves' sums added in order.  One wave per chunk
-// walking its rows one by one takes 61 us for 29,760 rows of 64 RHS in FP64 (31 MB
-// per vector).
-template <typename TB, int MODE>
-__global__ __launch_bounds__(64 * kDotWaves) void krylov_dot_kernel(const TB* __restrict__ a, const TB* __restrict__ b,
-                                                                    int64_t N, int R, int64_t rows_per_chunk,
-                                                                    double2* __restrict__ partial) {
-    __shared__ double2 gs[kDotWaves][64];
-    __shared__ double gn[MODE == 2 ? kDotWaves : 1][64];
+// [chunk][v][r]; a chunk's rows are dealt to kDotSums running sums (row n0 + j to sum
+// j mod kDotSums), which are added in order.  NW waves hold kDotSums / NW of them each.
+// One wave per chunk that walks its rows one by one takes 61 us for 29,760 rows of 64 RHS
+// in FP64 (31 MB per vector).
+template <typename TB, int MODE, int NW>
+__global__ __launch_bounds__(64 * NW) void krylov_dot_kernel(const TB* __restrict__ a, const TB* __restrict__ b,
+                                                             int64_t N, int R, int64_t rows_per_chunk,
+                                                             double2* __restrict__ partial) {
+    static_assert(NW == 1 || NW == kDotSums, "a wave has all sums or one");
+    constexpr int S = kDotSums / NW;
+    __shared__ double2 gs[NW][64];
+    __shared__ double gn[MODE == 2 ? NW : 1][64];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int r = blockIdx.x * 64 + lane;
     const int64_t chunk = blockIdx.y;
     const int64_t n0 = chunk * rows_per_chunk, n1 = min(N, n0 + rows_per_chunk);
-    double2 ab = make_double2(0, 0);
-    double aa = 0.0;
+    double2 ab[S];
+    double aa[S];
+#pragma unroll
+    for (int q = 0; q < S; ++q) {
+        ab[q] = make_double2(0, 0);
+        aa[q] = 0.0;
+    }
+    auto add = [&](int q, int64_t n) {
+        const double2 av = ld2(a + n * R + r), bv = ld2(b + n * R + r);
+        ab[q] = MODE == 0 ? cfmac(ab[q], av, bv) : cfma(ab[q], av, bv);
+        if (MODE == 2) aa[q] = nfma(aa[q], av);
+    };
     if (r < R) {
+        if constexpr (S == 1) {
 #pragma unroll 4
-        for (int64_t n = n0 + wave; n < n1; n += kDotWaves) {
-            const double2 av = ld2(a + n * R + r), bv = ld2(b + n * R + r);
-            ab = MODE == 0 ? cfmac(ab, av, bv) : cfma(ab, av, bv);
-            if (MODE == 2) aa = nfma(aa, av);
+            for (int64_t n = n0 + wave; n < n1; n += kDotSums) add(0, n);
+        } else {
+            int64_t n = n0;
+            for (; n + S <= n1; n += S)
+#pragma unroll
+                for (int q = 0; q < S; ++q) add(q, n + q);
+#pragma unroll
+            for (int q = 0; q < S; ++q)
+                if (n + q < n1) add(q, n + q);
         }
     }
-    gs[wave][lane] = ab;
-    if (MODE == 2) gn[wave][lane] = aa;
-    __syncthreads();
-    if (wave != 0 || r >= R) return;
-    for (int q = 1; q < kDotWaves; ++q) {
-        ab = cadd(ab, gs[q][lane]);
-        if (MODE == 2) aa += gn[q][lane];
+    if constexpr (S == 1) {
+        gs[wave][lane] = ab[0];
+        if (MODE == 2) gn[wave][lane] = aa[0];
+        __syncthreads();
+        if (wave != 0) return;
+    }
+    if (r >= R) return;
+#pragma unroll
+    for (int q = 1; q < kDotSums; ++q) {
+        ab[0] = cadd(ab[0], S == 1 ? gs[q % NW][lane] : ab[q % S]);
+        if (MODE == 2) aa[0] += S == 1 ? gn[q % NW][lane] : aa[q % S];
     }
     constexpr int nv = MODE == 2 ? 2 : 1;
-    partial[chunk * nv * R + r] = ab;
-    if (MODE == 2) partial[(chunk * nv + 1) * R + r] = make_double2(aa, 0.0);
+    partial[chunk * nv * R + r] = ab[0];
+    if (MODE == 2) partial[(chunk * nv + 1) * R + r] = make_double2(aa[0], 0.0);
 }
 
 // The chunk partials of NV dots added per RHS (in the order of
@@ -1875,8 +1897,17 @@ void krylov_dot(const TB* a, const TB* b, int64_t N, int R, double2* partial, co
                 unsigned long long* host_slot, uint32_t gen, hipStream_t s) {
     const int64_t rpc = gmres_rows_per_chunk(N);
     const int nchunk = gmres_nchunk(N);
-    hipLaunchKernelGGL((krylov_dot_kernel<TB, MODE>), dim3((R + 63) / 64, nchunk), dim3(64 * kDotWaves), 0, s, a, b, N, R,
-                       rpc, partial);
+    const dim3 grid((R + 63) / 64, nchunk);
+    // A wave for each running sum; from 3,072 workgroups on one wave for all eight, which then keeps the
+    // chip as busy with fewer of them waiting for each other (31,744 rows of 1,024 RHS in FP64, 3,968
+    // workgroups: 184 against 195 us, of two products 208 against 212; 512 RHS: 102 against 94,
+    // 64 RHS 46 against 12).  FP32 moves half the bytes, and its single products stay with a wave each
+    // (1,024 RHS: 118 against 110 us; of two products 120 against 124).
+    if ((int64_t)grid.x * nchunk >= 3072 && (sizeof(TB) == 16 || MODE == 2))
+        hipLaunchKernelGGL((krylov_dot_kernel<TB, MODE, 1>), grid, dim3(64), 0, s, a, b, N, R, rpc, partial);
+    else
+        hipLaunchKernelGGL((krylov_dot_kernel<TB, MODE, kDotSums>), grid, dim3(64 * kDotSums), 0, s, a, b, N, R, rpc,
+                           partial);
     hipLaunchKernelGGL((krylov_scalar_kernel<MODE == 2 ? 2 : 1, COUNT, Op>), dim3((R + kRedOut - 1) / kRedOut),
                        dim3(64 * kRedWaves), 0, s, partial, nchunk, R, op, counter, host_slot, gen);
     MBT_LAUNCH_CHECK();

@@ -42,3 +42,29 @@ def test_narrow_batches_have_the_bits_of_a_wide_one(ctx, nx, ny, M, prec):
             assert np.array_equal(I, ref[:, :R]) and np.array_equal(it, iters[:R])
     finally:
         mbt.mbt_array_destroy(arr)
+
+
+@pytest.mark.parametrize("solver,prec", [("cocg", "f64"), ("cocg", "mixed"), ("pcg", "f64")])
+def test_short_recurrences_keep_their_bits_in_wide_batches(ctx, solver, prec):
+    """The dots of COCG and PCG change from a wave per running sum to one wave for all at
+    3,072 workgroups (here 64 chunks of 16 rows, the last of 15, by 48 groups of 64 columns):
+    a RHS has the same bits and step count in a batch on either side and nearly alone."""
+    from paper_2608_17844_amd import mbt
+    lat, dip = W.Lattice(11, 31, 0.5, 0.5), W.Dipole(0.5, 0.005, 3)
+    V = W.random_vectors(1023, 3072, seed=9)
+    pc = mbt.MBT_PC_NORMAL_EQ if solver == "pcg" else mbt.MBT_PC_ELEMENT_BLOCK
+    flags = mbt.MBT_FLAG_PCG if solver == "pcg" else mbt.MBT_FLAG_COCG
+    if prec == "f64":
+        opts = mbt.mbt_default_opts(prec=mbt.MBT_FP64, pc=pc, tol=1e-6, flags=flags)
+    else:
+        opts = mbt.mbt_default_opts(prec=mbt.MBT_FP32, pc=pc, inner_tol=1e-3, refine_tol=1e-6, refine_max=6,
+                                    flags=flags)
+    arr = mbt.mbt_array_create_dipole(ctx, dip, lat)
+    try:
+        print(solver, prec, flush=True)
+        few, n_few, _ = mbt.mbt_dbg_solve(ctx, arr, 0.93, opts, V[:, :5])
+        for R in (3072, 3008):
+            I, n, _ = mbt.mbt_dbg_solve(ctx, arr, 0.93, opts, V[:, :R])
+            assert np.array_equal(I[:, :5], few) and np.array_equal(n[:5], n_few), R
+    finally:
+        mbt.mbt_array_destroy(arr)
