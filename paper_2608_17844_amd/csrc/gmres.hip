@@ -1008,8 +1008,11 @@ __global__ __launch_bounds__(256) void dcgs2_update_rows24_kernel(const p24x2* _
 // Rows per wave of the row-split sweeps.  Eight rows amortise the coefficients
 // over the basis traffic once the waves fill the chip; a short batch leaves each
 // wave alone on its CU, waiting one memory latency per vector, so below kFewWaves
-// waves of eight rows it takes two rows and four vectors at a time instead.
-constexpr int64_t kFewWaves = 2048;
+// waves of eight rows it takes two rows and four vectors at a time instead.  Update
+// sweep, two rows against eight: packed basis 992 waves 23 against 25 us, 1,052 26
+// against 48, 1,841 42 against 32, 1,984 49 against 38; FP64 526 24 against 26, 951 30 against
+// 32, 1,274 52 against 52, 1,841 74 against 67, 1,984 73 against 70.
+constexpr int64_t kFewWaves = 1280;
 
 // These sweeps treat every column of a row alike and know a column's RHS by its place
 // mod Rt, so rows shorter than half a wave (lanes of them: a column or a packed word
