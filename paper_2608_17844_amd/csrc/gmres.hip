@@ -656,13 +656,16 @@ __global__ __launch_bounds__(kStepR * kStepRows) void dcgs2_step_kernel(GmresSta
     }
 }
 
-// Workgroups of a sweep below which its vectors spread over several workgroups of
-// eight (each stages u and w again, from cache): with fewer than 1.5 workgroups
-// per CU the sweep waits for its loads rather than for memory bandwidth.  At 7,936
-// folded rows of 128 RHS (248 workgroups) a sweep over 5-31 vectors takes 120
-// instead of 125 us on average, at 5,797 rows of 187 RHS in FP64 (273) 110
-// instead of 119; with four times the workgroups the extra reads of u and w win.
-constexpr int kDotFewGroups = 384;
+// Whether a sweep of `groups` workgroups spreads its vectors over several workgroups of
+// eight (each stages u and w again, from cache).  It does where whole ones leave CUs idle or
+// leave a few CUs with two: there a sweep waits for its loads rather than for memory
+// bandwidth.  Packed basis, split against whole: 124 workgroups 59 against 92 us, 248 114
+// against 117, 320 31 against 36, 343 20 against 19.  FP64: 124 94 against 107, 273 98
+// against 114; but one workgroup a CU is as fast whole there (132: 23 against 22.5) or faster
+// (240: 33 against 31; 248: 179 against 162).
+template <typename TB> bool dots_split(int64_t groups) {
+    return groups <= 330 && !(sizeof(TB) == 16 && groups > 192 && groups <= 256);
+}
 
 // rows whose loads a wave of G vectors issues together: eight loads in flight, or as many as
 // fit beside the accumulators (two RHS per lane) without spilling
@@ -685,7 +688,7 @@ void launch_dcgs2_dots_rpl(const TV* V, int64_t vs, int k, int i0, int nv, const
     const int64_t groups = (int64_t)((R / RPL + 63) / 64) * nchunk;
     if (nv <= 4)
         launch_dcgs2_dots_cfg<TB, TV, 4, 1, RPL, HASW>(V, vs, k, i0, nv, u, w, N, R, rpc, nchunk, partial, s);
-    else if (nv <= 8 || groups <= kDotFewGroups)
+    else if (nv <= 8 || dots_split<TB>(groups))
         launch_dcgs2_dots_cfg<TB, TV, 8, 1, RPL, HASW>(V, vs, k, i0, nv, u, w, N, R, rpc, nchunk, partial, s);
     else if (nv <= 16)
         launch_dcgs2_dots_cfg<TB, TV, 8, 2, RPL, HASW>(V, vs, k, i0, nv, u, w, N, R, rpc, nchunk, partial, s);
@@ -1548,9 +1551,18 @@ inline unsigned ew_grid(int64_t n) {
 // chunk's rows one after the other, so on a small system the chunk length is the
 // length of the sweep: the 32-vector sweep of a 12x10 lattice of 15 bases (450
 // folded rows, 120 RHS) takes 98 us in chunks of 128 rows and 10.6 us in chunks
-// of 16.  Long systems have enough chunks; their partial sums are written and
-// read once per sweep (at 7,936 folded rows of 1024 RHS, 64-row chunks cost the
-// whole solve 3 % against 128), so the chunk grows with N.
+// of 16.  The partial sums are written and read once per sweep, so the chunk grows with N.
+// N alone decides, so each line weighs narrow batches, which short chunks serve, against
+// wide ones.  Sweep and its reduction, us per step, FP64 and packed, at 10 / 100 / 600 RHS on
+// 4 folded rows:
+//   450 rows (120 RHS), 16 against 32: 19.8 20.1; packed 14.2 17.5
+//   1,183 rows, 16 against 32: 13.6 14.4, 54.8 48.8, 308 281; packed 12.6 13.6, 25.1 24.4, 99 88
+//   2,535 rows, 32 against 64: 17.7 21.4, 115 110, 582 551; packed 16.7 20.1, 37.5 39.0, 164 155
+//   5,250 rows, 32, 64, 128: 30 28 35, 215 207 214, 1182 1090 1042; packed 26 25 33, 74 70 75, 353 328 319
+//   6,975 rows, 64 against 128: 35.6 38.4, 267 265, 1429 1346; packed 29.8 35.6, 87 98, 431 426
+//   7,936 rows, 64 against 128: 36.9 40.3, 309 285, 1632 1540; packed 31.3 35.6, 94 104, 487 461
+// (128 throughout: 33, 58, 293 at 1,183 rows and 33, 115, 502 at 2,535, packed 31, 62, 99 and
+// 32, 57, 171: wide FP64 batches of 2,000 to 7,000 rows pay 8 to 16 % of the sweep for it.)
 int64_t gmres_rows_per_chunk(int64_t N) {
     const int64_t least = N < 1024 ? 16 : N < 4096 ? 32 : N < 7000 ? 64 : 128;
     return std::max<int64_t>(least, (N + 2047) / 2048);
