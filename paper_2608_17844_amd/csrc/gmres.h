@@ -57,6 +57,7 @@ struct GmresParams {
     bool packed_basis = false;   // FP32 solves with DCGS2, even R, restart >= 4: basis in the packed 24-bit format
     int* host_count = nullptr;   // pinned host int for the active-count readback
     HostReport host;             // the steps' active counts (restart + 2 slots)
+    double2* partial = nullptr;  // krylov_partial_values: chunk sums, used between applications of the operator only
 };
 
 struct GmresResult {
@@ -67,7 +68,11 @@ struct GmresResult {
 
 int64_t gmres_rows_per_chunk(int64_t N);
 int gmres_nchunk(int64_t N);
-size_t gmres_state_bytes(int64_t N, int R, int m);
+// Complex values that the chunk sums of a solve take (restart m; the short recurrences take no
+// more than m = 1).  They live between two applications of the operator, whose scratch may hold
+// them, and are no part of the state sizes.
+size_t krylov_partial_values(int64_t N, int R, int m);
+size_t gmres_state_bytes(int R, int m);
 
 // Solves A x = b for R independent columns (b, basis of type TB = double2 or
 // float2; x accumulated in FP64).  Vbasis holds (restart+1) vectors of N x R of
@@ -84,19 +89,19 @@ GmresResult gmres_batched(const std::function<void(const TB*, TB*)>& apply, cons
 // of type TB; at most maxit iterations.  cycles is 1, matvecs counts Z and Z^H.
 // Batched COCG on complex symmetric Z with a complex symmetric preconditioner
 // (x = 0 start, stop at ||r|| <= tol ||b||); work: four N x R vectors of TB.
-size_t cocg_state_bytes(int64_t N, int R);
+size_t cocg_state_bytes(int R);
 template <typename TB>
 GmresResult cocg_batched(const std::function<void(const TB*, TB*)>& applyZ,
                          const std::function<void(const TB*, TB*)>& applyMinv, const TB* b, double2* x, TB* work,
-                         int64_t N, int R, double tol, int maxit, const HostReport& host, DevArena& arena,
-                         hipStream_t s);
+                         int64_t N, int R, double tol, int maxit, double2* partial, const HostReport& host,
+                         DevArena& arena, hipStream_t s);
 
-size_t pcg_state_bytes(int64_t N, int R);
+size_t pcg_state_bytes(int R);
 template <typename TB>
 GmresResult pcg_batched(const std::function<void(const TB*, TB*)>& applyN,
                         const std::function<void(const TB*, TB*)>& applyPinv, const TB* b, double2* x, TB* work,
-                        int64_t N, int R, double tol, int maxit, const HostReport& host, DevArena& arena,
-                         hipStream_t s);
+                        int64_t N, int R, double tol, int maxit, double2* partial, const HostReport& host,
+                         DevArena& arena, hipStream_t s);
 
 
 }  // namespace mbt

@@ -1578,14 +1578,13 @@ int gmres_nchunk(int64_t N) { return (int)((N + gmres_rows_per_chunk(N) - 1) / g
 // RHS's sums have the same order whatever the width of its batch.
 int gmres_fold(int64_t N) { return N % 4 == 0 ? 4 : (N % 2 == 0 ? 2 : 1); }
 
-static size_t partial_values(int64_t N, int R, int m) {
+size_t krylov_partial_values(int64_t N, int R, int m) {
     const int F = gmres_fold(N);
-    return std::max((size_t)gmres_nchunk(N) * (2 * m + 2) * R,            // unfolded (CGS2)
+    return std::max((size_t)gmres_nchunk(N) * (2 * m + 2) * R,            // unfolded (CGS2; PCG and COCG take two)
                     (size_t)gmres_nchunk(N / F) * (2 * m + 2) * R * F);   // folded (DCGS2)
 }
 
-size_t gmres_state_bytes(int64_t N, int R, int m) {
-    const int nchunk = gmres_nchunk(N);
+size_t gmres_state_bytes(int R, int m) {
     size_t s = 0;
     s += sizeof(double2) * (size_t)(m + 1) * (m + 1) * R;      // H (column j has m+1 rows, one spare)
     s += sizeof(double) * (size_t)m * R;                       // cs
@@ -1593,8 +1592,6 @@ size_t gmres_state_bytes(int64_t N, int R, int m) {
     s += sizeof(double2) * (size_t)(m + 1) * R;                // g
     s += sizeof(double2) * (size_t)(m + 1) * R * 2;            // h1, h2
     s += sizeof(double2) * (size_t)m * R;                      // y
-    (void)nchunk;
-    s += sizeof(double2) * partial_values(N, R, m);            // partials (of folded rows too)
     s += sizeof(unsigned long long) * (size_t)(m + 3) + 256;   // counters
     s += sizeof(double2) * (size_t)R + 256;                    // reduced squared norms
     s += sizeof(double) * (size_t)R * 4 + sizeof(int) * (size_t)R * 7 + 12 * 256;
@@ -1633,7 +1630,7 @@ GmresResult gmres_batched(const std::function<void(const TB*, TB*)>& apply, cons
     double2* h1 = arena.get<double2>((size_t)(m + 1) * R);
     double2* h2 = arena.get<double2>((size_t)(m + 1) * R);
     double2* y = arena.get<double2>((size_t)m * R);
-    double2* partial = arena.get<double2>(partial_values(N, R, m));
+    double2* partial = prm.partial;
     unsigned long long* counters = arena.get<unsigned long long>(m + 3);   // RHS still iterating, per step
     double2* nrm2 = arena.get<double2>(R);
     double2* Hraw = nullptr;
@@ -2028,16 +2025,15 @@ __global__ void pcg_p_kernel(TB* __restrict__ p, const TB* __restrict__ z, const
 
 }  // namespace
 
-size_t pcg_state_bytes(int64_t N, int R) {
-    return sizeof(double2) * (size_t)gmres_nchunk(N) * R + 2 * sizeof(double2) * (size_t)R +
-           4 * sizeof(double) * (size_t)R + 4 * sizeof(int) * (size_t)R + 16 * 256;
+size_t pcg_state_bytes(int R) {
+    return 2 * sizeof(double2) * (size_t)R + 4 * sizeof(double) * (size_t)R + 4 * sizeof(int) * (size_t)R + 16 * 256;
 }
 
 template <typename TB>
 GmresResult pcg_batched(const std::function<void(const TB*, TB*)>& applyN,
                         const std::function<void(const TB*, TB*)>& applyPinv, const TB* b, double2* x, TB* work,
-                        int64_t N, int R, double tol, int maxit, const HostReport& host, DevArena& arena,
-                         hipStream_t s) {
+                        int64_t N, int R, double tol, int maxit, double2* partial, const HostReport& host,
+                        DevArena& arena, hipStream_t s) {
     const size_t mark = arena.off;
     const int64_t NR = N * R;
     TB* rv = work;
@@ -2054,7 +2050,6 @@ GmresResult pcg_batched(const std::function<void(const TB*, TB*)>& applyN,
     st.conv = arena.get<int>(R);
     st.flag = arena.get<int>(R);
     st.iters = arena.get<int>(R);
-    double2* partial = arena.get<double2>((size_t)gmres_nchunk(N) * R);
     unsigned long long* counter = arena.get<unsigned long long>(2);
     GmresResult res;
     // x = 0, r = b, z = P^{-1} r, p = z, rho = r^H z
@@ -2201,16 +2196,15 @@ __global__ void cocg_p_kernel(TB* __restrict__ p, const TB* __restrict__ z, cons
 
 }  // namespace
 
-size_t cocg_state_bytes(int64_t N, int R) {
-    return 2 * sizeof(double2) * (size_t)gmres_nchunk(N) * R + 2 * sizeof(double2) * (size_t)R +
-           3 * sizeof(double2) * (size_t)R + sizeof(double) * (size_t)R + 4 * sizeof(int) * (size_t)R + 16 * 256;
+size_t cocg_state_bytes(int R) {
+    return 5 * sizeof(double2) * (size_t)R + sizeof(double) * (size_t)R + 4 * sizeof(int) * (size_t)R + 16 * 256;
 }
 
 template <typename TB>
 GmresResult cocg_batched(const std::function<void(const TB*, TB*)>& applyZ,
                          const std::function<void(const TB*, TB*)>& applyMinv, const TB* b, double2* x, TB* work,
-                         int64_t N, int R, double tol, int maxit, const HostReport& host, DevArena& arena,
-                         hipStream_t s) {
+                         int64_t N, int R, double tol, int maxit, double2* partial, const HostReport& host,
+                        DevArena& arena, hipStream_t s) {
     const size_t mark = arena.off;
     const int64_t NR = N * R;
     TB* rv = work;
@@ -2227,7 +2221,6 @@ GmresResult cocg_batched(const std::function<void(const TB*, TB*)>& applyZ,
     st.conv = arena.get<int>(R);
     st.flag = arena.get<int>(R);
     st.iters = arena.get<int>(R);
-    double2* partial = arena.get<double2>(2 * (size_t)gmres_nchunk(N) * R);
     unsigned long long* counter = arena.get<unsigned long long>(2);
     GmresResult res;
     // x = 0, r = b, z = M^{-1} r, p = z, rho = r^T z
@@ -2267,21 +2260,21 @@ GmresResult cocg_batched(const std::function<void(const TB*, TB*)>& applyZ,
 
 template GmresResult cocg_batched<double2>(const std::function<void(const double2*, double2*)>&,
                                            const std::function<void(const double2*, double2*)>&, const double2*,
-                                           double2*, double2*, int64_t, int, double, int, const HostReport&, DevArena&,
-                                           hipStream_t);
+                                           double2*, double2*, int64_t, int, double, int, double2*, const HostReport&,
+                                           DevArena&, hipStream_t);
 template GmresResult cocg_batched<float2>(const std::function<void(const float2*, float2*)>&,
                                           const std::function<void(const float2*, float2*)>&, const float2*, double2*,
-                                          float2*, int64_t, int, double, int, const HostReport&, DevArena&,
-                                           hipStream_t);
+                                          float2*, int64_t, int, double, int, double2*, const HostReport&,
+                                           DevArena&, hipStream_t);
 
 template GmresResult pcg_batched<double2>(const std::function<void(const double2*, double2*)>&,
                                           const std::function<void(const double2*, double2*)>&, const double2*,
-                                          double2*, double2*, int64_t, int, double, int, const HostReport&, DevArena&,
-                                           hipStream_t);
+                                          double2*, double2*, int64_t, int, double, int, double2*, const HostReport&,
+                                           DevArena&, hipStream_t);
 template GmresResult pcg_batched<float2>(const std::function<void(const float2*, float2*)>&,
                                          const std::function<void(const float2*, float2*)>&, const float2*, double2*,
-                                         float2*, int64_t, int, double, int, const HostReport&, DevArena&,
-                                           hipStream_t);
+                                         float2*, int64_t, int, double, int, double2*, const HostReport&,
+                                           DevArena&, hipStream_t);
 
 template GmresResult gmres_batched<double2>(const std::function<void(const double2*, double2*)>&, const double2*,
                                             double2*, double2*, int64_t, int, const GmresParams&, DevArena&, hipStream_t);

@@ -684,18 +684,25 @@ template <typename T> static void apply_rhs(const OpV<T>& o, const cplx<T>* v, c
 }
 
 // ------------------------------------------------------------------ solve drivers
+// Complex values of the two spectral buffers (FP64-sized, shared by all precisions).  The chunk
+// sums of the Krylov sweeps lie in them: they are used between two applications of the
+// operator, when no spectrum is held.
+static size_t spectral_values(const Geom& g, int R, int m) {
+    return std::max(2 * (size_t)g.bins() * g.M * R, krylov_partial_values(g.N, R, m));
+}
+
 size_t solve_bytes(const Geom& g, int R, const mbt_solve_opts& o) {
     const size_t NR = (size_t)g.N * R;
     const size_t tb = o.prec == MBT_FP64 ? 16 : 8;
     size_t b = 0;
     b += (size_t)std::max(o.restart + 1, 5) * NR * tb; // Krylov basis (PCG: four work vectors and b)
-    b += 2 * (size_t)g.bins() * g.M * R * 16;          // spectral buffers (FP64-sized, shared)
+    b += spectral_values(g, R, o.restart) * 16;        // spectral buffers, chunk sums
     b += NR * 16;                                      // operator temp
     b += NR * tb;                                      // preconditioned rhs
     b += 2 * NR * 16;                                  // V, X
     b += NR * 16;                                      // FP64 residual
     if (o.prec != MBT_FP64) b += NR * 16 + NR * 8;     // d, r32
-    b += std::max(gmres_state_bytes(g.N, R, o.restart), std::max(pcg_state_bytes(g.N, R), cocg_state_bytes(g.N, R)));
+    b += std::max(gmres_state_bytes(R, o.restart), std::max(pcg_state_bytes(R), cocg_state_bytes(R)));
     b += (size_t)R * 64 + ((size_t)g.N / 256 + 2) * R * 8 + (size_t)g.P * R * 16 + (1 << 20);
     b += margin_scratch_bytes(g, R);
     return b;
@@ -752,8 +759,9 @@ SolveOut solve_rhs(const OpData& op, const mbt_solve_opts& o, const double2* V, 
     out.iters.assign(R, 0);
     out.conv.assign(R, 0);
     out.flag.assign(R, 0);
-    void* Xh = arena.get<double2>((size_t)g.bins() * g.M * R);
-    void* Yh = arena.get<double2>((size_t)g.bins() * g.M * R);
+    double2* spectra = arena.get<double2>(spectral_values(g, R, m));
+    void* Xh = spectra;
+    void* Yh = spectra + (size_t)g.bins() * g.M * R;
     double2* tmp = arena.get<double2>(NR);
     void* mscr = g.Nc > 0 ? arena.get<char>(margin_scratch_bytes(g, R)) : nullptr;
     GmresParams prm;
@@ -762,6 +770,7 @@ SolveOut solve_rhs(const OpData& op, const mbt_solve_opts& o, const double2* V, 
     prm.matvecs_per_apply = o.pc == MBT_PC_NORMAL_EQ ? 2 : 1;
     prm.host_count = wk.host_count;
     prm.host = HostReport{wk.host_slots, &wk.host_gen};
+    prm.partial = spectra;
     prm.dcgs2 = !(o.flags & MBT_FLAG_CGS2);
     prm.packed_basis = o.prec != MBT_FP64 && !(o.flags & MBT_FLAG_FP32_BASIS);
     std::vector<double> vn;
@@ -787,7 +796,7 @@ SolveOut solve_rhs(const OpData& op, const mbt_solve_opts& o, const double2* V, 
             std::function<void(const double2*, double2*)> fp = [&](const double2* x, double2* y) {
                 pinv<double>(ov, x, y);
             };
-            gr = pcg_batched<double2>(fn, fp, b, X, basis, g.N, R, o.tol, pcg_maxit, prm.host, arena, s);
+            gr = pcg_batched<double2>(fn, fp, b, X, basis, g.N, R, o.tol, pcg_maxit, prm.partial, prm.host, arena, s);
         } else if (use_cocg) {
             // Z I = V with M = P_K, both complex symmetric
             std::function<void(const double2*, double2*)> fz = [&](const double2* x, double2* y) {
@@ -796,7 +805,7 @@ SolveOut solve_rhs(const OpData& op, const mbt_solve_opts& o, const double2* V, 
             std::function<void(const double2*, double2*)> fm = [&](const double2* x, double2* y) {
                 pinv<double>(ov, x, y);
             };
-            gr = cocg_batched<double2>(fz, fm, V, X, basis, g.N, R, o.tol, pcg_maxit, prm.host, arena, s);
+            gr = cocg_batched<double2>(fz, fm, V, X, basis, g.N, R, o.tol, pcg_maxit, prm.partial, prm.host, arena, s);
         } else {
             apply_rhs<double>(ov, V, b);
             out.matvecs += o.pc == MBT_PC_NORMAL_EQ ? 1 : 0;
@@ -895,7 +904,7 @@ SolveOut solve_rhs(const OpData& op, const mbt_solve_opts& o, const double2* V, 
                 std::function<void(const float2*, float2*)> fp = [&](const float2* x, float2* y) {
                     pinv<float>(ov32, x, y);
                 };
-                gr = pcg_batched<float2>(fn, fp, b32, d, basis, g.N, R, prm.tol, pcg_maxit, prm.host, arena, s);
+                gr = pcg_batched<float2>(fn, fp, b32, d, basis, g.N, R, prm.tol, pcg_maxit, prm.partial, prm.host, arena, s);
             } else if (use_cocg) {
                 std::function<void(const float2*, float2*)> fz = [&](const float2* x, float2* y) {
                     zmul<float>(ov32, 0, x, y);
@@ -903,7 +912,7 @@ SolveOut solve_rhs(const OpData& op, const mbt_solve_opts& o, const double2* V, 
                 std::function<void(const float2*, float2*)> fm = [&](const float2* x, float2* y) {
                     pinv<float>(ov32, x, y);
                 };
-                gr = cocg_batched<float2>(fz, fm, r32, d, basis, g.N, R, prm.tol, pcg_maxit, prm.host, arena, s);
+                gr = cocg_batched<float2>(fz, fm, r32, d, basis, g.N, R, prm.tol, pcg_maxit, prm.partial, prm.host, arena, s);
             } else {
                 apply_rhs<float>(ov32, r32, b32);
                 out.matvecs += o.pc == MBT_PC_NORMAL_EQ ? 1 : 0;
