@@ -230,11 +230,11 @@ __global__ __launch_bounds__(ROWS * TPR) void gj_small_kernel(const double2* __r
 // winner.  What workgroup 0 reads and writes is compact and column by column (column
 // pieces n rows apart would cost a cache line per value): the columns that it
 // factors are handed over by the launch before, and the factored ones are copied
-// into the matrix by the launch after.  A launch takes 11.4 us at n = 120, 17.7 at 512
-// and 24 at 1000 and 1024, of which workgroup 0 needs 10.9, 16.5 and 21.3; factoring
+// into the matrix by the launch after.  A launch takes 12.1 us at n = 120, 16.0 at 512
+// and 25 at 1000 and 1024, all but 0.5 to 3 us of it workgroup 0's chain; factoring
 // and update in launches of their own took 23 and 42 us at 120 and 1024.  A CU holds one
 // such workgroup: strips of four columns keep all of a launch resident up to 1024
-// rows (eight take 19.8 us at 512 rows, half the chip idle; a 257th workgroup, the next
+// rows (eight took 19.8 against 17.7 us at 512 rows, half the chip idle; a 257th workgroup, the next
 // panel's strips among them, 30 us at 1024), strips of eight up to 2048.
 template <int NB> struct GjPanel {
     double2* L;    // [NB][n]: multiplier of row i at step c, 0 for the step's pivot row
@@ -468,8 +468,8 @@ __global__ void permute_cols_kernel(const double2* __restrict__ in, double2* __r
 }
 
 // The row interchanges of the elimination become column interchanges of the
-// inverse, last first; one thread (n <= 1024 swaps).  An out-of-range pivot
-// marks the matrix singular.
+// inverse, last first; one thread, n swaps (a small part of the n launches before it).
+// An out-of-range pivot marks the matrix singular.
 __global__ void perm_from_pivots_kernel(const int* __restrict__ piv, int* __restrict__ src, int n,
                                         int* __restrict__ flag) {
     if (threadIdx.x != 0 || blockIdx.x != 0) return;
@@ -583,11 +583,12 @@ void gj_panels(double2* A, double2* out, int n, int* piv, int* flag, hipStream_t
 namespace {
 
 // The elimination and the inverse into out, all on the device; flag receives 1 if a
-// pivot is zero or not finite.
+// pivot's squared magnitude is zero or NaN (an infinite one passes, as its reciprocal 0 or NaN).
 // Each form takes what its registers hold (64 rows x 4 columns a thread; panel rows per
 // thread: one to 512, two to 1024, four beyond, so that the factoring workgroup has no
 // more waves to gather per step than it needs; with the copies 512 rows take 2.98 ms at
-// two rows a thread and 2.80 at one, 1024 the same with 1,024 threads).
+// two rows a thread and 2.80 at one, 1024 the same with 1,024 threads).  Lattices have up to
+// 4,096 ports; above, only callers of the bare inverse get there.
 void gj_on_device(double2* A, double2* out, int n, double2* colbuf, int* piv, int* flag, hipStream_t s) {
     hipLaunchKernelGGL(clear_flag_kernel, dim3(1), dim3(64), 0, s, flag);
     if (n <= 32) {

@@ -64,3 +64,20 @@ def test_pivot_between_nearly_equal_rows(ctx, n):
         X = mbt.mbt_dbg_inverse(ctx, A.T).T   # columns are the rows of the elimination
         assert (X[0, 0], X[n - 1, 0]) == want, (c, swapped)
         tried[swapped] += 1
+
+
+@pytest.mark.parametrize("n", [2048, 3073, 4096, 4097])
+def test_large_inverses(ctx, n):
+    """The largest sizes of the panelled forms with every row of a thread in use, a size between
+    them, and one past them (column by column), by their residual on random vectors:
+    ||A X v - v|| <= 1e-11 n ||v|| for a well-conditioned random matrix; a zero column is refused."""
+    from paper_2608_17844_amd import mbt
+    print("n=%d" % n, flush=True)
+    rng = np.random.default_rng(n)
+    A = rng.standard_normal((n, n)) + 1j * rng.standard_normal((n, n)) + 2 * np.eye(n)
+    v = rng.standard_normal((n, 4))
+    r = A @ (mbt.mbt_dbg_inverse(ctx, A) @ v) - v
+    assert np.linalg.norm(r) <= 1e-11 * n * np.linalg.norm(v)
+    A[:, n // 3] = 0.0
+    with pytest.raises(mbt.MbtError):
+        mbt.mbt_dbg_inverse(ctx, A)
