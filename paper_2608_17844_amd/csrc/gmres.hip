@@ -334,7 +334,10 @@ __global__ __launch_bounds__(NW * 64, (std::is_same<TV, p24x2>::value && G <= 4 
                                                              const TB* __restrict__ w, int64_t N, int R,
                                                              int64_t rows_per_chunk, double2* __restrict__ partial) {
     static_assert(kDotRows % RU == 0, "the stage holds whole groups of rows");
-    constexpr bool PF = G * RPL <= 2;    // the next rows of V are loaded while these are used
+    // The next rows of V are loaded while these are used: where a wave has few, and for pairs
+    // of FP32 columns, which would otherwise wait at three waves a SIMD for each row (7,936 folded
+    // rows of 1,024 RHS: 1,317 us per sweep of 17 to 32 vectors, 2,190 without).
+    constexpr bool PF = G * RPL <= 2 || (sizeof(TV) == 8 && RPL == 2);
     // blockIdx.z takes NW * G vectors of the launch's nv
     i0 += blockIdx.z * NW * G;
     nv = min(nv - (int)blockIdx.z * NW * G, NW * G);
@@ -668,8 +671,9 @@ template <typename TB> bool dots_split(int64_t groups) {
 }
 
 // rows whose loads a wave of G vectors issues together: eight loads in flight, or as many as
-// fit beside the accumulators (two RHS per lane) without spilling
-template <int NW, int G, int RPL> constexpr int dot_ru() {
+// fit beside the accumulators (two RHS per lane) and the rows loaded ahead without spilling
+template <typename TV, int NW, int G, int RPL> constexpr int dot_ru() {
+    if (sizeof(TV) == 8 && RPL == 2 && G > 1) return G == 2 ? 2 : 1;
     return G * RPL >= 8 ? 1 : (RPL == 2 && NW == 4) ? 2 : (RPL == 2 && G == 1) ? 4 : 8 / G;
 }
 
@@ -677,7 +681,7 @@ template <typename TB, typename TV, int NW, int G, int RPL, bool HASW>
 void launch_dcgs2_dots_cfg(const TV* V, int64_t vs, int k, int i0, int nv, const TB* u, const TB* w, int64_t N, int R,
                            int64_t rpc, int nchunk, double2* partial, hipStream_t s) {
     const dim3 grid((unsigned)((R / RPL + 63) / 64), (unsigned)nchunk, (unsigned)std::max(1, (nv + NW * G - 1) / (NW * G)));
-    hipLaunchKernelGGL((dcgs2_dots_kernel<TB, TV, NW, G, RPL, HASW, dot_ru<NW, G, RPL>()>), grid, dim3(NW * 64), 0, s, V, vs, k,
+    hipLaunchKernelGGL((dcgs2_dots_kernel<TB, TV, NW, G, RPL, HASW, dot_ru<TV, NW, G, RPL>()>), grid, dim3(NW * 64), 0, s, V, vs, k,
                        i0, nv, u, w, N, R, rpc, partial);
     MBT_LAUNCH_CHECK();
 }
