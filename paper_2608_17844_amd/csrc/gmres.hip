@@ -334,10 +334,11 @@ __global__ __launch_bounds__(NW * 64, (std::is_same<TV, p24x2>::value && G <= 4 
                                                              const TB* __restrict__ w, int64_t N, int R,
                                                              int64_t rows_per_chunk, double2* __restrict__ partial) {
     static_assert(kDotRows % RU == 0, "the stage holds whole groups of rows");
-    // The next rows of V are loaded while these are used: where a wave has few, and for pairs
-    // of FP32 columns, which would otherwise wait at three waves a SIMD for each row (7,936 folded
-    // rows of 1,024 RHS: 1,317 us per sweep of 17 to 32 vectors, 2,190 without).
-    constexpr bool PF = G * RPL <= 2 || (sizeof(TV) == 8 && RPL == 2);
+    // The next rows of V are loaded while these are used, but where the registers are short:
+    // the packed basis with two vectors a wave or more, eight vectors.  Sweeps of 17 to 32 vectors
+    // without it: FP32 pairs (7,936 folded rows of 1,024 RHS) 2,190 instead of 1,317 us, single
+    // FP32 columns (8,959 of 289) 254 instead of 135, FP64 (11,625 of 258) 271 instead of 263.
+    constexpr bool PF = G * RPL <= 2 || (sizeof(TV) == 8 && RPL == 2) || (!std::is_same<TV, p24x2>::value && G == 4);
     // blockIdx.z takes NW * G vectors of the launch's nv
     i0 += blockIdx.z * NW * G;
     nv = min(nv - (int)blockIdx.z * NW * G, NW * G);
@@ -674,6 +675,7 @@ template <typename TB> bool dots_split(int64_t groups) {
 // fit beside the accumulators (two RHS per lane) and the rows loaded ahead without spilling
 template <typename TV, int NW, int G, int RPL> constexpr int dot_ru() {
     if (sizeof(TV) == 8 && RPL == 2 && G > 1) return G == 2 ? 2 : 1;
+    if (sizeof(TV) == 16 && G == 4) return 1;
     return G * RPL >= 8 ? 1 : (RPL == 2 && NW == 4) ? 2 : (RPL == 2 && G == 1) ? 4 : 8 / G;
 }
 
@@ -1566,7 +1568,8 @@ inline unsigned ew_grid(int64_t n) {
 //   6,975 rows, 64 against 128: 35.6 38.4, 267 265, 1429 1346; packed 29.8 35.6, 87 98, 431 426
 //   7,936 rows, 64 against 128: 36.9 40.3, 309 285, 1632 1540; packed 31.3 35.6, 94 104, 487 461
 // (128 throughout: 33, 58, 293 at 1,183 rows and 33, 115, 502 at 2,535, packed 31, 62, 99 and
-// 32, 57, 171: wide FP64 batches of 2,000 to 7,000 rows pay 8 to 16 % of the sweep for it.)
+// 32, 57, 171: wide FP64 batches of 2,000 to 7,000 rows pay 8 to 16 % of the sweep for it, and the
+// update after it up to 8 %, as more partial sums pass through the last-level cache.)
 int64_t gmres_rows_per_chunk(int64_t N) {
     const int64_t least = N < 1024 ? 16 : N < 4096 ? 32 : N < 7000 ? 64 : 128;
     return std::max<int64_t>(least, (N + 2047) / 2048);
